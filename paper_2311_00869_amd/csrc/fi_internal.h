@@ -118,8 +118,6 @@ enum : int {
   C_NISO = 5,       // isolated vertices (create)
   C_NANCH = 6,      // anchors of non-trivial components (create)
   C_FLAGS = 7,      // validation flags (create)
-  C_BAR = 16,       // grid barrier: arrivals (own 128-byte line)
-  C_GEN = 32,       // grid barrier: generation (own line)
   C_ACC = 48,       // tree accumulators: switches, key_hi, key_lo
   C_RING = 64,      // per-level frontier counters, 4 slots x 4 words
   C_UNIT = 96,      // per-block work-unit ticket broadcast (unused on host)
@@ -179,7 +177,7 @@ enum : int { kSamplerBfs = 0, kSamplerRdfs = 1, kSamplerHybrid = 2, kSamplerKrus
 // ----------------------------------------------------------------- layout
 constexpr int kGridSlots = 8;  // trees in flight on the whole-grid path (max)
 constexpr int kGridCtlWords = 128;          // control words per tree slot
-constexpr int kGridBarWords = 32 + 16 * 512;  // barrier words per tree slot
+constexpr int kGridBarWords = 32;             // barrier words per tree slot (group_sync)
 
 struct Layout {
   size_t row_ptr, adj, edges, cedges, comp, word_comp, word_mask, word_main, anchors, tmp, cloud, ctl;

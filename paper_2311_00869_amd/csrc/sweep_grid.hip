@@ -43,7 +43,6 @@ constexpr int kStage = 2048;        // LDS staging entries for next-level lists
 constexpr int kBUWordsPerWave = 4;  // bottom-up words per wave per unit
 constexpr int kWordCost = 16;       // bottom-up cost of one word, in edge visits
 constexpr int kTDCost = 4;          // top-down cost of one frontier edge
-constexpr int kGroup = kBarGroup;   // workgroups per barrier group
 
 // control words of slot s: gctl + s * kSlotWords
 //   [r * 8 + k], r = level % 4: k = 0 light count, 1 heavy (count << 32 |
@@ -51,8 +50,7 @@ constexpr int kGroup = kBarGroup;   // workgroups per barrier group
 //   [32 + 8 r]: work ticket of level slot r
 //   [64 .. 66]: switches, key_hi, key_lo accumulators
 constexpr int kSlotWords = kGridCtlWords;
-// barrier words of slot s: bar + s * kBarWords: [0] generation, [16] root,
-// [32 + 16 g] group g
+// barrier words of slot s: bar + s * kBarWords (group_sync's)
 constexpr int kBarWords = kGridBarWords;
 
 struct GridArgs {
@@ -110,11 +108,6 @@ __device__ __forceinline__ void aadd64(uint64_t* p, uint64_t v) {
 }
 __device__ __forceinline__ uint32_t bit_at(const uint64_t* words, uint32_t v) {
   return (uint32_t)(words[v >> 6] >> (v & 63)) & 1u;
-}
-
-// Barrier among the `nb` workgroups of one sub-grid (local ranks 0..nb-1).
-__device__ __forceinline__ void sub_sync(uint64_t* bar, uint32_t rank, uint32_t nb) {
-  group_sync(bar, rank, nb);
 }
 
 // Move the LDS staging list into a global list (one reservation per block).
@@ -267,7 +260,7 @@ __global__ void __launch_bounds__(NT, 4) k_sweep_grid(DevGraph G, GridArgs A) {
       }
       if (cur >= 0 && lane == 0) amin64(rootkey + cur, cmin);
     }
-    sub_sync(bar, rank, nb);
+    group_sync(bar, nb);
 
     // ---- P1: the roots form level 0 (lists and frontier bits)
     {
@@ -302,7 +295,7 @@ __global__ void __launch_bounds__(NT, 4) k_sweep_grid(DevGraph G, GridArgs A) {
         aadd64(ring0 + 3, sh.deg);
       }
     }
-    sub_sync(bar, rank, nb);
+    group_sync(bar, nb);
 
     // ---- P2: levels
     for (uint32_t L = 0;; ++L) {
@@ -336,7 +329,7 @@ __global__ void __launch_bounds__(NT, 4) k_sweep_grid(DevGraph G, GridArgs A) {
           const int32_t u = i < sh.nl ? ql[i] : qh[i - sh.nl].x;
           if (pw[u] & 1) aor64(sbs + (u >> 6), 1ull << (u & 63));
         }
-        sub_sync(bar, rank, nb);
+        group_sync(bar, nb);
       } else if (sh.mode == 1 && sh.prev == 2) {
         // top-down after bottom-up: list the frontier bitmap
         for (int64_t c0 = (int64_t)rank * (NT / 64); c0 < nw; c0 += (int64_t)nb * (NT / 64)) {
@@ -350,7 +343,7 @@ __global__ void __launch_bounds__(NT, 4) k_sweep_grid(DevGraph G, GridArgs A) {
           if (sh.qn > kStage - NT) stage_flush<NT>(sh, ql, ring);
         }
         stage_flush<NT>(sh, ql, ring);
-        sub_sync(bar, rank, nb);
+        group_sync(bar, nb);
         if (tid == 0) plan_level<NT>(sh, ctl, G.nnz, nw, L, true);
         __syncthreads();
       }
@@ -533,7 +526,7 @@ __global__ void __launch_bounds__(NT, 4) k_sweep_grid(DevGraph G, GridArgs A) {
         __syncthreads();
       }
       if (tid == 0) sh.prev = sh.mode;
-      sub_sync(bar, rank, nb);
+      group_sync(bar, nb);
     }
 
     // ---- P3: canonical words, key terms and the exact count
@@ -576,7 +569,7 @@ __global__ void __launch_bounds__(NT, 4) k_sweep_grid(DevGraph G, GridArgs A) {
         if (klo) aadd64(ctl + 66, klo);
       }
     }
-    sub_sync(bar, rank, nb);
+    group_sync(bar, nb);
 
     // ---- P4: insert the tree
     if (rank == 0 && tid == 0) {
@@ -585,7 +578,7 @@ __global__ void __launch_bounds__(NT, 4) k_sweep_grid(DevGraph G, GridArgs A) {
       if (A.tree_switches) A.tree_switches[t - A.t0] = s0;
     }
     // the next tree clears the control words; finish reading them first
-    sub_sync(bar, rank, nb);
+    group_sync(bar, nb);
   }
 }
 
@@ -598,7 +591,7 @@ hipError_t launch_nt(fi_graph* g, const GridArgs& a, hipStream_t s) {
   const int maxg = per_cu * g->cu_count;
   int grid = g->sched.grid > 0 ? std::min(g->sched.grid, maxg) : std::min(maxg, 2 * g->cu_count);
   grid = std::max(grid, a.batch);
-  if (grid > maxg || (grid + a.batch - 1) / a.batch > kGroup * 512) return hipErrorInvalidConfiguration;
+  if (grid > maxg) return hipErrorInvalidConfiguration;
   DevGraph G = g->dg;
   GridArgs A = a;
   void* args[] = {(void*)&G, (void*)&A};

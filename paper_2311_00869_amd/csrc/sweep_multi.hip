@@ -373,7 +373,7 @@ __global__ void __launch_bounds__(NT) k_sweep_multi(DevGraph G, MArgs A) {
       sh.qn = 0;
       sh.qn2 = 0;
     }
-    group_sync(A.bar, rank, nb);
+    group_sync(A.bar, nb);
     log_phase(A, rank, kPhReset, 0);
 
     // ---- roots: the minimum key of every component, per tree; they form
@@ -400,7 +400,7 @@ __global__ void __launch_bounds__(NT) k_sweep_multi(DevGraph G, MArgs A) {
         }
         mflush<NT>(sh, A.pl, A.pm, A.ctl + cF(0));
       }
-      group_sync(A.bar, rank, nb);
+      group_sync(A.bar, nb);
       log_phase(A, rank, kPhRoots, 0);
       for (int64_t it = gwave; it < (int64_t)A.nbig * 64 * W; it += nwaves) {
         const int t = (int)(it % (64 * W));
@@ -417,7 +417,7 @@ __global__ void __launch_bounds__(NT) k_sweep_multi(DevGraph G, MArgs A) {
         if (fin) aadd64(ctl + cUNF, (uint64_t)0 - fin);
       }
     }
-    group_sync(A.bar, rank, nb);
+    group_sync(A.bar, nb);
     log_phase(A, rank, kPhBigRoots, 0);
 
     // ---- levels
@@ -627,7 +627,7 @@ __global__ void __launch_bounds__(NT) k_sweep_multi(DevGraph G, MArgs A) {
         }
       }
       mflush<NT>(sh, pln, pmn, rf);
-      group_sync(A.bar, rank, nb);
+      group_sync(A.bar, nb);
       log_phase(A, rank, kPhLists, L);
 
       // ---- phase 2: pull
@@ -762,7 +762,7 @@ __global__ void __launch_bounds__(NT) k_sweep_multi(DevGraph G, MArgs A) {
         }
       }
       const uint32_t nheavy = uni(sh.nh);
-      group_sync(A.bar, rank, nb);
+      group_sync(A.bar, nb);
       log_phase(A, rank, kPhPull, L);
 
       // ---- phase 3: split rows take their minima (one wave per row)
@@ -790,7 +790,7 @@ __global__ void __launch_bounds__(NT) k_sweep_multi(DevGraph G, MArgs A) {
           }
           if (fin) aadd64(ctl + cUNF, (uint64_t)0 - fin);
         }
-        group_sync(A.bar, rank, nb);
+        group_sync(A.bar, nb);
         log_phase(A, rank, kPhSplit, L);
       }
     }
@@ -917,7 +917,7 @@ __global__ void __launch_bounds__(NT) k_sweep_multi(DevGraph G, MArgs A) {
         aadd64(ctl + cACC + 4 * t + 2, sh.tacc[2][t]);
       }
     }
-    group_sync(A.bar, rank, nb);
+    group_sync(A.bar, nb);
     log_phase(A, rank, kPhCountKey, 0);
 
     // ---- the trees of the pass enter the cloud
@@ -930,7 +930,7 @@ __global__ void __launch_bounds__(NT) k_sweep_multi(DevGraph G, MArgs A) {
       if (A.tree_switches) A.tree_switches[t - A.t0] = S;
     }
     // the next pass clears the control words; finish reading them first
-    group_sync(A.bar, rank, nb);
+    group_sync(A.bar, nb);
     log_phase(A, rank, kPhInsert, 0);
   }
 }
@@ -949,7 +949,6 @@ hipError_t launch_mt(fi_graph* g, const MArgs& a, hipStream_t s) {
   const int64_t work = (int64_t)g->dg.n + g->dg.m / 2;
   const int auto_grid = (int)std::max<int64_t>(64, std::min<int64_t>(maxg, work / 16384) & ~7);
   int grid = std::min(g->sched.grid > 0 ? g->sched.grid : auto_grid, maxg);
-  if (grid > kBarGroup * 512) grid = kBarGroup * 512;
   DevGraph G = g->dg;
   MArgs A = a;
   void* args[] = {(void*)&G, (void*)&A};
