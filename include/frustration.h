@@ -439,21 +439,24 @@ int fi_bcloud_stats(fi_bcloud* c, int64_t* out_trees, int64_t* out_dropped, void
 /* ---------------------------------------------------------------- schedule */
 
 /* How a sweep is laid on the GPU.  Every schedule gives bit-identical
- * results; fi_set_schedule only changes speed.  path: 0 = automatic (path 1
- * when the tree fits LDS, 2 while n + m/2 <= 135,000 with m undirected
- * edges, else 5; the block is then chosen from the graph's size and the
- * sampler, the block field is ignored, and a grid of 0 is sized to the
- * graph), 1 = one workgroup per tree with the tree state in LDS
+ * results; fi_set_schedule only changes speed.  path: 0 = automatic (from the
+ * graph's size n + m/2 with m undirected edges, its BFS depth, the sampler and
+ * the call's tree count: path 1 when the tree fits LDS and the trees are few
+ * or the graph below 20,000, path 2 for deep graphs up to 135,000, else 4 or
+ * 5; the block is chosen too, the block field is ignored, and a grid of 0 is
+ * sized to the graph), 1 = one workgroup per tree with the tree state in LDS
  * (n <= 12,000), 2 = one workgroup per tree with the tree state in workspace memory
  * (n <= 1,000,000), 3 = the whole grid on a few trees at a time
- * (persistent cooperative kernel, any n), 4 = the whole grid on 64 trees
- * at once with one bit per tree in each field of a per-vertex record
- * (cooperative, any n; fi_tree_state falls back to path 3), 5 = the same
- * with 128 trees at once (two-word fields; a vertex's record is one 64-byte
- * line, so a pass moves about as many lines as a pass of 64; not for batch
- * handles).  block: threads per workgroup (256, 512 or 1024); grid:
- * workgroups (0 = default; on paths 4 and 5 one per 16,384 of n + m/2, a
- * multiple of 8, at least 64, at most what can be resident); heavy: degree above
+ * (persistent cooperative kernel, any n), 4 = passes of 64 trees at once with
+ * one bit per tree in each field of a per-vertex record (cooperative, any n;
+ * fi_tree_state falls back to path 3), 5 = the same with 128 trees at once
+ * (two-word fields; a vertex's record is one 64-byte line, so a pass moves
+ * about as many lines as a pass of 64; not for batch handles).  block: threads
+ * per workgroup (256, 512 or 1024); grid: workgroups (0 = default; on paths 4
+ * and 5 up to eight passes in flight share the chip, as many as the graph's
+ * size and the trees make worthwhile, and a pass alone takes one workgroup
+ * per 1,024 of n + m/2, at least 64, at most what can be resident; a grid
+ * given runs one pass at a time); heavy: degree above
  * which a top-down frontier vertex is expanded by several workgroups
  * (path 3, >= 32); batch: trees in flight on path 3 (1 .. 8). */
 typedef struct {
@@ -481,6 +484,7 @@ int fi_prof_read(fi_graph* g, int kernel, double* out_ms, int64_t* out_launches)
  * BFS level, time): d_log[0] counts the records (the caller zeroes it),
  * record i sits at d_log[2 + 2 i] and d_log[3 + 2 i], records past cap are
  * dropped, and time is the GPU's constant-rate real-time counter (100 MHz).
+ * While it is on, passes run one at a time.
  * Phases: 0 launch start, 1 reset, 2 root search, 3 big-component roots,
  * 4 lists of a level, 5 pull of a level, 6 split rows of a level, 7 counts
  * and keys, 8 cloud insert.  NULL turns the log off. */

@@ -499,11 +499,8 @@ __global__ void __launch_bounds__(NT) k_batch_multi(BatchMArgs B) {
   const size_t nm = (size_t)B.n_max;
   // vertex records of one word per field, then the unfinished-vertex bitmap
   mt::MState S;
-  S.nbw[0] = (uint64_t*)slot;
-  S.stw = S.nbw[0] + 1;
-  S.nbw[1] = S.nbw[0] + 2;
-  S.vis = S.nbw[0] + 3;
-  S.unf = S.nbw[0] + mt::kRecFields * nm;
+  S.rec = (uint64_t*)slot;
+  S.unf = S.rec + mt::kRecFields * nm;
   S.cand = nullptr;
   S.stc = nullptr;
   uint64_t* table = S.unf + (nm / 64 + 2);
@@ -540,7 +537,7 @@ __global__ void __launch_bounds__(NT) k_batch_multi(BatchMArgs B) {
     const KeyMix km = key_mix(tree_salt(B.seed, (uint64_t)(tb + lane)));
 
     // ---- reset
-    for (int32_t v = tid; v < mt::kRecFields * n; v += NT) S.nbw[0][v] = 0;
+    for (int32_t v = tid; v < mt::kRecFields * n; v += NT) S.rec[v] = 0;
     for (int32_t w = wave; w < nw; w += NW) {
       const int32_t v = w * 64 + lane;
       const uint64_t m = __ballot(v < n && rp[v + 1] > rp[v]);
@@ -592,8 +589,8 @@ __global__ void __launch_bounds__(NT) k_batch_multi(BatchMArgs B) {
           const uint64_t msk = __ballot(ok && r == r1);
           rem &= ~msk;
           if (lane == 0) {
-            mt::stw_<1>(S.nbw[0], r1, mt::TW<1>{{msk}});
-            mt::stw_<1>(S.vis, r1, mt::TW<1>{{msk}});
+            mt::stw_<1>(S.nbw<1>(0), r1, mt::TW<1>{{msk}});
+            mt::stw_<1>(S.vis<1>(), r1, mt::TW<1>{{msk}});
             if (msk == valid) mt::aand64(S.unf + (r1 >> 6), ~(1ull << (r1 & 63)));
           }
         }
@@ -630,10 +627,10 @@ __global__ void __launch_bounds__(NT) k_batch_multi(BatchMArgs B) {
           const int j = __builtin_ctzll(big);
           big &= big - 1;
           const int32_t vj = w * 64 + j;
-          const mt::TW<1> want = mt::uni_w(mt::and_not(mt::TW<1>{{valid}}, mt::ldw<1>(S.vis, vj)));
+          const mt::TW<1> want = mt::uni_w(mt::and_not(mt::TW<1>{{valid}}, mt::ldw<1>(S.vis<1>(), vj)));
           uint64_t best = kUnvisited;
-          if (want.w[0]) mt::pull_edges_w<1>(G.adj, S.nbw[pp], S.stw, rp[vj], rp[vj + 1], want, &km, &best);
-          mt::settle_w<1>(S, vj, mt::ldw<1>(S.vis, vj), mt::ldw<1>(S.stw, vj), rp[vj + 1] - rp[vj], &best,
+          if (want.w[0]) mt::pull_edges_w<1>(G.adj, S.nbw<1>(pp), S.stw<1>(), rp[vj], rp[vj + 1], want, &km, &best);
+          mt::settle_w<1>(S, vj, mt::ldw<1>(S.vis<1>(), vj), mt::ldw<1>(S.stw<1>(), vj), rp[vj + 1] - rp[vj], &best,
                           p, mt::TW<1>{{valid}}, cnt, deg, fin);
         }
       }
@@ -666,7 +663,7 @@ __global__ void __launch_bounds__(NT) k_batch_multi(BatchMArgs B) {
         uint64_t x = 0;
         if (e < G.m) {
           const uint2 uv = G.edges[e];
-          x = mt::ldw<1>(S.stw, uv.x).w[0] ^ mt::ldw<1>(S.stw, uv.y & kVertexMask).w[0];
+          x = mt::ldw<1>(S.stw<1>(), uv.x).w[0] ^ mt::ldw<1>(S.stw<1>(), uv.y & kVertexMask).w[0];
           if (uv.y >> 31) x = ~x;
         }
 #pragma unroll
@@ -685,7 +682,7 @@ __global__ void __launch_bounds__(NT) k_batch_multi(BatchMArgs B) {
       for (int32_t i = wave; i < nw; i += NW) {
         const int32_t v = i * 64 + lane;
         uint64_t cs = 0;
-        if (v < n) cs = mt::ldw<1>(S.stw, v).w[0] ^ mt::ldw<1>(S.stw, G.comp[v]).w[0];
+        if (v < n) cs = mt::ldw<1>(S.stw<1>(), v).w[0] ^ mt::ldw<1>(S.stw<1>(), G.comp[v]).w[0];
         key_terms((uint64_t)i, mt::transpose64(cs), khi, klo);
       }
       atomicAdd((unsigned long long*)&s_acc[0][lane], (unsigned long long)myS);

@@ -190,9 +190,15 @@ struct Layout {
   size_t gwstride;     // per-slot bitmap stride (words rounded up to 32)
   size_t slots;        // one-workgroup-per-tree scratch in workspace memory
   size_t nslots, slot_stride;
-  // multi-tree path: 32-byte per-vertex records, split-row partial minima,
-  // vertices listed by component, and root-finding tasks
-  size_t mrec, mhslot, mhcap, mreach, aslot, cverts, ccount, cptr, mtasks, mtcap, rootbig, nbigcap;
+  // multi-tree path: vertices listed by component, root-finding tasks, and
+  // `msets` sets of a pass's working state, mset_stride bytes apart
+  size_t aslot, cverts, ccount, cptr, mtasks, mtcap, mhcap, nbigcap;
+  size_t mset, mset_stride, msets;
+  // within a set: vertex records, the final-state copy, the unfinished and
+  // candidate bitmaps, the pull lists of two levels in three classes and
+  // their reached bitmaps, split-row and big-component minima, control and
+  // barrier words
+  size_t mrec, mstc, munf, mcand, mpl, mpm, mph, mrl, mrm, mrh, mhslot, mrootbig, mctl, mbar;
   size_t swtile;       // switch lists: per-tile counts and offsets (8 bytes each)
   size_t glheavy;      // graphL: rows longer than kGLHeavy
   size_t glfirst;      // graphL: first item of each of those rows, and the item count
@@ -212,6 +218,12 @@ constexpr int kOrderMax = 16384;
 
 // multi-tree path constants shared by create and the kernel
 constexpr int kMSplit = 2048;     // rows longer than this are split into units of this many edges
+// The automatic schedule, by work = n + m/2: the multi-tree path from
+// kMultiMinWork on; on a deep graph only past kDeepWork
+constexpr int64_t kMultiMinWork = 20000;
+constexpr int64_t kDeepWork = 135000;
+constexpr int kMSets = 8;         // passes in flight on the multi-tree path (max)
+constexpr int kMCtlWords = 1024;  // control words of a pass
 constexpr int kBigComp = 1024;    // components larger than this find their roots in chunks
 constexpr int kRootChunk = 1024;  // vertices per root-finding task of a big component
 
@@ -238,6 +250,8 @@ void prof_end(fi_graph* g, hipStream_t s, void* token, int kernel);
 hipError_t launch_sweep(fi_graph* g, const SweepArgs& a, hipStream_t s);
 hipError_t launch_grid(fi_graph* g, const SweepArgs& a, hipStream_t s);
 hipError_t launch_multi(fi_graph* g, const SweepArgs& a, int words, hipStream_t s);
+// words per vertex (1 or 2) of the automatic schedule's multi-tree pass over `trees` trees
+int multi_words(const fi_graph* g, uint64_t trees);
 // exact count of up to 64 states given as one word per vertex (bit b = the
 // vertex's state in state b, set = -1; uint32 words for up to 32 states,
 // else uint64): counts[b] += frustrated edges
@@ -270,6 +284,7 @@ struct fi_graph {
   int32_t main_begin, main_end;  // its vertices in cverts
   int32_t main_big;       // its row of big-component root minima (-1: not a big component)
   bool cent;              // distance sums for the tree order are in the workspace
+  bool deep;              // a BFS of the main component takes more than kDeepLevels levels
   uint64_t* plog;         // phase log of the multi-tree kernel (null: off)
   int64_t pcap;           // its length in words
   fi_schedule sched;

@@ -14,20 +14,24 @@
 namespace fi {
 namespace mt {
 
-// Per-vertex state of one pass: the trees that discovered the vertex at the
-// last even / odd level, its state bits and the trees that have visited it
-// (the fields of the vertex records, below); the vertices with an edge not yet
-// visited by every tree, and the push candidates of the level (n/64 words
-// each).
+// Per-vertex state of one pass: the vertex records (the trees that discovered
+// the vertex at the last even / odd level, its state bits and the trees that
+// have visited it; below), the vertices with an edge not yet visited by every
+// tree, and the push candidates of the level (n/64 words each).
 struct MState {
-  uint64_t* nbw[2];
-  uint64_t* stw;
-  uint64_t* vis;
+  uint64_t* rec;
   uint64_t* unf;
   uint64_t* cand;
   // final states, W words per vertex side by side, written when the vertex
   // is visited by every tree (null: not kept)
   uint64_t* stc;
+  // a field's word of vertex 0: discoveries at levels of parity p, states, visits
+  template <int W>
+  __device__ __forceinline__ uint64_t* nbw(int p) const { return rec + 2 * W * p; }
+  template <int W>
+  __device__ __forceinline__ uint64_t* stw() const { return rec + W; }
+  template <int W>
+  __device__ __forceinline__ uint64_t* vis() const { return rec + 3 * W; }
 };
 
 __device__ __forceinline__ uint64_t amin64(uint64_t* p, uint64_t v) {
@@ -147,7 +151,7 @@ __device__ __forceinline__ int select_lane(uint64_t mask, int k) {
 // tree 64 w + t, and lane t of a wavefront carries trees t, 64 + t, ...  The
 // four fields of a vertex (discoveries at even levels, states, discoveries at
 // odd levels, visits) form one record of 4 W words, field f of vertex v at
-// words 4 W v + f W .. + W - 1; MState's pointers point at field f of vertex 0.
+// words 4 W v + f W .. + W - 1; MState gives field f of vertex 0.
 // A gather of a neighbour's discoveries and states then touches one record,
 // and a pass of 64 W trees moves about as many lines as a pass of 64.
 constexpr int kRecFields = 4;
@@ -370,9 +374,9 @@ __device__ __forceinline__ bool settle_w(const MState& A, int32_t v, const TW<W>
   const TW<W> nv = or_w(vis, newb);
   const bool full = eq_w(nv, valid);
   if (lane_id() == 0) {
-    stw_<W>(A.vis, v, nv);
-    stw_<W>(A.nbw[p], v, newb);
-    if (any_w(stb)) stw_<W>(A.stw, v, or_w(st, stb));
+    stw_<W>(A.vis<W>(), v, nv);
+    stw_<W>(A.nbw<W>(p), v, newb);
+    if (any_w(stb)) stw_<W>(A.stw<W>(), v, or_w(st, stb));
     if (full) {
       aand64(A.unf + (v >> 6), ~(1ull << (v & 63)));
       put_final<W>(A, v, or_w(st, stb));
@@ -409,7 +413,7 @@ __device__ __forceinline__ uint64_t pull_small_w(const DevGraph& G, const MState
   if (ok) {
     s = G.row_ptr[v];
     d = G.row_ptr[v + 1] - s;
-    want = and_not(valid, ldw<W>(A.vis, v));
+    want = and_not(valid, ldw<W>(A.vis<W>(), v));
   }
   lw[lane] = want;
   lw[64 + lane] = TW<W>{};
@@ -458,8 +462,8 @@ __device__ __forceinline__ uint64_t pull_small_w(const DevGraph& G, const MState
   uint32_t an = G.adj[lane < c0.total ? c0.pos : 0];
   uint32_t un = lane < c0.total ? (an & kVertexMask) : 0u;
   uint64_t gn = (an >> 31) ? ~0ull : 0ull;
-  TW<W> nb = ldw<W>(A.nbw[pp], un);
-  TW<W> su = ldw<W>(A.stw, un);  // the same record
+  TW<W> nb = ldw<W>(A.nbw<W>(pp), un);
+  TW<W> su = ldw<W>(A.stw<W>(), un);  // the same record
   bool m1 = c0.k1 < ne;
   Chunk c1 = m1 ? chunk_at(c0.k1) : c0;
   an = G.adj[m1 && lane < c1.total ? c1.pos : 0];
@@ -484,8 +488,8 @@ __device__ __forceinline__ uint64_t pull_small_w(const DevGraph& G, const MState
     // c1's records
     un = m1 && lane < c1.total ? (an & kVertexMask) : 0u;
     gn = (an >> 31) ? ~0ull : 0ull;
-    nb = ldw<W>(A.nbw[pp], un);
-    su = ldw<W>(A.stw, un);
+    nb = ldw<W>(A.nbw<W>(pp), un);
+    su = ldw<W>(A.stw<W>(), un);
     // the adjacency of the chunk after c1
     const bool m2 = m1 && c1.k1 < ne;
     const Chunk c2 = m2 ? chunk_at(c1.k1) : c1;
@@ -560,15 +564,15 @@ __device__ __forceinline__ uint64_t pull_small_w(const DevGraph& G, const MState
   }
   const bool got = ok && any_w(mnew);
   if (got) {
-    vis = ldw<W>(A.vis, v);
-    st = ldw<W>(A.stw, v);
+    vis = ldw<W>(A.vis<W>(), v);
+    st = ldw<W>(A.stw<W>(), v);
   }
   const TW<W> nv = or_w(vis, mnew);
   const bool full = got && eq_w(nv, valid);
   if (got) {
-    stw_<W>(A.vis, v, nv);
-    stw_<W>(A.nbw[p], v, mnew);
-    if (any_w(mstb)) stw_<W>(A.stw, v, or_w(st, mstb));
+    stw_<W>(A.vis<W>(), v, nv);
+    stw_<W>(A.nbw<W>(p), v, mnew);
+    if (any_w(mstb)) stw_<W>(A.stw<W>(), v, or_w(st, mstb));
     if (full) {
       aand64(A.unf + (v >> 6), ~(1ull << (v & 63)));
       put_final<W>(A, v, or_w(st, mstb));

@@ -530,6 +530,16 @@ uint64_t table_size_for(int64_t cloud_capacity) {
 constexpr int32_t kRootChunkSmall = 256;
 constexpr int32_t kRootWide = 2097152;
 
+// Sets of working state, so passes of the multi-tree path that can be in
+// flight at once (about 110 bytes per vertex each).  On graphs of 10^4 to 10^6
+// vertices a pass leaves most of the chip waiting at its barriers and on its
+// longest rows; past about 16M in n + m/2 one pass keeps the memory busy alone
+// (plan_multi has the figures).
+static size_t multi_sets(int32_t n, int64_t nnz) {
+  const int64_t work = (int64_t)n + nnz / 4;
+  return work <= 1000000 ? kMSets : work <= 8000000 ? 4 : work <= 16000000 ? 2 : 1;
+}
+
 Layout make_layout(int32_t n, int64_t nnz, int64_t cloud_capacity, uint64_t table_size) {
   Layout L{};
   size_t off = 0;
@@ -576,13 +586,6 @@ Layout make_layout(int32_t n, int64_t nnz, int64_t cloud_capacity, uint64_t tabl
     L.nslots = std::min<size_t>(2048, std::max<size_t>(1, budget / L.slot_stride));
   }
   L.slots = take(L.slot_stride * L.nslots);
-  // multi-tree path (the lists, bitmaps, control and barrier words are the
-  // whole-grid path's, which never runs at the same time)
-  L.mrec = take(64 * nn);  // a record per vertex: four fields of up to two 8-byte tree words
-  L.mhcap = (size_t)nnz / kMSplit + 1;
-  L.mhslot = take(8 * 128 * L.mhcap);
-  // reached bitmaps over the two levels' list entries: light, then split rows
-  L.mreach = take(8 * (4 * ((nn + 64) / 64 + 2) + 2 * (L.mhcap / 64 + 2)));
   L.aslot = take(4 * nn);
   L.cverts = take(4 * nn);
   L.ccount = take(4 * (nn / 2 + 1));
@@ -590,7 +593,31 @@ Layout make_layout(int32_t n, int64_t nnz, int64_t cloud_capacity, uint64_t tabl
   L.mtcap = nn / 2 + nn / kRootChunkSmall + 2;
   L.mtasks = take(16 * L.mtcap);
   L.nbigcap = nn / kBigComp + 1;
-  L.rootbig = take(8 * 128 * L.nbigcap);
+  L.mhcap = (size_t)nnz / kMSplit + 1;
+  {
+    // one set of a pass's working state, laid out from 0
+    const size_t before = off;
+    off = 0;
+    const size_t lists = 4 * 2 * (nn + 64), reach = 8 * 2 * ((nn + 64) / 64 + 2);
+    L.mrec = take(64 * nn);  // a record per vertex: four fields of up to two 8-byte tree words
+    L.mstc = take(16 * nn);
+    L.munf = take(8 * nw);
+    L.mcand = take(8 * nw);
+    L.mpl = take(lists);
+    L.mpm = take(lists);
+    L.mph = take(8 * 2 * (L.mhcap + 64));
+    L.mrl = take(reach);
+    L.mrm = take(reach);
+    L.mrh = take(8 * 2 * (L.mhcap / 64 + 2));
+    L.mhslot = take(8 * 128 * L.mhcap);
+    L.mrootbig = take(8 * 128 * L.nbigcap);
+    L.mctl = take(8 * kMCtlWords);
+    L.mbar = take(8 * kGridBarWords);
+    L.mset_stride = off;
+    off = before;
+    L.msets = multi_sets(n, nnz);
+    L.mset = take(L.mset_stride * L.msets);
+  }
   L.swtile = take(16 * ((size_t)switch_tiles((int64_t)m) + 1));
   L.glheavy = take(4 * ((size_t)nnz / kGLHeavy + 2));
   L.glfirst = take(4 * ((size_t)nnz / kGLHeavy + 3));
@@ -606,6 +633,20 @@ Layout make_layout(int32_t n, int64_t nnz, int64_t cloud_capacity, uint64_t tabl
   return L;
 }
 
+// Every set's rows of 128 minima (two tree words of 64 trees each), and its
+// barrier words (the control words are reset by each pass).
+__global__ void k_mset_init(char* sets, Layout L) {
+  char* set = sets + blockIdx.y * L.mset_stride;
+  uint64_t* hs = (uint64_t*)(set + L.mhslot);
+  uint64_t* rb = (uint64_t*)(set + L.mrootbig);
+  uint64_t* bar = (uint64_t*)(set + L.mbar);
+  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  const int64_t step = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = t; i < 128 * (int64_t)L.mhcap; i += step) hs[i] = kUnvisited;
+  for (int64_t i = t; i < 128 * (int64_t)L.nbigcap; i += step) rb[i] = kUnvisited;
+  if (t < kGridBarWords) bar[t] = 0;
+}
+
 // The multi-tree path's component lists and root-finding tasks: every
 // component with an edge gets one task if it has at most kBigComp vertices,
 // else one task per chunk of its vertices and a row of big-component minima.
@@ -613,7 +654,7 @@ Layout make_layout(int32_t n, int64_t nnz, int64_t cloud_capacity, uint64_t tabl
 // the same 64 W minima: components up to kRootWide vertices take chunks of
 // kRootChunkSmall (more waves on the scan), larger ones kRootChunk (fewer
 // atomic minima on those words).  Also resets the split-row and big-component
-// minima.
+// minima of every set.
 int build_components(fi_graph* g, hipStream_t s) {
   const Layout& L = g->L;
   char* ws = g->ws;
@@ -669,11 +710,9 @@ int build_components(fi_graph* g, hipStream_t s) {
     hipLaunchKernelGGL(k_cfill, dim3(grid_for(n, B)), dim3(B), 0, s, G.row_ptr, G.comp, aslot, cptr,
                        n, count, (int32_t*)(ws + L.cverts));
   }
-  // every row of 128 minima (two tree words of 64 trees each)
-  hipLaunchKernelGGL(k_fill_u64, dim3(grid_for(128 * (int64_t)L.mhcap, B)), dim3(B), 0, s,
-                     (uint64_t*)(ws + L.mhslot), 128 * (int64_t)L.mhcap, kUnvisited);
-  hipLaunchKernelGGL(k_fill_u64, dim3(grid_for(128 * (int64_t)L.nbigcap, B)), dim3(B), 0, s,
-                     (uint64_t*)(ws + L.rootbig), 128 * (int64_t)L.nbigcap, kUnvisited);
+  hipLaunchKernelGGL(k_mset_init, dim3(grid_for(128 * (int64_t)std::max(L.mhcap, L.nbigcap), B, 4096),
+                                       (unsigned)L.msets),
+                     dim3(B), 0, s, ws + L.mset, L);
   if (hipStreamSynchronize(s) != hipSuccess || hipGetLastError() != hipSuccess) return FI_EDEVICE;
   g->mtasks = (int32_t)tasks.size();
   g->mnbig = nbig;

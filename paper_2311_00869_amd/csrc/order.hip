@@ -29,9 +29,11 @@ namespace fi {
 namespace {
 
 constexpr int kHubs = 8;
-constexpr int32_t kCentMinVertices = 65536;  // main components below this keep tree order
-constexpr int kChunk = 4096;                  // vertices per root-search task
-constexpr int32_t kInvertMin = 1 << 18;       // main components from this size invert the key
+constexpr int kChunkMax = 4096;               // vertices per root-search task (fewer while
+constexpr int kRootTasks = 4096;              // that leaves less than this many tasks)
+constexpr int32_t kInvertMin = 1 << 17;       // main components from this size invert the key
+constexpr int kCentBatch = 8;                 // BFS levels launched per look at their flags
+constexpr uint32_t kDeepLevels = 64;          // a BFS from the hubs of more levels is deep
 constexpr int kInvPerLane = 4;                // candidate keys per lane and step
 constexpr int32_t kCentWide = 256;            // rows longer than this take a wave each
 
@@ -66,21 +68,24 @@ inline int grid_for(int64_t work, int block, int cap = 65536) {
   return (int)std::max<int64_t>(1, std::min<int64_t>((work + block - 1) / block, cap));
 }
 
-__global__ void k_cent_clear(int32_t n, uint8_t* vis, uint8_t* front, uint16_t* dsum) {
+struct Hubs {
+  int32_t v[kHubs];  // distinct vertices
+  int32_t count;
+};
+
+// Empty bytes, but hub h starts its BFS: bit h of its visit and frontier bytes.
+__global__ void k_cent_seed(int32_t n, Hubs hubs, uint8_t* vis, uint8_t* front, uint16_t* dsum,
+                            uint32_t* any) {
+  if (blockIdx.x == 0 && threadIdx.x < kCentBatch) any[threadIdx.x] = 0;
   for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n;
        v += (int64_t)gridDim.x * blockDim.x) {
-    vis[v] = 0;
-    front[v] = 0;
+    uint8_t m = 0;
+#pragma unroll
+    for (int h = 0; h < kHubs; ++h)
+      if (h < hubs.count && hubs.v[h] == v) m |= (uint8_t)(1u << h);
+    vis[v] = m;
+    front[v] = m;
     dsum[v] = 0;
-  }
-}
-
-// Hub h (distinct vertices) starts its BFS: bit h of its visit and frontier bytes.
-__global__ void k_cent_seed(const int32_t* hubs, int nh, uint8_t* vis, uint8_t* front) {
-  const int h = threadIdx.x;
-  if (h < nh) {
-    vis[hubs[h]] = (uint8_t)(1u << h);
-    front[hubs[h]] = (uint8_t)(1u << h);
   }
 }
 
@@ -99,50 +104,49 @@ __device__ __forceinline__ void cent_take(int32_t v, uint8_t have, uint8_t nb, u
   }
 }
 
-__global__ void k_cent_level(const int32_t* rp, const uint32_t* adj, int32_t n, uint8_t full,
-                             const uint8_t* front, uint8_t* next, uint8_t* vis, uint16_t* dsum,
-                             uint32_t level, uint32_t* any) {
+// Workgroups 0 .. row_blocks - 1 take the short rows, a thread each; the
+// others the rows longer than kCentWide (rows[0, nrows)), a wave each with its
+// lanes over the row's entries.
+__global__ void k_cent_level(const int32_t* rp, const uint32_t* adj, int32_t n, const int32_t* rows,
+                             int32_t nrows, uint32_t row_blocks, uint8_t full, const uint8_t* front,
+                             uint8_t* next, uint8_t* vis, uint16_t* dsum, uint32_t level,
+                             uint32_t* any) {
   bool grew = false;
-  for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n;
-       v += (int64_t)gridDim.x * blockDim.x) {
-    if (rp[v + 1] - rp[v] > kCentWide) continue;
-    const uint8_t have = vis[v];
-    uint8_t nb = 0;
-    if (have != full) {
-      for (int32_t e = rp[v]; e < rp[v + 1]; ++e) {
-        nb |= front[adj[e] & kVertexMask];
-        if ((uint8_t)(nb | have) == full) break;
+  if (blockIdx.x < row_blocks) {
+    for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n;
+         v += (int64_t)row_blocks * blockDim.x) {
+      if (rp[v + 1] - rp[v] > kCentWide) continue;
+      const uint8_t have = vis[v];
+      uint8_t nb = 0;
+      if (have != full) {
+        for (int32_t e = rp[v]; e < rp[v + 1]; ++e) {
+          nb |= front[adj[e] & kVertexMask];
+          if ((uint8_t)(nb | have) == full) break;
+        }
       }
+      cent_take((int32_t)v, have, nb, next, vis, dsum, level, grew);
     }
-    cent_take((int32_t)v, have, nb, next, vis, dsum, level, grew);
+  } else {
+    const int lane = lane_id();
+    const int64_t wave =
+        ((blockIdx.x - row_blocks) * (int64_t)blockDim.x + threadIdx.x) >> 6;
+    const int64_t nwaves = ((int64_t)(gridDim.x - row_blocks) * blockDim.x) >> 6;
+    for (int64_t k = wave; k < nrows; k += nwaves) {
+      const int32_t v = rows[k];
+      const uint8_t have = vis[v];
+      uint32_t nb = 0;
+      if (have != full) {
+        const int32_t e1 = rp[v + 1];
+        for (int32_t c = rp[v]; c < e1; c += 64) {
+          if (c + lane < e1) nb |= front[adj[c + lane] & kVertexMask];
+          if ((uint8_t)(wave_or_u32(nb) | have) == full) break;
+        }
+        nb = wave_or_u32(nb);
+      }
+      if (lane == 0) cent_take(v, have, (uint8_t)nb, next, vis, dsum, level, grew);
+    }
   }
   if (__ballot(grew) && lane_id() == 0) atomicOr(any, 1u);
-}
-
-// The same step for the rows longer than kCentWide (rows[0, nrows)), one
-// wave per row, its lanes over the row's entries.
-__global__ void k_cent_wide(const int32_t* rp, const uint32_t* adj, const int32_t* rows,
-                            int32_t nrows, uint8_t full, const uint8_t* front, uint8_t* next,
-                            uint8_t* vis, uint16_t* dsum, uint32_t level, uint32_t* any) {
-  const int lane = lane_id();
-  const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
-  const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-  bool grew = false;
-  for (int64_t k = wave; k < nrows; k += nwaves) {
-    const int32_t v = rows[k];
-    const uint8_t have = vis[v];
-    uint32_t nb = 0;
-    if (have != full) {
-      const int32_t e1 = rp[v + 1];
-      for (int32_t c = rp[v]; c < e1; c += 64) {
-        if (c + lane < e1) nb |= front[adj[c + lane] & kVertexMask];
-        if ((uint8_t)(wave_or_u32(nb) | have) == full) break;
-      }
-      nb = wave_or_u32(nb);
-    }
-    if (lane == 0) cent_take(v, have, (uint8_t)nb, next, vis, dsum, level, grew);
-  }
-  if (lane == 0 && grew) atomicOr(any, 1u);
 }
 
 __global__ void k_fill64(uint64_t* p, int64_t len, uint64_t v) {
@@ -152,22 +156,22 @@ __global__ void k_fill64(uint64_t* p, int64_t len, uint64_t v) {
 }
 
 // Root candidates (key << 32 | vertex << 1) of trees t0 .. t0 + count - 1 in
-// the main component (cverts[b, e)): one wave per (64 trees, kChunk
+// the main component (cverts[b, e)): one wave per (64 trees, `chunk`
 // vertices), lane t the minimum for its tree, then one atomic minimum per
 // tree.  Two running minima keep two compare chains in flight.
 __global__ void k_main_roots(const int32_t* cverts, int32_t b, int32_t e, uint64_t seed,
-                             uint64_t t0, uint32_t count, uint64_t* oroot) {
+                             uint64_t t0, uint32_t count, int32_t chunk, uint64_t* oroot) {
   const int lane = lane_id();
   const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
   const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-  const int64_t nchunks = ((int64_t)e - b + kChunk - 1) / kChunk;
+  const int64_t nchunks = ((int64_t)e - b + chunk - 1) / chunk;
   const int64_t ngroups = (count + 63) / 64;
   for (int64_t task = wave; task < nchunks * ngroups; task += nwaves) {
     const int64_t gi = task / nchunks, ci = task - gi * nchunks;
     const uint32_t slot = (uint32_t)(gi * 64 + lane);
     const KeyMix km = key_mix(tree_salt(seed, t0 + slot));
     uint64_t best = kUnvisited, alt = kUnvisited;
-    const int32_t c0 = b + (int32_t)(ci * kChunk), c1 = min(e, c0 + kChunk);
+    const int32_t c0 = b + (int32_t)(ci * chunk), c1 = min(e, c0 + chunk);
     for (int32_t c = c0; c < c1; c += 64) {
       const int32_t mine = c + lane < c1 ? cverts[c + lane] : 0;
       const uint32_t hm = fmix32((uint32_t)mine);
@@ -277,8 +281,9 @@ __global__ void __launch_bounds__(kSortThreads) k_order(const uint64_t* oroot, c
 
 int centrality_setup(fi_graph* g, hipStream_t s) {
   g->cent = false;
+  g->deep = false;
   const int32_t n = g->dg.n;
-  if (g->main_big < 0 || g->main_end - g->main_begin < kCentMinVertices) return FI_OK;
+  if (g->main_big < 0 || (int64_t)n + g->dg.m / 2 < kMultiMinWork) return FI_OK;
   // the kHubs vertices of highest degree (ties to the smaller id)
   std::vector<int32_t> rp((size_t)n + 1);
   if (hipMemcpyAsync(rp.data(), g->dg.row_ptr, 4 * ((size_t)n + 1), hipMemcpyDeviceToHost, s) !=
@@ -296,35 +301,46 @@ int centrality_setup(fi_graph* g, hipStream_t s) {
   uint8_t* front = vis + n;
   uint8_t* next = front + n;
   uint32_t* any = (uint32_t*)(g->ws + g->L.oroot);
-  int32_t* hubs = (int32_t*)(g->ws + g->L.operm);
+  Hubs hubs{};
+  hubs.count = nh;
+  for (int h = 0; h < nh; ++h) hubs.v[h] = order[h];
   uint16_t* dsum = (uint16_t*)(g->ws + g->L.cent);
   // the long rows, after the three byte maps (the scratch region holds 8 (n + 64) bytes)
   std::vector<int32_t> wide;
   for (int32_t v = 0; v < n; ++v)
     if (rp[v + 1] - rp[v] > kCentWide) wide.push_back(v);
   int32_t* rows = (int32_t*)(g->ws + g->L.scratch + ((3 * (size_t)n + 255) & ~(size_t)255));
-  if (hipMemcpyAsync(hubs, order.data(), 4 * nh, hipMemcpyHostToDevice, s) != hipSuccess ||
-      (!wide.empty() && hipMemcpyAsync(rows, wide.data(), 4 * wide.size(), hipMemcpyHostToDevice,
-                                       s) != hipSuccess))
+  if (!wide.empty() &&
+      hipMemcpyAsync(rows, wide.data(), 4 * wide.size(), hipMemcpyHostToDevice, s) != hipSuccess)
     return FI_EDEVICE;
   const int32_t nwide = (int32_t)wide.size();
-  hipLaunchKernelGGL(k_cent_clear, dim3(grid_for(n, 256)), dim3(256), 0, s, n, vis, front, dsum);
-  hipLaunchKernelGGL(k_cent_seed, dim3(1), dim3(64), 0, s, (const int32_t*)hubs, nh, vis, front);
+  const unsigned row_blocks = (unsigned)grid_for(n, 256);
+  const unsigned blocks = row_blocks + (nwide > 0 ? (unsigned)grid_for((int64_t)nwide * 64, 256) : 0u);
+  hipLaunchKernelGGL(k_cent_seed, dim3(row_blocks), dim3(256), 0, s, n, hubs, vis, front, dsum, any);
   const uint8_t full = (uint8_t)((1u << nh) - 1);
-  for (uint32_t level = 1;; ++level) {
-    uint32_t grew = 0;
-    if (hipMemsetAsync(any, 0, 4, s) != hipSuccess) return FI_EDEVICE;
-    hipLaunchKernelGGL(k_cent_level, dim3(grid_for(n, 256)), dim3(256), 0, s, g->dg.row_ptr, g->dg.adj,
-                       n, full, (const uint8_t*)front, next, vis, dsum, level, any);
-    if (nwide > 0)
-      hipLaunchKernelGGL(k_cent_wide, dim3(grid_for((int64_t)nwide * 64, 256)), dim3(256), 0, s,
-                         g->dg.row_ptr, g->dg.adj, (const int32_t*)rows, nwide, full,
-                         (const uint8_t*)front, next, vis, dsum, level, any);
-    if (hipMemcpyAsync(&grew, any, 4, hipMemcpyDeviceToHost, s) != hipSuccess ||
+  // kCentBatch levels per look at their flags (a level past the last one
+  // finds an empty frontier and changes nothing)
+  bool grows = true;
+  for (uint32_t level = 1; grows;) {
+    uint32_t grew[kCentBatch];
+    if (level > 1)
+      hipLaunchKernelGGL(k_fill64, dim3(1), dim3(64), 0, s, (uint64_t*)any, (int64_t)kCentBatch / 2,
+                         (uint64_t)0);
+    for (int k = 0; k < kCentBatch; ++k, ++level) {
+      hipLaunchKernelGGL(k_cent_level, dim3(blocks), dim3(256), 0, s, g->dg.row_ptr, g->dg.adj, n,
+                         (const int32_t*)rows, nwide, row_blocks, full, (const uint8_t*)front, next,
+                         vis, dsum, level, any + k);
+      std::swap(front, next);
+    }
+    if (hipMemcpyAsync(grew, any, sizeof(grew), hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
       return FI_EDEVICE;
-    std::swap(front, next);
-    if (!grew) break;
+    for (int k = 0; k < kCentBatch; ++k) grows = grows && grew[k];
+    if (grows && level > kDeepLevels) {
+      g->deep = true;
+      // below kDeepWork such a graph is swept one tree per workgroup, in any order
+      if ((int64_t)n + g->dg.m / 2 <= kDeepWork) return FI_OK;
+    }
   }
   if (hipGetLastError() != hipSuccess) return FI_EDEVICE;
   g->cent = true;
@@ -342,10 +358,13 @@ hipError_t order_trees(fi_graph* g, uint64_t seed, uint64_t t0, uint32_t count, 
   } else {
     hipLaunchKernelGGL(k_fill64, dim3(grid_for(count, 256)), dim3(256), 0, s, oroot, (int64_t)count,
                        kUnvisited);
-    const int64_t nchunks = ((int64_t)g->main_end - g->main_begin + kChunk - 1) / kChunk;
-    const int64_t tasks = nchunks * (((int64_t)count + 63) / 64);
+    const int64_t verts = (int64_t)g->main_end - g->main_begin, groups = ((int64_t)count + 63) / 64;
+    // whole rounds of 64 vertices
+    const int32_t chunk = (int32_t)std::max<int64_t>(
+        64, std::min<int64_t>(kChunkMax, verts * groups / kRootTasks & ~63));
+    const int64_t tasks = (verts + chunk - 1) / chunk * groups;
     hipLaunchKernelGGL(k_main_roots, dim3(grid_for(tasks * 64, 256, 8192)), dim3(256), 0, s, cverts,
-                       g->main_begin, g->main_end, seed, t0, count, oroot);
+                       g->main_begin, g->main_end, seed, t0, count, chunk, oroot);
   }
   uint32_t npow = 1;
   while (npow < count) npow <<= 1;

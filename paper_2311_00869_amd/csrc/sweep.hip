@@ -95,7 +95,10 @@ hipError_t launch_wg(fi_graph* g, const SweepArgs& a, int path, hipStream_t s) {
   return launch_wg_smp<NT, kSamplerBfs>(g, a, path, s);
 }
 
-int pick_path(fi_graph* g) {
+// Trees per CU from which a small graph's sweep goes to the multi-tree path.
+constexpr uint64_t kMultiTreesPerCu = 3;
+
+int pick_path(fi_graph* g, uint64_t trees) {
   const int32_t n = g->dg.n;
   const bool fits = wg_lds_bytes(n, g->sampler) + 32768 <= (size_t)g->max_shared;
   if (g->sampler != kSamplerBfs) {
@@ -106,37 +109,49 @@ int pick_path(fi_graph* g) {
     return g->L.nslots > 0 ? 2 : 0;
   }
   if (g->sched.path != 0) return g->sched.path;
-  if (fits) return 1;
-  // one tree per workgroup costs about m per tree, while 128 trees per pass
-  // (on a grid sized to the graph) cost about their BFS depth: past n + m/2 of
-  // about 135,000 the pass wins (measured at average degrees 4, 10 and 16)
-  if ((int64_t)n + g->dg.m / 2 <= 135000 && g->L.nslots > 0) return 2;
-  return 5;
+  const int64_t work = (int64_t)n + g->dg.m / 2;
+  // A tree in LDS is swept alone in 40 to 160 us, as many at once as the CUs
+  // hold; the multi-tree pass needs 300 us and up whatever its trees (n =
+  // 6,000, m = 50,000: 1,000 trees 531 us and 424 on it, 300 trees 276 and
+  // 556; 4,000 / 20,000: 1,000 trees 277 and 389), but on a deep graph it
+  // pays its barriers at every level.
+  const bool many = trees >= kMultiTreesPerCu * (uint64_t)g->cu_count && work >= kMultiMinWork;
+  if (fits && (!many || g->deep)) return 1;
+  // One tree per workgroup in workspace memory costs about m per tree (30,000
+  // / 150,000: 1.5 ms for 100 trees, 7.3 ms for 1,000; the multi-tree path 0.4
+  // and 0.77), but a level of it needs no grid barrier.
+  if (g->deep && work <= kDeepWork && g->L.nslots > 0) return 2;
+  return multi_words(g, trees) == 1 ? 4 : 5;
 }
 
 // threads per workgroup of the automatic schedule's one-tree-per-workgroup
 // paths (measured up to 3 times apart).  Path 2: 256 for sparse graphs
 // (average degree up to 10), else 1,024.  Path 1: the tree's LDS bounds the
-// workgroups a CU holds, so the fewer fit, the wider each one (BFS and
-// Kruskal; the randomized DFS keeps most waves idle and takes 256).
-int auto_block(fi_graph* g, int path) {
+// workgroups a CU holds, so the fewer fit, the wider each one; while the trees
+// are few, a tree's own time counts, so up to one tree per CU takes 1,024
+// threads (n = 1,000: 43 us for 100 trees, 70 with 256; n = 4,000: 90 and
+// 213) and up to three per CU 512 (n = 1,000, 300 trees: 60 us, 78 with 256,
+// 74 with 1,024).  (BFS and Kruskal; the randomized DFS keeps most waves idle
+// and takes 256.)
+int auto_block(fi_graph* g, int path, uint64_t trees) {
   if (path == 2) return g->dg.m <= 5 * (int64_t)g->dg.n ? 256 : 1024;
   if (path != 1 || g->sampler == kSamplerRdfs || g->sampler == kSamplerHybrid) return 256;
   const size_t lds = wg_lds_bytes(g->dg.n, g->sampler);
-  return lds <= 24576 ? 256 : lds <= 65536 ? 512 : 1024;
+  if (lds > 65536 || trees <= (uint64_t)g->cu_count) return 1024;
+  return lds <= 24576 && trees > 3 * (uint64_t)g->cu_count ? 256 : 512;
 }
 
 }  // namespace
 
 hipError_t launch_sweep(fi_graph* g, const SweepArgs& a, hipStream_t s) {
   if (a.t1 <= a.t0) return hipSuccess;
-  int path = pick_path(g);
+  int path = pick_path(g, a.t1 - a.t0);
   if (path == 0) return hipErrorInvalidValue;  // a sampler other than BFS above 1M vertices
   // the multi-tree path keeps no per-tree state words to hand out; it alone
   // gathers the cloud statistics
   if ((path == 4 || path == 5) && a.bits_out) path = 3;
   if (a.vminus || a.eswitch) path = path == 5 ? 5 : 4;  // (BFS only: checked by the caller)
-  const int nt = g->sched.path == 0 ? auto_block(g, path) : g->sched.block;
+  const int nt = g->sched.path == 0 ? auto_block(g, path, a.t1 - a.t0) : g->sched.block;
   void* tok = nullptr;
   if (prof_begin(g, s, &tok)) return hipErrorUnknown;
   hipError_t e;

@@ -56,6 +56,11 @@ constexpr int kPushCost = 32;      // push while kPushCost * frontier edges < un
 constexpr int kSmall = 32;         // rows up to this many edges are pulled 64 vertices per wave
 static_assert(stage_small<1024>() / (kSmall + 1) <= kStageM, "sparse listing: medium rows");
 constexpr int kMedChunk = 4;       // medium frontier rows per push unit (at most 8,192 edges)
+constexpr int kBatchesPerWave = 2; // small-row batches per wave that a short list is cut for
+constexpr int kCoopRow = 256;      // medium rows longer than this may be shared by a block's waves
+constexpr int kCoopPart = 128;     // in parts of this many edges
+constexpr int kCoopRowsPerWave = 4; // while a level has fewer medium rows than this per wave
+constexpr int kCoopMax = 64;       // at most so many per block and level
 constexpr int kPlanes = 8;         // bit-sliced counter planes (flushed before 255 edges)
 constexpr int kCountBatch = 4;     // edges per lane in flight in the count
 
@@ -89,8 +94,8 @@ __host__ __device__ constexpr int cTQ(int r) { return 192 + 16 * r; }
 __host__ __device__ constexpr int cTM(int r) { return 384 + 16 * r; }
 constexpr int cUNF = 256;
 constexpr int cACC = 512;
-constexpr int kMCtlWords = 1024;  // ACC holds 4 words for each of up to 128 trees
-static_assert(kMCtlWords <= kGridSlots * kGridCtlWords, "control block");
+// ACC holds 4 words for each of up to 128 trees
+static_assert(cACC + 4 * 128 <= kMCtlWords, "control block");
 
 struct MArgs {
   uint64_t seed, t0, t1;
@@ -110,6 +115,11 @@ struct MArgs {
   uint64_t* eswitch;     // [m] statistics, or null
   int insert;
   int32_t ntasks, nbig;
+  // passes in flight (nsets = 1 << lgsets): set k of working state serves passes k, k + nsets, ...
+  // of `per` trees each.  The pointers below are set 0's; set k's lie k
+  // set_stride bytes on.
+  int32_t lgsets, per;
+  size_t set_stride;
   MState S;              // per-vertex words and bitmaps of the pass
   int32_t* pl;          // [2][lstride] pull lists of rows up to kSmall (by level parity)
   int32_t* pm;          // [2][lstride] pull lists of rows up to kMSplit
@@ -132,11 +142,16 @@ struct MS {
   int start[NT];
   uint64_t base[NT * W];
   int scan[NT / 64 + 1];
-  int32_t q[stage_small<NT>()];  // staging: small rows
+  // staging: small rows; in the pull phase, the minima of the rows a block
+  // shares among its waves
+  alignas(16) int32_t q[stage_small<NT>()];
   int32_t q2[kStageM];  // staging: medium rows
   uint32_t qn, qn2;
   uint32_t bnext;       // next small-row batch of the block
   uint32_t mnext;       // next medium row of the block
+  uint32_t cqn, cnext;  // shared rows queued, next part of the round's rows
+  int32_t cq[kCoopMax];          // their places in the medium list
+  int32_t cpart[kCoopMax + 1];   // the round's rows: first part of each
   uint32_t unit;
   int hidx;
   int2 heavy;
@@ -244,8 +259,8 @@ __device__ __forceinline__ void put_root(uint32_t r0, const TW<W>& mine, const T
   const int dv = rp[r0 + 1] - rp[r0];
   const bool full = eq_w(mine, valid);
   if (lane == 0) {
-    stw_<W>(A.S.nbw[0], r0, mine);
-    stw_<W>(A.S.vis, r0, mine);
+    stw_<W>(A.S.nbw<W>(0), r0, mine);
+    stw_<W>(A.S.vis<W>(), r0, mine);
     if (full) {
       aand64(A.S.unf + (r0 >> 6), ~(1ull << (r0 & 63)));
       put_final<W>(A.S, r0, TW<W>{});  // a root's state is +1 in its trees
@@ -321,12 +336,38 @@ __device__ __forceinline__ void big_root(const uint64_t* rb, int t, const bool* 
   if (first == t) put_root<W, void>(rt, mine, valid, A, rp, cnt, deg, fin, nullptr);
 }
 
+template <class T>
+__device__ __forceinline__ void shift_by(T*& p, size_t bytes) {
+  p = (T*)((char*)p + bytes);
+}
+
 template <int NT, bool STATS, int W>
 __global__ void __launch_bounds__(NT) k_sweep_multi(DevGraph G, MArgs A) {
   __shared__ MS<NT, W> sh;
   constexpr int NW = NT / 64;
   const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
-  const uint32_t rank = blockIdx.x, nb = gridDim.x;
+  // workgroup b works on set b % nsets: workgroups are dealt to the XCDs
+  // round-robin, so eight sets run on one XCD each
+  const uint32_t nsets = 1u << A.lgsets, set = blockIdx.x & (nsets - 1);
+  const uint32_t rank = blockIdx.x >> A.lgsets, nb = gridDim.x >> A.lgsets;
+  {
+    const size_t o = set * A.set_stride;
+    shift_by(A.S.rec, o);
+    shift_by(A.S.unf, o);
+    shift_by(A.S.cand, o);
+    shift_by(A.S.stc, o);
+    shift_by(A.pl, o);
+    shift_by(A.pm, o);
+    shift_by(A.ph, o);
+    shift_by(A.rl, o);
+    shift_by(A.rm, o);
+    shift_by(A.rh, o);
+    shift_by(A.hslot, o);
+    shift_by(A.rootbig, o);
+    shift_by(A.ctl, o);
+    shift_by(A.bar, o);
+    if (set) A.plog = nullptr;  // set 0 logs its passes
+  }
   const int64_t stid = (int64_t)rank * NT + tid, sstride = (int64_t)nb * NT;
   const int64_t gwave = stid >> 6, nwaves = sstride >> 6;
   const int32_t n = G.n, nw = G.nwords;
@@ -337,8 +378,9 @@ __global__ void __launch_bounds__(NT) k_sweep_multi(DevGraph G, MArgs A) {
   const uint64_t ntrees = A.t1 - A.t0;
   // the tree carried by slot i of the launch
   auto tree_of = [&](uint64_t i) -> uint64_t { return A.perm ? (uint64_t)A.perm[i] : A.t0 + i; };
-  for (uint64_t sb = 0; sb < ntrees; sb += 64 * W) {
-    const int nvalid = (int)min<uint64_t>(64 * W, ntrees - sb);
+  const uint64_t per = (uint64_t)A.per;
+  for (uint64_t sb = set * per; sb < ntrees; sb += nsets * per) {
+    const int nvalid = (int)min<uint64_t>(per, ntrees - sb);
     TW<W> valid;
     bool vlane[W];
     KeyMix km[W];
@@ -352,7 +394,7 @@ __global__ void __launch_bounds__(NT) k_sweep_multi(DevGraph G, MArgs A) {
 
     // ---- reset: records, bitmaps, control words
     const int64_t ptid = fresh_index(stid);
-    for (int64_t v = ptid; v < (int64_t)n * W * kRecFields; v += sstride) A.S.nbw[0][v] = 0;
+    for (int64_t v = ptid; v < (int64_t)n * W * kRecFields; v += sstride) A.S.rec[v] = 0;
     for (int64_t i = ptid; i < nw; i += sstride) {
       A.S.unf[i] = G.word_mask[i];
       A.S.cand[i] = 0;
@@ -505,7 +547,7 @@ __global__ void __launch_bounds__(NT) k_sweep_multi(DevGraph G, MArgs A) {
             if (u >= 0) {
               st = rp[u];
               d = rp[u + 1] - st;
-              const TW<W> nbu = ldw<W>(A.S.nbw[pp], u);
+              const TW<W> nbu = ldw<W>(A.S.nbw<W>(pp), u);
 #pragma unroll
               for (int w = 0; w < W; ++w) bits.w[w] = nbu.w[w] & valid.w[w];
             }
@@ -534,7 +576,7 @@ __global__ void __launch_bounds__(NT) k_sweep_multi(DevGraph G, MArgs A) {
               const uint32_t part = hk - (uint32_t)uni(sh.heavy.y);
               e0 = rp[u] + (int64_t)part * kMSplit;
               const int64_t e1 = min<int64_t>(rp[u + 1], e0 + kMSplit);
-              const TW<W> nbu = ldw<W>(A.S.nbw[pp], u);
+              const TW<W> nbu = ldw<W>(A.S.nbw<W>(pp), u);
 #pragma unroll
               for (int w = 0; w < W; ++w) hbits.w[w] = nbu.w[w] & valid.w[w];
               total = (int)(e1 - e0);
@@ -558,7 +600,7 @@ __global__ void __launch_bounds__(NT) k_sweep_multi(DevGraph G, MArgs A) {
                 bits = hbits;
               }
               v = (int32_t)(a & kVertexMask);
-              if (any_w(and_not(bits, ldw<W>(A.S.vis, v)))) {
+              if (any_w(and_not(bits, ldw<W>(A.S.vis<W>(), v)))) {
                 const uint64_t bit = 1ull << (v & 63);
                 if (!(aor64(A.S.cand + (v >> 6), bit) & bit)) {
                   first = true;
@@ -642,28 +684,49 @@ __global__ void __launch_bounds__(NT) k_sweep_multi(DevGraph G, MArgs A) {
         sh.fin = 0;
         sh.bnext = 0;
         sh.mnext = 0;
+        sh.cqn = 0;
       }
       __syncthreads();
       {
         uint64_t cnt = 0, deg = 0, fin = 0;
-        // small rows: 64 list entries per wave, whole bitmap words; block b
-        // owns batches b, b + nb, ... and its waves draw them one at a time
+        // small rows: 64 list entries per wave, whole bitmap words (fewer
+        // entries, down to bytes of the bitmap, when the list is too short for
+        // a batch or two per wave); block b owns batches b, b + nb, ... and
+        // its waves draw them one at a time
         const int64_t nl = (int64_t)uni(sh.nl);
+        int lgb = 6;
+        while (lgb > 3 && (nl >> lgb) < kBatchesPerWave * nwaves) --lgb;
         while (true) {
           uint32_t i = 0;
           if (lane == 0) i = atomicAdd(&sh.bnext, 1u);
           const int64_t b = (int64_t)rank + (int64_t)uni((int)i) * nb;
-          if (b * 64 >= nl) break;
-          const int ne = (int)min<int64_t>(64, nl - b * 64);
+          const int64_t i0 = b << lgb;
+          if (i0 >= nl) break;
+          const int ne = (int)min<int64_t>(1 << lgb, nl - i0);
           const uint64_t r =
-              pull_small_w<W, kSmall>(G, A.S, b * 64 + lane < nl ? pln[b * 64 + lane] : 0, ne, pp,
-                                      p, valid, km, push, sh.pw[wave], sh.pe[wave], cnt, deg, fin);
-          if (lane == 0) rln[b] = r;
+              pull_small_w<W, kSmall>(G, A.S, lane < ne ? pln[i0 + lane] : 0, ne, pp, p, valid, km,
+                                      push, sh.pw[wave], sh.pe[wave], cnt, deg, fin);
+          if (lane == 0) {
+            if (lgb == 6) rln[b] = r;
+            else if (lgb == 5) ((uint32_t*)rln)[b] = (uint32_t)r;
+            else if (lgb == 4) ((uint16_t*)rln)[b] = (uint16_t)r;
+            else ((uint8_t*)rln)[b] = (uint8_t)r;
+          }
         }
         // medium rows: block b owns rows b, b + nb, ...; its waves draw them
         // one at a time and walk each with all lanes
         {
+          // the write-back of medium row i (vertex v of degree dq; its wave's)
+          auto settle_medium = [&](int32_t v, int64_t i, int dq, const uint64_t* best) {
+            const TW<W> vis = ldw<W>(A.S.vis<W>(), v), st = ldw<W>(A.S.stw<W>(), v);
+            if (settle_w<W>(A.S, v, vis, st, dq, best, p, valid, cnt, deg, fin) && lane == 0)
+              aor64(rmn + (i >> 6), 1ull << (i & 63));
+            if (push && lane == 0) aand64(A.S.cand + (v >> 6), ~(1ull << (v & 63)));
+          };
           const uint32_t nm = uni(sh.nm);
+          // with few rows per wave the longest one decides the level's time:
+          // such rows wait for the whole block (below)
+          const bool coop = (int64_t)nm < kCoopRowsPerWave * nwaves;
           while (true) {
             uint32_t c = 0;
             if (lane == 0) c = atomicAdd(&sh.mnext, 1u);
@@ -671,37 +734,79 @@ __global__ void __launch_bounds__(NT) k_sweep_multi(DevGraph G, MArgs A) {
             if (i >= (int64_t)nm) break;
             const int32_t v = pmn[i];
             const int64_t e0 = rp[v], e1 = rp[v + 1];
-            const TW<W> want = uni_w(and_not(valid, ldw<W>(A.S.vis, v)));  // v is the wave's
+            if (coop && e1 - e0 > kCoopRow) {
+              uint32_t at = 0;
+              if (lane == 0) at = atomicAdd(&sh.cqn, 1u);
+              at = (uint32_t)uni((int)at);
+              if (at < kCoopMax) {
+                if (lane == 0) sh.cq[at] = (int32_t)i;
+                continue;
+              }
+            }
+            const TW<W> want = uni_w(and_not(valid, ldw<W>(A.S.vis<W>(), v)));  // v is the wave's
             uint64_t best[W];
 #pragma unroll
             for (int w = 0; w < W; ++w) best[w] = kUnvisited;
-            if (any_w(want)) pull_edges_w<W>(G.adj, A.S.nbw[pp], A.S.stw, e0, e1, want, km, best);
-            TW<W> mnew, mstb;
-#pragma unroll
-            for (int w = 0; w < W; ++w) {
-              mnew.w[w] = __ballot(best[w] != kUnvisited);
-              mstb.w[w] = __ballot(best[w] != kUnvisited && (best[w] & 1));
-            }
-            const int dq = (int)(e1 - e0);
-            if (any_w(mnew)) {
-              const TW<W> visq = ldw<W>(A.S.vis, v), stq = ldw<W>(A.S.stw, v);
-              const TW<W> nv = or_w(visq, mnew);
-              const bool full = eq_w(nv, valid);
-              if (lane == 0) {
-                stw_<W>(A.S.vis, v, nv);
-                stw_<W>(A.S.nbw[p], v, mnew);
-                if (any_w(mstb)) stw_<W>(A.S.stw, v, or_w(stq, mstb));
-                if (full) {
-                  aand64(A.S.unf + (v >> 6), ~(1ull << (v & 63)));
-                  put_final<W>(A.S, v, or_w(stq, mstb));
+            if (any_w(want))
+              pull_edges_w<W>(G.adj, A.S.nbw<W>(pp), A.S.stw<W>(), e0, e1, want, km, best);
+            settle_medium(v, i, (int)(e1 - e0), best);
+          }
+          if (coop) {
+            // the queued rows, as many at a time as their minima fit in LDS:
+            // the waves draw parts of them, then each wave settles whole rows
+            constexpr int kRound = (int)(sizeof(sh.q) / (8 * 64 * W)) < kCoopMax
+                                       ? (int)(sizeof(sh.q) / (8 * 64 * W)) : kCoopMax;
+            uint64_t* cmin = (uint64_t*)sh.q;
+            __syncthreads();
+            const int nq = min((int)uni((int)sh.cqn), kCoopMax);
+            for (int q0 = 0; q0 < nq; q0 += kRound) {
+              const int nr = min(kRound, nq - q0);
+              for (int k = tid; k < nr * 64 * W; k += NT) cmin[k] = kUnvisited;
+              if (wave == 0) {
+                int parts = 0;
+                if (lane < nr) {
+                  const int32_t v = pmn[sh.cq[q0 + lane]];
+                  parts = (rp[v + 1] - rp[v] + kCoopPart - 1) / kCoopPart;
                 }
-                aor64(rmn + (i >> 6), 1ull << (i & 63));
+                const int inc = wave_incl_sum_i32(parts);
+                if (lane <= nr) sh.cpart[lane] = inc - parts;
+                if (lane == 0) sh.cnext = 0;
+                if (nr == 64 && lane == 63) sh.cpart[64] = inc;
               }
-              cnt += 1;
-              deg += (uint64_t)dq;
-              if (full) fin += (uint64_t)dq;
+              __syncthreads();
+              const int np = uni(sh.cpart[nr]);
+              while (true) {
+                uint32_t c = 0;
+                if (lane == 0) c = atomicAdd(&sh.cnext, 1u);
+                const int k = uni((int)c);
+                if (k >= np) break;
+                const int q = uni(upper_index(sh.cpart, nr, k));
+                const int32_t v = uni(pmn[sh.cq[q0 + q]]);
+                const int64_t e0 = rp[v] + (int64_t)(k - uni(sh.cpart[q])) * kCoopPart;
+                const int64_t e1 = min<int64_t>(rp[v + 1], e0 + kCoopPart);
+                const TW<W> want = uni_w(and_not(valid, ldw<W>(A.S.vis<W>(), v)));
+                uint64_t best[W];
+#pragma unroll
+                for (int w = 0; w < W; ++w) best[w] = kUnvisited;
+                if (any_w(want))
+                  pull_edges_w<W>(G.adj, A.S.nbw<W>(pp), A.S.stw<W>(), e0, e1, want, km, best);
+#pragma unroll
+                for (int w = 0; w < W; ++w)
+                  if (best[w] != kUnvisited)
+                    atomicMin((unsigned long long*)&cmin[(q * W + w) * 64 + lane],
+                              (unsigned long long)best[w]);
+              }
+              __syncthreads();
+              for (int q = wave; q < nr; q += NW) {
+                const int64_t i = uni(sh.cq[q0 + q]);
+                const int32_t v = uni(pmn[i]);
+                uint64_t best[W];
+#pragma unroll
+                for (int w = 0; w < W; ++w) best[w] = cmin[(q * W + w) * 64 + lane];
+                settle_medium(v, i, rp[v + 1] - rp[v], best);
+              }
+              __syncthreads();
             }
-            if (push && lane == 0) aand64(A.S.cand + (v >> 6), ~(1ull << (v & 63)));
           }
         }
         if (lane == 0 && cnt) {
@@ -735,7 +840,7 @@ __global__ void __launch_bounds__(NT) k_sweep_multi(DevGraph G, MArgs A) {
           const uint32_t part = hk - (uint32_t)uni(sh.heavy.y);
           const int64_t e0 = rp[v] + (int64_t)part * kMSplit;
           const int64_t e1 = min<int64_t>(rp[v + 1], e0 + kMSplit);
-          const TW<W> want = uni_w(and_not(valid, ldw<W>(A.S.vis, v)));  // v is the block's
+          const TW<W> want = uni_w(and_not(valid, ldw<W>(A.S.vis<W>(), v)));  // v is the block's
           const int64_t seg = ((e1 - e0 + NW - 1) / NW + 63) / 64 * 64;
           const int64_t s0 = min<int64_t>(e1, e0 + (int64_t)wave * seg);
           const int64_t s1 = min<int64_t>(e1, s0 + seg);
@@ -743,7 +848,7 @@ __global__ void __launch_bounds__(NT) k_sweep_multi(DevGraph G, MArgs A) {
 #pragma unroll
           for (int w = 0; w < W; ++w) best[w] = kUnvisited;
           if (any_w(want) && s0 < s1)
-            pull_edges_w<W>(G.adj, A.S.nbw[pp], A.S.stw, s0, s1, want, km, best);
+            pull_edges_w<W>(G.adj, A.S.nbw<W>(pp), A.S.stw<W>(), s0, s1, want, km, best);
 #pragma unroll
           for (int w = 0; w < W; ++w)
             if (best[w] != kUnvisited)
@@ -777,7 +882,7 @@ __global__ void __launch_bounds__(NT) k_sweep_multi(DevGraph G, MArgs A) {
             best[w] = hs[64 * w + lane];
             if (best[w] != kUnvisited) hs[64 * w + lane] = kUnvisited;
           }
-          const TW<W> vis = ldw<W>(A.S.vis, v), st = ldw<W>(A.S.stw, v);
+          const TW<W> vis = ldw<W>(A.S.vis<W>(), v), st = ldw<W>(A.S.stw<W>(), v);
           const int dv = rp[v + 1] - rp[v];
           if (settle_w<W>(A.S, v, vis, st, dv, best, p, valid, cnt, deg, fin) && lane == 0)
             aor64(rhn + (h >> 6), 1ull << (h & 63));
@@ -851,13 +956,18 @@ __global__ void __launch_bounds__(NT) k_sweep_multi(DevGraph G, MArgs A) {
               const uint64_t neg = (uv[k].y >> 31) ? ~0ull : 0ull;
 #pragma unroll
               for (int w = 0; w < W; ++w) x.w[w] = su[k].w[w] ^ sv[k].w[w] ^ neg;
-              // one owner per edge word in every pass
+              // one owner per edge word in every pass; passes in flight share
+              // the counters
               if constexpr (STATS) {
                 if (A.eswitch) {
                   uint64_t c1 = 0;
 #pragma unroll
                   for (int w = 0; w < W; ++w) c1 += (uint64_t)__popcll(x.w[w] & valid.w[w]);
-                  A.eswitch[e] += c1;
+                  if (nsets > 1) {
+                    if (c1) aadd64(A.eswitch + e, c1);
+                  } else {
+                    A.eswitch[e] += c1;
+                  }
                 }
               }
             }
@@ -898,7 +1008,11 @@ __global__ void __launch_bounds__(NT) k_sweep_multi(DevGraph G, MArgs A) {
             uint64_t k = 0;
 #pragma unroll
             for (int w = 0; w < W; ++w) k += (uint64_t)__popcll(cs.w[w] & valid.w[w]);
-            A.vminus[v] += k;
+            if (nsets > 1) {
+              if (k) aadd64(A.vminus + v, k);
+            } else {
+              A.vminus[v] += k;
+            }
           }
         }
 #pragma unroll
@@ -930,9 +1044,38 @@ __global__ void __launch_bounds__(NT) k_sweep_multi(DevGraph G, MArgs A) {
       if (A.tree_switches) A.tree_switches[t - A.t0] = S;
     }
     // the next pass clears the control words; finish reading them first
-    group_sync(A.bar, nb);
+    if (sb + nsets * per < ntrees) group_sync(A.bar, nb);
     log_phase(A, rank, kPhInsert, 0);
   }
+}
+
+// How the passes over `trees` trees of W words go.  A pass takes about
+// a + b work, where a is its barriers and longest rows (the same on the whole
+// chip or a part of it) and b work its share of the memory system, so s passes
+// in flight take 1 + c s of one another's time with c = work / 10^6 (measured:
+// 105,000 in n + m/2 with 8 in flight 1.6 times one pass's time, 350,000 3.1
+// times, 700,000 3.6 times; 6M with 4 in flight 3.6 times).  The sets are the
+// power of two with the least rounds (1 + c s), and the trees are dealt evenly
+// to the passes of those rounds.  1,000 trees on 30,000 vertices and 150,000
+// edges: 3.8 ms with one set, 0.77 with eight; 100,000 / 500,000: 4.2 and 1.6;
+// 1M / 10M: 12.0 and, with two, 10.6; 16M / 64M: 94.9 and 93.4 with two, but
+// 250 trees 29.5 and 32.1.
+struct MultiPlan {
+  int lgsets;
+  uint64_t per;
+  double cost;
+};
+MultiPlan plan_multi(const fi_graph* g, uint64_t trees, int words) {
+  const double c = ((double)g->dg.n + (double)(g->dg.m / 2)) * 1e-6;
+  const uint64_t cap = 64 * (uint64_t)words, npass = (trees + cap - 1) / cap;
+  MultiPlan best{0, cap, 0.0};
+  for (int lg = 0; (size_t)1 << lg <= g->L.msets; ++lg) {
+    const uint64_t sets = 1ull << lg, rounds = (npass + sets - 1) / sets;
+    const double cost = (double)rounds * (1.0 + c * (double)sets);
+    if (lg == 0 || cost < best.cost)
+      best = MultiPlan{lg, lg == 0 ? cap : (trees + rounds * sets - 1) / (rounds * sets), cost};
+  }
+  return best;
 }
 
 template <int NT, bool STATS, int W>
@@ -943,14 +1086,29 @@ hipError_t launch_mt(fi_graph* g, const MArgs& a, hipStream_t s) {
   if (e != hipSuccess) return e;
   if (per_cu < 1) return hipErrorInvalidConfiguration;
   const int maxg = per_cu * g->cu_count;
-  // by default one workgroup per 16,384 of n + m/2, a multiple of 8 (the
-  // XCDs), at least 64: on graphs of 10^5 vertices most of a level is its grid
-  // barriers, and 64 workgroups ran 1.5 to 1.7 times faster than 256
-  const int64_t work = (int64_t)g->dg.n + g->dg.m / 2;
-  const int auto_grid = (int)std::max<int64_t>(64, std::min<int64_t>(maxg, work / 16384) & ~7);
-  int grid = std::min(g->sched.grid > 0 ? g->sched.grid : auto_grid, maxg);
-  DevGraph G = g->dg;
   MArgs A = a;
+  A.lgsets = 0;
+  A.per = 64 * W;
+  A.set_stride = g->L.mset_stride;
+  int grid;
+  if (g->sched.grid > 0) {
+    grid = std::min(g->sched.grid, maxg);
+  } else {
+    // one pass at a time takes a workgroup per 1,024 of n + m/2, at least 64
+    // (128 trees: 3,000 vertices and 15,000 edges 292 us on 64 workgroups, 340
+    // on 256; 50,000 / 250,000 468 and 440; 100,000 / 500,000 828 and 602);
+    // several share the whole chip
+    const int64_t work = (int64_t)g->dg.n + g->dg.m / 2;
+    grid = (int)std::min<int64_t>(maxg, std::max<int64_t>(64, work / 1024 & ~7));
+    // (the phase log follows passes one at a time)
+    const MultiPlan p = plan_multi(g, A.t1 - A.t0, W);
+    if (p.lgsets > 0 && !A.plog && maxg >> p.lgsets > 0) {
+      A.lgsets = p.lgsets;
+      A.per = (int32_t)p.per;
+      grid = maxg >> p.lgsets << p.lgsets;
+    }
+  }
+  DevGraph G = g->dg;
   void* args[] = {(void*)&G, (void*)&A};
   e = hipLaunchCooperativeKernel((const void*)k_sweep_multi<NT, STATS, W>, dim3(grid), dim3(NT),
                                  args, 0, s);
@@ -969,6 +1127,16 @@ hipError_t launch_mt_block(fi_graph* g, const MArgs& a, hipStream_t s) {
 
 }  // namespace
 
+// One word (64 trees per pass) for few trees on small graphs: its pass takes
+// about 0.8 of the two-word pass's time (30,000 vertices, 250 trees: 466 us in
+// four passes of one word, 545 in two of two; 100 trees 410 and 489), while past
+// 200,000 in n + m/2 the two-word pass moves about as many lines.
+int multi_words(const fi_graph* g, uint64_t trees) {
+  if (trees <= 64) return 1;
+  if ((int64_t)g->dg.n + g->dg.m / 2 > 200000) return 2;
+  return 0.8 * plan_multi(g, trees, 1).cost < plan_multi(g, trees, 2).cost ? 1 : 2;
+}
+
 // words: tree words per vertex (1: 64 trees per pass, 2: 128)
 hipError_t launch_multi(fi_graph* g, const SweepArgs& sa, int words, hipStream_t s) {
   const Layout& L = g->L;
@@ -984,31 +1152,27 @@ hipError_t launch_multi(fi_graph* g, const SweepArgs& sa, int words, hipStream_t
   a.ntasks = g->mtasks;
   a.nbig = g->mnbig;
   // one record of kRecFields fields of `words` words per vertex
-  a.S.nbw[0] = (uint64_t*)(ws + L.mrec);
-  a.S.stw = a.S.nbw[0] + words;
-  a.S.nbw[1] = a.S.nbw[0] + 2 * words;
-  a.S.vis = a.S.nbw[0] + 3 * words;
-  a.S.unf = (uint64_t*)(ws + L.gvis);
-  a.S.cand = (uint64_t*)(ws + L.gsb);
-  // the final-state copy sits in the whole-grid path's tree words (8 words a
-  // vertex per slot, never in use at the same time)
-  a.S.stc = (uint64_t*)(ws + L.gpw);
+  char* set0 = ws + L.mset;
+  a.S.rec = (uint64_t*)(set0 + L.mrec);
+  a.S.unf = (uint64_t*)(set0 + L.munf);
+  a.S.cand = (uint64_t*)(set0 + L.mcand);
+  a.S.stc = (uint64_t*)(set0 + L.mstc);
   a.lstride = (int64_t)g->dg.n + 64;
-  a.hstride = (int64_t)L.hcap + 64;
+  a.hstride = (int64_t)L.mhcap + 64;
   a.rlstride = a.lstride / 64 + 2;
   a.rhstride = (int64_t)L.mhcap / 64 + 2;
-  a.pl = (int32_t*)(ws + L.gql);
-  a.pm = a.pl + 2 * a.lstride;
-  a.ph = (int2*)(ws + L.gqh);
-  a.rl = (uint64_t*)(ws + L.mreach);
-  a.rm = a.rl + 2 * a.rlstride;
-  a.rh = a.rm + 2 * a.rlstride;
-  a.hslot = (uint64_t*)(ws + L.mhslot);
+  a.pl = (int32_t*)(set0 + L.mpl);
+  a.pm = (int32_t*)(set0 + L.mpm);
+  a.ph = (int2*)(set0 + L.mph);
+  a.rl = (uint64_t*)(set0 + L.mrl);
+  a.rm = (uint64_t*)(set0 + L.mrm);
+  a.rh = (uint64_t*)(set0 + L.mrh);
+  a.hslot = (uint64_t*)(set0 + L.mhslot);
+  a.rootbig = (uint64_t*)(set0 + L.mrootbig);
+  a.ctl = (uint64_t*)(set0 + L.mctl);
+  a.bar = (uint64_t*)(set0 + L.mbar);
   a.tasks = (const int4*)(ws + L.mtasks);
   a.cverts = (const int32_t*)(ws + L.cverts);
-  a.rootbig = (uint64_t*)(ws + L.rootbig);
-  a.ctl = (uint64_t*)(ws + L.gctl);
-  a.bar = (uint64_t*)(ws + L.gbar);
   a.perm = nullptr;
   a.oroot = nullptr;
   a.main_big = g->main_big;
