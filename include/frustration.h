@@ -251,6 +251,13 @@ int fi_graphl_descend(fi_graph* g, float* d_gamma, float* d_work, int32_t R, flo
                       int64_t steps, int32_t rescale_log2, void* d_aux, size_t aux_bytes,
                       void* stream);
 
+/* The same descent from Gamma_0 in a buffer of its own: d_gamma0 float32[n][R]
+ * is only read (no overlap with d_gamma or d_work), and d_gamma need not hold
+ * anything on entry, so a caller that keeps its Gamma_0 copies nothing. */
+int fi_graphl_descend_from(fi_graph* g, const float* d_gamma0, float* d_gamma, float* d_work,
+                           int32_t R, float alpha, int64_t steps, int32_t rescale_log2, void* d_aux,
+                           size_t aux_bytes, void* stream);
+
 /* The log2 scale of every vertex and restart after fi_graphl_descend:
  * d_out int32[n][R] (0 for vertices without edges). */
 int fi_graphl_scales(fi_graph* g, const void* d_aux, int32_t R, int32_t* d_out, void* stream);

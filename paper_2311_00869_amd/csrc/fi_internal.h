@@ -201,6 +201,7 @@ struct Layout {
   size_t mrec, mstc, munf, mcand, mpl, mpm, mph, mrl, mrm, mrh, mhslot, mrootbig, mctl, mbar;
   size_t swtile;       // switch lists: per-tile counts and offsets (8 bytes each)
   size_t glheavy;      // graphL: rows longer than kGLHeavy
+  size_t glmid;        // graphL: rows longer than kGLMid, up to kGLHeavy
   size_t glfirst;      // graphL: first item of each of those rows, and the item count
   size_t glitems;      // graphL: items (heavy row, chunk)
   size_t glicap;       // graphL: item capacity
@@ -238,7 +239,8 @@ int read_cloud_table(const CloudSlot* d_table, uint64_t tsize, fi_cloud_entry* h
 constexpr int kGraphLMaxR = 64;
 constexpr int kGraphLBlocks = 1024;
 constexpr int kGLHeavy = 256;   // graphL rows longer than this are cut into items
-constexpr int kGLChunk = 4096;  // CSR entries per item of a long graphL row
+constexpr int kGLMid = 48;      // and rows longer than this take a wave each
+constexpr int kGLChunk = 1024;  // CSR entries per item of a long graphL row
 
 // profiling events around one launch (no-ops unless profiling is on)
 void batch_info_free(void* p);
@@ -279,6 +281,8 @@ struct fi_graph {
   int32_t ncomp, nisolated, nanch;
   int32_t mtasks, mnbig;  // multi-tree path: root-finding tasks, big components
   int32_t gl_nheavy;      // graphL rows longer than kGLHeavy (their items are planned at upload)
+  int32_t gl_nitems;      // and their items
+  int32_t gl_nmid;        // rows longer than kGLMid, up to kGLHeavy
   int32_t sampler;        // kSampler*
   int32_t gl_main_slot;   // slot of the component with the most vertices (-1: none)
   int32_t main_begin, main_end;  // its vertices in cverts

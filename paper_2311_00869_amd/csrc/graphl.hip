@@ -70,11 +70,7 @@ __global__ void k_gl_forward_final(const double* part, int nblocks, int R, doubl
 
 // Row gathers: g[i][r] = -1/2 * w_r * sum over the row of e_ij G[j][r].
 // With `update` the kernels write the descent update G - alpha * g instead.
-// Rows of up to kGLHeavy entries: one row per group of lanes, float32
-// accumulation in CSR order.  Longer rows (power-law hubs): one row per
-// workgroup, the groups striding over the row and their partial sums added
-// in group order.  Either way every row's summation order is fixed, so the
-// result is bit-reproducible.
+// Every row's summation order is fixed, so the result is bit-reproducible.
 //
 // Overflow policy of the descent (graphs whose hubs make the update grow by
 // up to (1 + alpha * lambda_max / 2) per step).  The update never mixes
@@ -94,6 +90,7 @@ struct RowArgs {
   // descent with scaling (all null for a plain step or gradient)
   const int32_t* comp;      // anchor of each vertex's component
   const int32_t* aslot;     // component slot of each anchor
+  const int32_t* anchors;   // anchor of each component slot
   const uint32_t* max_in;   // [C][R] float bits of max |G_in|
   uint32_t* max_out;        // [C][R] max |G_out| (atomic max)
   uint32_t* max_clear;      // [C][R] the buffer the step after next fills
@@ -121,218 +118,287 @@ __device__ __forceinline__ void note_row(const RowArgs& A, int64_t i, int32_t c,
   if (A.comp[i] == i && sc != 1.0f) A.exps[(size_t)c * R + sub] += A.shift;
 }
 
-__device__ __forceinline__ void block_max_main(const RowArgs& A, float mx, float* s_mx, int P,
-                                               int R, int sub, int grp, int gpb, bool active) {
-  s_mx[threadIdx.x] = mx;
-  __syncthreads();
-  if (grp == 0 && active && A.main_slot >= 0) {
-    float m = 0.0f;
-    for (int g = 0; g < gpb; ++g) m = fmaxf(m, s_mx[g * P + sub]);
-    if (m > 0.0f)
-      atomicMax((unsigned int*)&A.max_out[(size_t)A.main_slot * R + sub], __float_as_uint(m));
+// max_out = max(max_out, m) for the main component, whose maximum every
+// workgroup updates: only a workgroup above the value it reads does (the value
+// never falls within a launch, so a stale read costs an atomic and loses
+// nothing).  65,536 workgroups of 32 atomics each on one line took 2.1 ms of a
+// 3.1 ms step on 4M vertices.
+__device__ __forceinline__ void raise_max(uint32_t* max_out, float m) {
+  const uint32_t b = __float_as_uint(m);
+  if (m > 0.0f && b > __hip_atomic_load(max_out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    atomicMax((unsigned int*)max_out, b);
+}
+
+// The component slot of row i (-1: no edges): most rows lie in the main
+// component (anchor main_label), which needs no second load.
+__device__ __forceinline__ int32_t row_slot(const RowArgs& A, int64_t i, int64_t e0, int64_t e1,
+                                            int32_t main_label) {
+  if (e1 <= e0) return -1;
+  const int32_t label = A.comp[i];
+  return label == main_label ? A.main_slot : A.aslot[label];
+}
+
+// The rows that are not one group's, as listed at upload.
+struct GLPlan {
+  const int32_t* heavy;  // rows of more than kGLHeavy entries, cut into items
+  const int2* items;     // (place in heavy, chunk)
+  float* part;           // [nitems][kGraphLMaxR]
+  const int32_t* mid;    // rows of kGLMid + 1 .. kGLHeavy entries
+  uint32_t nitems, nmid;
+};
+
+// V consecutive restarts of a lane (4 as one 16-byte access, or 1).
+template <int V>
+struct Lane {
+  float x[V];
+};
+template <int V>
+__device__ __forceinline__ Lane<V> load_lane(const float* p) {
+  Lane<V> r;
+  if constexpr (V == 4) {
+    const float4 q = *reinterpret_cast<const float4*>(p);
+    r.x[0] = q.x;
+    r.x[1] = q.y;
+    r.x[2] = q.z;
+    r.x[3] = q.w;
+  } else {
+    r.x[0] = *p;
+  }
+  return r;
+}
+template <int V>
+__device__ __forceinline__ void store_lane(float* p, const Lane<V>& v) {
+  if constexpr (V == 4) *reinterpret_cast<float4*>(p) = make_float4(v.x[0], v.x[1], v.x[2], v.x[3]);
+  else *p = v.x[0];
+}
+
+constexpr int kGLBatch = 8;  // gathers of a row in flight per lane
+
+// Entries a[k] = e0 + k step (k < 8) that lie below e1, and y[k] = G[j] for the
+// lane's restarts, zero past e1.  All entries are loaded before the gathers
+// and all gathers are in flight together, those of the last few entries of a
+// row too.  With P >= 8 lanes to a row each lane loads one of the eight
+// entries and they are exchanged.
+template <int P, int V>
+__device__ __forceinline__ void gather8(const uint32_t* adj, int64_t e0, int64_t e1, int64_t step,
+                                        const float* gamma, int R, int sub, bool active,
+                                        uint32_t* a, Lane<V>* y) {
+  if constexpr (P >= kGLBatch) {
+    const int base = lane_id() & ~(P - 1);
+    const uint32_t mine = adj[min(e0 + (sub & (kGLBatch - 1)) * step, e1 - 1)];
+#pragma unroll
+    for (int k = 0; k < kGLBatch; ++k) a[k] = (uint32_t)__shfl((int)mine, base + k);
+  } else {
+#pragma unroll
+    for (int k = 0; k < kGLBatch; ++k) a[k] = adj[min(e0 + k * step, e1 - 1)];
+  }
+#pragma unroll
+  for (int k = 0; k < kGLBatch; ++k) {
+    y[k] = Lane<V>{};
+    if (active && e0 + k * step < e1)
+      y[k] = load_lane<V>(gamma + (size_t)(a[k] & kVertexMask) * R + V * sub);
   }
 }
 
-__device__ __forceinline__ int32_t row_slot(const RowArgs& A, int64_t i, int64_t e0, int64_t e1) {
-  return e1 > e0 ? A.aslot[A.comp[i]] : -1;
+// y[k] = e_ij * G[j] * sc.
+template <int V>
+__device__ __forceinline__ void sign_scale(const uint32_t* a, const Lane<V>& sc, Lane<V>* y) {
+#pragma unroll
+  for (int k = 0; k < kGLBatch; ++k) {
+    const bool ng = (a[k] >> 31) != 0;
+#pragma unroll
+    for (int q = 0; q < V; ++q) {
+      const float x = y[k].x[q] * sc.x[q];
+      y[k].x[q] = ng ? -x : x;
+    }
+  }
 }
 
-// Sum of e_ij * G[j][sub] * sc over entries e0, e0 + step, ... < e1, added
-// in that order.  Eight entries are loaded before their gathers so that
-// eight gathers are in flight per lane.
-__device__ __forceinline__ float row_sum(const uint32_t* adj, int64_t e0, int64_t e1, int step,
-                                         const float* gamma, int R, int sub, float sc) {
-  float acc = 0.0f;
-  int64_t e = e0;
-  for (; e + 7 * (int64_t)step < e1; e += 8 * (int64_t)step) {
-    uint32_t a[8];
-    float x[8];
+// Sum over entries e0, e0 + step, ... < e1, added in that order.  The scale is
+// asked for once the first gathers are in flight, so that its own loads do not
+// go before them.
+template <int P, int V, class Scale>
+__device__ __forceinline__ Lane<V> row_sum(const uint32_t* adj, int64_t e0, int64_t e1, int64_t step,
+                                           const float* gamma, int R, int sub, bool active,
+                                           Scale scale) {
+  Lane<V> acc{};
+  Lane<V> sc{};
+  for (int64_t e = e0; e < e1; e += kGLBatch * step) {
+    uint32_t a[kGLBatch];
+    Lane<V> y[kGLBatch];
+    gather8<P, V>(adj, e, e1, step, gamma, R, sub, active, a, y);
+    if (e == e0) sc = scale();
+    sign_scale<V>(a, sc, y);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) a[k] = adj[e + k * step];
+    for (int k = 0; k < kGLBatch; ++k)
+      if (e + k * step < e1)
 #pragma unroll
-    for (int k = 0; k < 8; ++k) x[k] = gamma[(size_t)(a[k] & kVertexMask) * R + sub] * sc;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) acc += (a[k] >> 31) ? -x[k] : x[k];
-  }
-  for (; e < e1; e += step) {
-    const uint32_t a = adj[e];
-    const float gj = gamma[(size_t)(a & kVertexMask) * R + sub] * sc;
-    acc += (a >> 31) ? -gj : gj;
+        for (int q = 0; q < V; ++q) acc.x[q] += y[k].x[q];
   }
   return acc;
 }
 
-__global__ void __launch_bounds__(kGLBlock) k_gl_rows(const int32_t* rp, const uint32_t* adj,
-                                                      int32_t n, const float* gamma, int R,
+// One pass over the rows: g[i][r] = -1/2 * w_r * sum over the row, or the
+// update.  Each lane owns V restarts and P lanes (a power of two with V P >= R)
+// share a row; a wave holds 64 / P such groups.
+//   long rows (more than kGLHeavy entries): items of up to kGLChunk entries,
+//     one per workgroup, its groups striding over the item and their sums added
+//     in group order into part[item][r]; k_gl_combine adds a row's items in order
+//   rows of kGLMid + 1 .. kGLHeavy entries: one wave each, eight entries per
+//     group at a time, laid in LDS and added there in the row's order
+//   shorter rows: one group each
+// Longest first, so that no long chain starts last.  Every row but the long
+// ones is summed in its own order whatever P and V are, so the variants agree
+// bit for bit.  Bound by the rate of random line fetches (52 to 59 G/s of 128
+// bytes here; R = 32 gathers one line per entry), as long as a row's gathers
+// are in flight together: with a row's last few entries gathered one by one
+// and long rows in a launch of their own, 4M vertices and 16M edges at R = 32
+// took 3.28 ms per step (2.1 of it the maxima, raise_max), now 0.95 (0.72 for
+// a gradient); 100,000 / 500,000 took 76 us with rows up to 256 entries on one
+// group each, now 51.
+template <int P, int V>
+__global__ void __launch_bounds__(kGLBlock) k_gl_pass(const int32_t* rp, const uint32_t* adj,
+                                                      int32_t n, GLPlan L, const float* gamma, int R,
                                                       RowArgs A, float* out) {
-  __shared__ float s_mx[kGLBlock];
-  const int P = lanes_for(R);
-  const int sub = threadIdx.x % P;
-  const int grp = threadIdx.x / P;
-  const int gpb = kGLBlock / P;
-  const bool active = sub < R;
+  constexpr int kGroups = kGLBlock / P, kWaveGroups = 64 / P, NW = kGLBlock / 64;
+  constexpr int kStage = kWaveGroups * kGLBatch;  // entries a wave lays down at a time
+  __shared__ Lane<V> s_y[NW][kStage * P];
+  __shared__ float s_mx[kGLBlock * V];
+  const int sub = threadIdx.x % P, grp = threadIdx.x / P;
+  const int wave = threadIdx.x >> 6, wgrp = grp % kWaveGroups;
+  const int r0 = V * sub;
+  const bool active = r0 < R;
   const bool scaled = A.max_in != nullptr;
-  const float wr = (A.w && active) ? (float)A.w[sub] : 1.0f;
-  if (scaled)
-    for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < A.ncr;
-         k += (int64_t)gridDim.x * blockDim.x)
-      A.max_clear[k] = 0;
-  float mx_main = 0.0f;
-  if (active) {
-    for (int64_t i = (int64_t)blockIdx.x * gpb + grp; i < n; i += (int64_t)gridDim.x * gpb) {
-      const int64_t e0 = rp[i], e1 = rp[i + 1];
-      if (e1 - e0 > kGLHeavy) continue;
-      const int32_t c = scaled ? row_slot(A, i, e0, e1) : -1;
-      const float sc = scaled ? pair_scale(A, c, R, sub) : 1.0f;
-      const float acc = row_sum(adj, e0, e1, 1, gamma, R, sub, sc);
-      const float g = -0.5f * acc * wr;
-      const size_t o = (size_t)i * R + sub;
-      const float v = A.update ? gamma[o] * sc - A.alpha * g : g;
-      out[o] = v;
-      if (scaled) note_row(A, i, c, R, sub, sc, v, mx_main);
-    }
+  const int32_t main_label = scaled && A.main_slot >= 0 ? A.anchors[A.main_slot] : -1;
+  Lane<V> wr, scm, mx;
+#pragma unroll
+  for (int k = 0; k < V; ++k) {
+    wr.x[k] = (A.w && active) ? (float)A.w[r0 + k] : 1.0f;
+    scm.x[k] = scaled && active ? pair_scale(A, A.main_slot, R, r0 + k) : 1.0f;
+    mx.x[k] = 0.0f;
   }
-  if (scaled) block_max_main(A, mx_main, s_mx, P, R, sub, grp, gpb, active);
-}
-
-// The same for R divisible by 4: each lane owns four consecutive restarts and
-// gathers them as one 16-byte load, so a wave covers 64 / (R / 4) rows per
-// load instead of 64 / R and keeps that many more row gathers in flight.
-// Every restart's sum runs over the row in the same order as in k_gl_rows,
-// so the results are the same bit for bit.
-__global__ void __launch_bounds__(kGLBlock) k_gl_rows4(const int32_t* rp, const uint32_t* adj,
-                                                       int32_t n, const float* gamma, int R,
-                                                       RowArgs A, float* out) {
-  __shared__ float s_mx[kGLBlock][4];
-  const int RV = R / 4;
-  const int P = lanes_for(RV);
-  const int sub = threadIdx.x % P;
-  const int grp = threadIdx.x / P;
-  const int gpb = kGLBlock / P;
-  const bool active = sub < RV;
-  const bool scaled = A.max_in != nullptr;
-  const int r0 = 4 * sub;
-  float wr[4];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) wr[k] = (A.w && active) ? (float)A.w[r0 + k] : 1.0f;
   if (scaled)
     for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < A.ncr;
          k += (int64_t)gridDim.x * blockDim.x)
       A.max_clear[k] = 0;
-  float mx_main[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-  if (active) {
-    for (int64_t i = (int64_t)blockIdx.x * gpb + grp; i < n; i += (int64_t)gridDim.x * gpb) {
-      const int64_t e0 = rp[i], e1 = rp[i + 1];
-      if (e1 - e0 > kGLHeavy) continue;
-      const int32_t c = scaled ? row_slot(A, i, e0, e1) : -1;
-      float sc[4];
+  auto slot_of = [&](int32_t label) {
+    return !scaled ? -1 : label == main_label ? A.main_slot : A.aslot[label];
+  };
+  auto scale_of = [&](int32_t c) {
+    Lane<V> sc;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) sc[k] = scaled ? pair_scale(A, c, R, r0 + k) : 1.0f;
-      float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-      int64_t e = e0;
-      for (; e + 7 < e1; e += 8) {
-        uint32_t a[8];
-        float4 x[8];
+    for (int k = 0; k < V; ++k)
+      sc.x[k] = !scaled || !active || c < 0 ? 1.0f
+                : c == A.main_slot          ? scm.x[k]
+                                            : pair_scale(A, c, R, r0 + k);
+    return sc;
+  };
+  // (read before the row's gathers, so that it is in flight with them)
+  auto load_self = [&](int64_t i) {
+    return A.update && active ? load_lane<V>(gamma + (size_t)i * R + r0) : Lane<V>{};
+  };
+  auto finish = [&](int64_t i, int32_t c, const Lane<V>& sc, const Lane<V>& self, const Lane<V>& acc) {
+    const size_t o = (size_t)i * R + r0;
+    Lane<V> v;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) a[j] = adj[e + j];
+    for (int k = 0; k < V; ++k) {
+      const float g = -0.5f * acc.x[k] * wr.x[k];
+      v.x[k] = A.update ? self.x[k] * sc.x[k] - A.alpha * g : g;
+    }
+    store_lane<V>(out + o, v);
+    if (scaled)
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
-          x[j] = *reinterpret_cast<const float4*>(gamma + (size_t)(a[j] & kVertexMask) * R + r0);
+      for (int k = 0; k < V; ++k) note_row(A, i, c, R, r0 + k, sc.x[k], v.x[k], mx.x[k]);
+  };
+
+  // long rows' items
+  for (uint32_t it = blockIdx.x; it < L.nitems; it += gridDim.x) {
+    const int2 hc = L.items[it];
+    const int64_t i = L.heavy[hc.x];
+    const int64_t b0 = rp[i], b1 = rp[i + 1];
+    const int64_t e0 = b0 + (int64_t)hc.y * kGLChunk;
+    const int64_t e1 = min(b1, e0 + kGLChunk);
+    const Lane<V> acc = row_sum<P, V>(adj, e0 + grp, e1, kGroups, gamma, R, sub, active, [&] {
+      return scale_of(scaled ? row_slot(A, i, b0, b1, main_label) : -1);
+    });
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const bool ng = (a[j] >> 31) != 0;
-          const float x0 = x[j].x * sc[0], x1 = x[j].y * sc[1], x2 = x[j].z * sc[2],
-                      x3 = x[j].w * sc[3];
-          acc[0] += ng ? -x0 : x0;
-          acc[1] += ng ? -x1 : x1;
-          acc[2] += ng ? -x2 : x2;
-          acc[3] += ng ? -x3 : x3;
+    for (int k = 0; k < V; ++k) s_mx[threadIdx.x * V + k] = acc.x[k];
+    __syncthreads();
+    if ((int)threadIdx.x < R) {
+      float tot = 0.0f;
+      for (int g = 0; g < kGroups; ++g) tot += s_mx[g * P * V + threadIdx.x];
+      L.part[(size_t)it * kGraphLMaxR + threadIdx.x] = tot;
+    }
+    __syncthreads();
+  }
+
+  // rows of one wave each
+  const int64_t gwave = (int64_t)blockIdx.x * NW + wave, nwaves = (int64_t)gridDim.x * NW;
+  for (int64_t m = gwave; m < (int64_t)L.nmid; m += nwaves) {
+    const int64_t i = L.mid[m];
+    const int64_t b0 = rp[i], b1 = rp[i + 1];
+    const int32_t label = scaled ? A.comp[i] : -1;
+    const Lane<V> self = load_self(i);
+    int32_t c = -1;
+    Lane<V> acc{}, sc{};
+    for (int64_t e = b0; e < b1; e += kStage) {
+      const int64_t eg = e + wgrp * kGLBatch;
+      uint32_t a[kGLBatch];
+      Lane<V> y[kGLBatch];
+      if (eg < b1) gather8<P, V>(adj, eg, b1, 1, gamma, R, sub, active, a, y);
+      if (e == b0) {
+        c = slot_of(label);
+        sc = scale_of(c);
+      }
+      if (eg < b1) sign_scale<V>(a, sc, y);
+#pragma unroll
+      for (int k = 0; k < kGLBatch; ++k)
+        if (eg + k < b1) s_y[wave][(wgrp * kGLBatch + k) * P + sub] = y[k];
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      const int cnt = (int)min<int64_t>(kStage, b1 - e);
+      if (wgrp == 0) {
+        for (int k = 0; k < cnt; ++k) {
+          const Lane<V> t = s_y[wave][k * P + sub];
+#pragma unroll
+          for (int q = 0; q < V; ++q) acc.x[q] += t.x[q];
         }
       }
-      for (; e < e1; ++e) {
-        const uint32_t a = adj[e];
-        const float4 x = *reinterpret_cast<const float4*>(gamma + (size_t)(a & kVertexMask) * R + r0);
-        const bool ng = (a >> 31) != 0;
-        const float x0 = x.x * sc[0], x1 = x.y * sc[1], x2 = x.z * sc[2], x3 = x.w * sc[3];
-        acc[0] += ng ? -x0 : x0;
-        acc[1] += ng ? -x1 : x1;
-        acc[2] += ng ? -x2 : x2;
-        acc[3] += ng ? -x3 : x3;
-      }
-      const size_t o = (size_t)i * R + r0;
-      const float4 self = *reinterpret_cast<const float4*>(gamma + o);
-      const float sv[4] = {self.x, self.y, self.z, self.w};
-      float v[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const float g = -0.5f * acc[k] * wr[k];
-        v[k] = A.update ? sv[k] * sc[k] - A.alpha * g : g;
-      }
-      *reinterpret_cast<float4*>(out + o) = make_float4(v[0], v[1], v[2], v[3]);
-      if (scaled)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) note_row(A, i, c, R, r0 + k, sc[k], v[k], mx_main[k]);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
+    if (wgrp == 0 && active) finish(i, c, sc, self, acc);
   }
+
+  // short rows
+  for (int64_t i = (int64_t)blockIdx.x * kGroups + grp; i < n; i += (int64_t)gridDim.x * kGroups) {
+    const int64_t e0 = rp[i], e1 = rp[i + 1];
+    if (e1 - e0 > kGLMid) continue;
+    const int32_t label = scaled ? A.comp[i] : -1;
+    const Lane<V> self = load_self(i);
+    int32_t c = -1;
+    Lane<V> sc = scale_of(-1);  // (of a row without entries)
+    const Lane<V> acc = row_sum<P, V>(adj, e0, e1, 1, gamma, R, sub, active, [&] {
+      c = slot_of(label);
+      sc = scale_of(c);
+      return sc;
+    });
+    if (active) finish(i, c, sc, self, acc);
+  }
+
   if (scaled) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) s_mx[threadIdx.x][k] = mx_main[k];
+    for (int k = 0; k < V; ++k) s_mx[threadIdx.x * V + k] = mx.x[k];
     __syncthreads();
-    if (grp == 0 && active && A.main_slot >= 0) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        float m = 0.0f;
-        for (int g = 0; g < gpb; ++g) m = fmaxf(m, s_mx[g * P + sub][k]);
-        if (m > 0.0f)
-          atomicMax((unsigned int*)&A.max_out[(size_t)A.main_slot * R + r0 + k],
-                    __float_as_uint(m));
-      }
+    if ((int)threadIdx.x < R && A.main_slot >= 0) {
+      float m = 0.0f;
+      for (int g = 0; g < kGroups; ++g) m = fmaxf(m, s_mx[g * P * V + threadIdx.x]);
+      raise_max(&A.max_out[(size_t)A.main_slot * R + threadIdx.x], m);
     }
-  }
-}
-
-// Heavy rows (more than kGLHeavy entries) are cut into items of up to
-// kGLChunk entries spread over workgroups.  An item's groups stride over its
-// entries and their sums are added in group order into part[item][r]; a row
-// then adds its items in order.  Items of one row are consecutive.
-__global__ void __launch_bounds__(kGLBlock) k_gl_chunks(const int32_t* rp, const uint32_t* adj,
-                                                        const int32_t* list, const int2* items,
-                                                        const uint32_t* ctl, const float* gamma,
-                                                        int R, RowArgs A, float* part) {
-  __shared__ float s_part[kGLBlock];
-  const int P = lanes_for(R);
-  const int sub = threadIdx.x % P;
-  const int grp = threadIdx.x / P;
-  const int gpb = kGLBlock / P;
-  const bool active = sub < R;
-  const bool scaled = A.max_in != nullptr;
-  const uint32_t nitems = ctl[1];
-  for (uint32_t it = blockIdx.x; it < nitems; it += gridDim.x) {
-    const int2 hc = items[it];
-    const int64_t i = list[hc.x];
-    const int64_t r0 = rp[i], r1 = rp[i + 1];
-    const int64_t e0 = r0 + (int64_t)hc.y * kGLChunk;
-    const int64_t e1 = min(r1, e0 + kGLChunk);
-    float acc = 0.0f;
-    if (active) {
-      const int32_t c = scaled ? row_slot(A, i, r0, r1) : -1;
-      const float sc = scaled ? pair_scale(A, c, R, sub) : 1.0f;
-      acc = row_sum(adj, e0 + grp, e1, gpb, gamma, R, sub, sc);
-    }
-    s_part[threadIdx.x] = acc;
-    __syncthreads();
-    if (grp == 0 && active) {
-      float tot = 0.0f;
-      for (int g = 0; g < gpb; ++g) tot += s_part[g * P + sub];
-      part[(size_t)it * kGraphLMaxR + sub] = tot;
-    }
-    __syncthreads();
   }
 }
 
 // One group of lanes per heavy row: its items in order, then the update.
 __global__ void __launch_bounds__(kGLBlock) k_gl_combine(const int32_t* rp, const int32_t* list,
-                                                         const int32_t* first, const uint32_t* ctl,
+                                                         const int32_t* first, uint32_t cnt,
                                                          const float* part, const float* gamma,
                                                          int R, RowArgs A, float* out) {
   __shared__ float s_mx[kGLBlock];
@@ -343,15 +409,24 @@ __global__ void __launch_bounds__(kGLBlock) k_gl_combine(const int32_t* rp, cons
   const bool active = sub < R;
   const bool scaled = A.max_in != nullptr;
   const float wr = (A.w && active) ? (float)A.w[sub] : 1.0f;
-  const uint32_t cnt = ctl[0];
+  const int32_t main_label = scaled && A.main_slot >= 0 ? A.anchors[A.main_slot] : -1;
   float mx_main = 0.0f;
   if (active) {
     for (int64_t h = (int64_t)blockIdx.x * gpb + grp; h < cnt; h += (int64_t)gridDim.x * gpb) {
       const int64_t i = list[h];
-      const int32_t c = scaled ? row_slot(A, i, rp[i], rp[i + 1]) : -1;
+      const int32_t c = scaled ? row_slot(A, i, rp[i], rp[i + 1], main_label) : -1;
       const float sc = scaled ? pair_scale(A, c, R, sub) : 1.0f;
       float tot = 0.0f;
-      for (int32_t it = first[h]; it < first[h + 1]; ++it) tot += part[(size_t)it * kGraphLMaxR + sub];
+      const int32_t i1 = first[h + 1];
+      for (int32_t it = first[h]; it < i1; it += 8) {  // eight loads in flight, added in order
+        float x[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+          x[k] = it + k < i1 ? part[(size_t)(it + k) * kGraphLMaxR + sub] : 0.0f;
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+          if (it + k < i1) tot += x[k];
+      }
       const float g = -0.5f * tot * wr;
       const size_t o = (size_t)i * R + sub;
       const float v = A.update ? gamma[o] * sc - A.alpha * g : g;
@@ -359,7 +434,15 @@ __global__ void __launch_bounds__(kGLBlock) k_gl_combine(const int32_t* rp, cons
       if (scaled) note_row(A, i, c, R, sub, sc, v, mx_main);
     }
   }
-  if (scaled) block_max_main(A, mx_main, s_mx, P, R, sub, grp, gpb, active);
+  if (scaled) {
+    s_mx[threadIdx.x] = mx_main;
+    __syncthreads();
+    if (grp == 0 && active && A.main_slot >= 0) {
+      float m = 0.0f;
+      for (int g = 0; g < gpb; ++g) m = fmaxf(m, s_mx[g * P + sub]);
+      raise_max(&A.max_out[(size_t)A.main_slot * R + sub], m);
+    }
+  }
 }
 
 // Items of the heavy rows (one workgroup): first[h] = the first item of
@@ -408,7 +491,8 @@ __global__ void __launch_bounds__(1024) k_gl_descend_small(const int32_t* rp_g,
                                                            const int32_t* comp,
                                                            const int32_t* aslot, int32_t n,
                                                            int32_t ncomp, int R, float alpha,
-                                                           int64_t steps, int shift, float* gamma,
+                                                           int64_t steps, int shift,
+                                                           const float* start, float* gamma,
                                                            int32_t* exps) {
   extern __shared__ uint32_t sm[];
   float* G0 = (float*)sm;
@@ -432,7 +516,7 @@ __global__ void __launch_bounds__(1024) k_gl_descend_small(const int32_t* rp_g,
   const uint32_t thresh = (uint32_t)(127 + shift) << 23;
   const float down = __uint_as_float((uint32_t)(127 - shift) << 23);
   for (int32_t i = threadIdx.x; i < n; i += blockDim.x) {
-    G0[i] = gamma[(size_t)i * R + r];
+    G0[i] = start[(size_t)i * R + r];
     cs[i] = rp[i + 1] > rp[i] ? aslot[comp[i]] : -1;
   }
   for (int32_t c = threadIdx.x; c < 3 * ncomp; c += blockDim.x) mx[c] = 0;
@@ -540,12 +624,15 @@ __global__ void k_gl_scales(const int32_t* rp, const int32_t* comp, const int32_
   }
 }
 
-// Rows longer than kGLHeavy, in any order (each is summed on its own).
-__global__ void k_gl_heavy_list(const int32_t* rp, int32_t n, int32_t* list, uint32_t* count) {
+// Rows longer than kGLHeavy and rows longer than kGLMid, in any order (each is
+// summed on its own).
+__global__ void k_gl_heavy_list(const int32_t* rp, int32_t n, int32_t* list, int32_t* mid,
+                                uint32_t* ctl) {
   for (int64_t b = (int64_t)blockIdx.x * blockDim.x; b < n; b += (int64_t)gridDim.x * blockDim.x) {
     const int64_t i = b + threadIdx.x;
-    const bool heavy = i < n && rp[i + 1] - rp[i] > kGLHeavy;
-    wave_append(heavy, (int32_t)i, list, count);
+    const int32_t d = i < n ? rp[i + 1] - rp[i] : 0;
+    wave_append(d > kGLHeavy, (int32_t)i, list, ctl);
+    wave_append(d > kGLMid && d <= kGLHeavy, (int32_t)i, mid, ctl + 2);
   }
 }
 
@@ -664,13 +751,14 @@ int grid_for_gl(int64_t work, int block) {
   return (int)std::max<int64_t>(1, std::min<int64_t>((work + block - 1) / block, 65536));
 }
 
-int rows_grid(int32_t n, int R) {
-  const int gpb = kGLBlock / lanes_for(R);
-  int64_t g = ((int64_t)n + gpb - 1) / gpb;
-  return (int)std::max<int64_t>(1, std::min<int64_t>(g, 65536));
+// Workgroups of a pass whose rows take P lanes: a few rounds of short rows per
+// workgroup, so that its start and its share of the maxima cost little.
+int pass_grid(int32_t n, int P) {
+  const int gpb = kGLBlock / P;
+  return (int)std::max<int64_t>(1, std::min<int64_t>(((int64_t)n + gpb - 1) / gpb, 4096));
 }
 
-// graphL control words in the workspace: heavy rows, their items
+// graphL control words in the workspace: heavy rows, their items, mid rows
 uint32_t* gl_ctl(fi_graph* g) { return (uint32_t*)(g->ws + g->L.glctl); }
 
 // Descent scales in the caller's buffer: exponents, then three max buffers,
@@ -680,29 +768,49 @@ size_t aux_part(const fi_graph* g, int R) {
   return (4 * c * (size_t)R + 255) / 256 * 256;
 }
 
+template <int P, int V>
+void launch_pass(fi_graph* g, const GLPlan& plan, const float* gin, int R, const RowArgs& A,
+                 float* out, hipStream_t s) {
+  hipLaunchKernelGGL((k_gl_pass<P, V>), dim3(pass_grid(g->dg.n, P)), dim3(kGLBlock), 0, s,
+                     g->dg.row_ptr, g->dg.adj, g->dg.n, plan, gin, R, A, out);
+}
+
 hipError_t launch_rows(fi_graph* g, const float* gin, int R, const RowArgs& A, float* out,
                        hipStream_t s) {
   const Layout& L = g->L;
-  int32_t* list = (int32_t*)(g->ws + L.glheavy);
-  int32_t* first = (int32_t*)(g->ws + L.glfirst);
-  int2* items = (int2*)(g->ws + L.glitems);
-  float* part = (float*)(g->ws + L.glpart);
-  uint32_t* ctl = gl_ctl(g);
-  if (R % 4 == 0 && (uintptr_t)gin % 16 == 0 && (uintptr_t)out % 16 == 0)
-    hipLaunchKernelGGL(k_gl_rows4, dim3(rows_grid(g->dg.n, R / 4)), dim3(kGLBlock), 0, s,
-                       g->dg.row_ptr, g->dg.adj, g->dg.n, gin, R, A, out);
-  else
-    hipLaunchKernelGGL(k_gl_rows, dim3(rows_grid(g->dg.n, R)), dim3(kGLBlock), 0, s,
-                       g->dg.row_ptr, g->dg.adj, g->dg.n, gin, R, A, out);
+  const int32_t* first = (const int32_t*)(g->ws + L.glfirst);
+  GLPlan plan;
+  plan.heavy = (const int32_t*)(g->ws + L.glheavy);
+  plan.items = (const int2*)(g->ws + L.glitems);
+  plan.part = (float*)(g->ws + L.glpart);
+  plan.mid = (const int32_t*)(g->ws + L.glmid);
+  plan.nitems = (uint32_t)g->gl_nitems;
+  plan.nmid = (uint32_t)g->gl_nmid;
+  // four restarts per lane when each vertex's R floats are whole aligned float4s
+  if (R % 4 == 0 && (uintptr_t)gin % 16 == 0 && (uintptr_t)out % 16 == 0) {
+    switch (lanes_for(R / 4)) {
+      case 1: launch_pass<1, 4>(g, plan, gin, R, A, out, s); break;
+      case 2: launch_pass<2, 4>(g, plan, gin, R, A, out, s); break;
+      case 4: launch_pass<4, 4>(g, plan, gin, R, A, out, s); break;
+      case 8: launch_pass<8, 4>(g, plan, gin, R, A, out, s); break;
+      default: launch_pass<16, 4>(g, plan, gin, R, A, out, s); break;
+    }
+  } else {
+    switch (lanes_for(R)) {
+      case 1: launch_pass<1, 1>(g, plan, gin, R, A, out, s); break;
+      case 2: launch_pass<2, 1>(g, plan, gin, R, A, out, s); break;
+      case 4: launch_pass<4, 1>(g, plan, gin, R, A, out, s); break;
+      case 8: launch_pass<8, 1>(g, plan, gin, R, A, out, s); break;
+      case 16: launch_pass<16, 1>(g, plan, gin, R, A, out, s); break;
+      case 32: launch_pass<32, 1>(g, plan, gin, R, A, out, s); break;
+      default: launch_pass<64, 1>(g, plan, gin, R, A, out, s); break;
+    }
+  }
   if (g->gl_nheavy == 0) return hipGetLastError();
-  const int cgrid = (int)std::min<int64_t>((int64_t)L.glicap, 8192);
-  hipLaunchKernelGGL(k_gl_chunks, dim3(cgrid), dim3(kGLBlock), 0, s, g->dg.row_ptr, g->dg.adj, list,
-                     items, ctl, gin, R, A, part);
-  const int64_t hcap = g->dg.nnz / kGLHeavy + 1;
-  const int hgrid = (int)std::max<int64_t>(1, std::min<int64_t>(hcap / (kGLBlock / lanes_for(R)) + 1,
-                                                                4096));
-  hipLaunchKernelGGL(k_gl_combine, dim3(hgrid), dim3(kGLBlock), 0, s, g->dg.row_ptr, list, first,
-                     ctl, part, gin, R, A, out);
+  const uint32_t nheavy = (uint32_t)g->gl_nheavy, rows_per_block = kGLBlock / lanes_for(R);
+  const int hgrid = (int)std::min<uint32_t>((nheavy + rows_per_block - 1) / rows_per_block, 4096);
+  hipLaunchKernelGGL(k_gl_combine, dim3(hgrid), dim3(kGLBlock), 0, s, g->dg.row_ptr, plan.heavy, first,
+                     nheavy, plan.part, gin, R, A, out);
   return hipGetLastError();
 }
 
@@ -715,18 +823,20 @@ hipError_t graphl_setup(fi_graph* g, hipStream_t s) {
   int32_t* first = (int32_t*)(g->ws + L.glfirst);
   int2* items = (int2*)(g->ws + L.glitems);
   uint32_t* ctl = gl_ctl(g);
-  hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s, ctl, (int64_t)2, 0u);
+  hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s, ctl, (int64_t)3, 0u);
   if (g->dg.n > 0) {
     const int grid =
         (int)std::max<int64_t>(1, std::min<int64_t>(((int64_t)g->dg.n + 255) / 256, 16384));
     hipLaunchKernelGGL(k_gl_heavy_list, dim3(grid), dim3(256), 0, s, g->dg.row_ptr, g->dg.n, list,
-                       ctl);
+                       (int32_t*)(g->ws + L.glmid), ctl);
     hipLaunchKernelGGL(k_gl_plan, dim3(1), dim3(1024), 0, s, g->dg.row_ptr, list, ctl, first, items);
   }
-  uint32_t cnt[2] = {0, 0};
+  uint32_t cnt[3] = {0, 0, 0};
   hipError_t e = hipMemcpyAsync(cnt, ctl, sizeof(cnt), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   g->gl_nheavy = (int32_t)cnt[0];
+  g->gl_nitems = (int32_t)cnt[1];
+  g->gl_nmid = (int32_t)cnt[2];
   return e == hipSuccess ? hipGetLastError() : e;
 }
 
@@ -784,20 +894,29 @@ int fi_graphl_aux_size(fi_graph* g, int32_t R, size_t* out_bytes) {
   return FI_OK;
 }
 
-int fi_graphl_descend(fi_graph* g, float* d_gamma, float* d_work, int32_t R, float alpha,
-                      int64_t steps, int32_t rescale_log2, void* d_aux, size_t aux_bytes,
-                      void* stream) {
+}  // extern "C"
+
+namespace {
+
+// The descent from `start` (d_gamma itself, or another buffer, which is only
+// read) into d_gamma, with d_work as the other buffer.
+int descend(fi_graph* g, const float* start, float* d_gamma, float* d_work, int32_t R, float alpha,
+            int64_t steps, int32_t rescale_log2, void* d_aux, size_t aux_bytes, void* stream) {
   if (!g || g->is_batch || R < 1 || R > kGraphLMaxR || steps < 0) return FI_EINVAL;
   if (rescale_log2 == 0) rescale_log2 = 64;
   if (rescale_log2 < 1 || rescale_log2 > 100) return FI_EINVAL;
   const size_t part = aux_part(g, R);
   if (!d_aux || aux_bytes < 4 * part || ((uintptr_t)d_aux % 256)) return FI_EWORKSPACE;
-  if (g->dg.n > 0 && (!d_gamma || !d_work || d_gamma == d_work)) return FI_EINVAL;
+  if (g->dg.n > 0 && (!start || !d_gamma || !d_work || d_gamma == d_work || start == d_work))
+    return FI_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   char* aux = (char*)d_aux;
   // exponents and all three max buffers start at zero
   hipLaunchKernelGGL(k_fill_u32, dim3(256), dim3(256), 0, s, (uint32_t*)aux,
                      (int64_t)(part), 0u);
+  const size_t bytes = sizeof(float) * (size_t)g->dg.n * R;
+  if (g->dg.n > 0 && steps == 0 && start != d_gamma)
+    FI_HIP(hipMemcpyAsync(d_gamma, start, bytes, hipMemcpyDeviceToDevice, s));
   if (g->dg.n == 0 || steps == 0) return hipGetLastError() == hipSuccess ? FI_OK : FI_EDEVICE;
   const int32_t ncomp = std::max<int32_t>(g->nanch, 1);
   const size_t lds = 12 * (size_t)g->dg.n + 16 * (size_t)ncomp;
@@ -809,23 +928,28 @@ int fi_graphl_descend(fi_graph* g, float* d_gamma, float* d_work, int32_t R, flo
                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_csr));
       hipLaunchKernelGGL(k_gl_descend_small<true>, dim3(R), dim3(1024), lds_csr, s, g->dg.row_ptr,
                          g->dg.adj, g->dg.comp, aslot, g->dg.n, ncomp, (int)R, alpha, steps,
-                         (int)rescale_log2, d_gamma, (int32_t*)aux);
+                         (int)rescale_log2, start, d_gamma, (int32_t*)aux);
     } else {
       FI_HIP(hipFuncSetAttribute((const void*)k_gl_descend_small<false>,
                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
       hipLaunchKernelGGL(k_gl_descend_small<false>, dim3(R), dim3(1024), lds, s, g->dg.row_ptr,
                          g->dg.adj, g->dg.comp, aslot, g->dg.n, ncomp, (int)R, alpha, steps,
-                         (int)rescale_log2, d_gamma, (int32_t*)aux);
+                         (int)rescale_log2, start, d_gamma, (int32_t*)aux);
     }
     return hipGetLastError() == hipSuccess ? FI_OK : FI_EDEVICE;
   }
-  float* buf[2] = {d_gamma, d_work};
+  // steps alternate between the buffers; from another start the last one ends
+  // in d_gamma, from d_gamma an odd number of steps ends in d_work
+  const bool own = start == d_gamma;
+  const float* in = start;
   for (int64_t k = 0; k < steps; ++k) {
+    float* outb = own ? (k & 1 ? d_gamma : d_work) : ((steps - 1 - k) & 1 ? d_work : d_gamma);
     RowArgs A{};
     A.alpha = alpha;
     A.update = 1;
     A.comp = g->dg.comp;
     A.aslot = (const int32_t*)(g->ws + g->L.aslot);
+    A.anchors = g->dg.anchors;
     A.exps = (int32_t*)aux;
     A.max_in = (const uint32_t*)(aux + (1 + k % 3) * part);
     A.max_out = (uint32_t*)(aux + (1 + (k + 1) % 3) * part);
@@ -833,12 +957,28 @@ int fi_graphl_descend(fi_graph* g, float* d_gamma, float* d_work, int32_t R, flo
     A.ncr = (int64_t)std::max<int32_t>(g->nanch, 1) * R;
     A.main_slot = g->gl_main_slot;
     A.shift = rescale_log2;
-    if (launch_rows(g, buf[k & 1], R, A, buf[(k + 1) & 1], s) != hipSuccess) return FI_EDEVICE;
+    if (launch_rows(g, in, R, A, outb, s) != hipSuccess) return FI_EDEVICE;
+    in = outb;
   }
-  if (steps & 1)
-    FI_HIP(hipMemcpyAsync(d_gamma, d_work, sizeof(float) * (size_t)g->dg.n * R,
-                          hipMemcpyDeviceToDevice, s));
+  if (in != d_gamma) FI_HIP(hipMemcpyAsync(d_gamma, in, bytes, hipMemcpyDeviceToDevice, s));
   return FI_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+int fi_graphl_descend(fi_graph* g, float* d_gamma, float* d_work, int32_t R, float alpha,
+                      int64_t steps, int32_t rescale_log2, void* d_aux, size_t aux_bytes,
+                      void* stream) {
+  return descend(g, d_gamma, d_gamma, d_work, R, alpha, steps, rescale_log2, d_aux, aux_bytes, stream);
+}
+
+int fi_graphl_descend_from(fi_graph* g, const float* d_gamma0, float* d_gamma, float* d_work,
+                           int32_t R, float alpha, int64_t steps, int32_t rescale_log2, void* d_aux,
+                           size_t aux_bytes, void* stream) {
+  if (d_gamma0 && d_gamma0 == d_gamma) return FI_EINVAL;
+  return descend(g, d_gamma0, d_gamma, d_work, R, alpha, steps, rescale_log2, d_aux, aux_bytes, stream);
 }
 
 int fi_graphl_scales(fi_graph* g, const void* d_aux, int32_t R, int32_t* d_out, void* stream) {

@@ -33,7 +33,7 @@ SYMBOLS = (
     "fi_bcloud_workspace_size", "fi_bcloud_fmax_for", "fi_bcloud_create", "fi_bcloud_destroy",
     "fi_bcloud_reset", "fi_bcloud_merge", "fi_sweep_bounded", "fi_bcloud_size", "fi_bcloud_read",
     "fi_bcloud_min", "fi_bcloud_stats", "fi_edge_list", "fi_switch_list", "fi_sweep_stats",
-    "fi_graphl_descend", "fi_graphl_aux_size", "fi_graphl_scales", "fi_set_sampler",
+    "fi_graphl_descend", "fi_graphl_descend_from", "fi_graphl_aux_size", "fi_graphl_scales", "fi_set_sampler",
     "fi_get_sampler", "fi_clean_workspace_size", "fi_clean", "fi_clean_no_alloc",
     "fi_batch_cloud_read", "fi_prof_phases", "fi_probe_gather",
 )
@@ -116,6 +116,7 @@ def load_library(path: str = LIB_PATH):
             "fi_switch_list": ([vp, vp, vp, i64, vp, vp], c.c_int),
             "fi_sweep_stats": ([vp, i64, i64, u64, vp, vp, vp], c.c_int),
             "fi_graphl_descend": ([vp, vp, vp, i32, c.c_float, i64, i32, vp, sz, vp], c.c_int),
+            "fi_graphl_descend_from": ([vp, vp, vp, vp, i32, c.c_float, i64, i32, vp, sz, vp], c.c_int),
             "fi_graphl_aux_size": ([vp, i32, P(sz)], c.c_int),
             "fi_graphl_scales": ([vp, vp, i32, vp, vp], c.c_int),
             "fi_set_sampler": ([vp, i32], c.c_int),
@@ -403,15 +404,27 @@ class Graph:
         R = gamma0.shape[1]
         g = out if out is not None else torch.empty((self.n, R), dtype=torch.float32,
                                                     device=self.device)
-        g.copy_(gamma0)
         work = torch.empty_like(g)
+        # a plain Gamma_0 that nothing else writes during the call is read where
+        # it lies; any other (another type, layout, device or stream, under
+        # autograd, or sharing memory with the result) is copied first
+        direct = (type(gamma0) is torch.Tensor and gamma0.dtype == torch.float32
+                  and gamma0.shape == g.shape and gamma0.device == g.device and gamma0.is_contiguous()
+                  and g.is_contiguous() and not gamma0.requires_grad and stream is None
+                  and gamma0.untyped_storage().data_ptr() != g.untyped_storage().data_ptr())
+        if not direct:
+            g.copy_(gamma0)
         size = ctypes.c_size_t()
         _check(self.lib.fi_graphl_aux_size(self.handle, R, ctypes.byref(size)), "graphl_aux_size")
         raw = torch.empty(size.value + 256, dtype=torch.uint8, device=self.device)
         ptr = (raw.data_ptr() + 255) // 256 * 256
-        _check(self.lib.fi_graphl_descend(self.handle, _ptr(g), _ptr(work), R, float(alpha),
-                                          int(steps), int(rescale_log2), ctypes.c_void_p(ptr),
-                                          size.value, _stream_ptr(stream)), "graphl_descend")
+        rest = (_ptr(g), _ptr(work), R, float(alpha), int(steps), int(rescale_log2),
+                ctypes.c_void_p(ptr), size.value, _stream_ptr(stream))
+        if direct:
+            rc = self.lib.fi_graphl_descend_from(self.handle, _ptr(gamma0), *rest)
+        else:
+            rc = self.lib.fi_graphl_descend(self.handle, *rest)
+        _check(rc, "graphl_descend")
         graph = self
 
         class Scales:
