@@ -183,6 +183,7 @@ struct Layout {
   size_t row_ptr, adj, edges, cedges, comp, word_comp, word_mask, word_main, anchors, tmp, cloud, ctl;
   size_t scratch;      // create temporaries, cloud staging, rounded graphL states
   size_t gl;           // graphL loss partials
+  size_t cntpart;      // exact count: per-block totals
   // whole-grid path: kGridSlots trees in flight
   size_t gpw, gql, gqh, gfb, gvis, gsb, grootkey, gctl, gbar;
   size_t hcap;         // heavy-list entries per list
@@ -237,7 +238,8 @@ int read_cloud_table(const CloudSlot* d_table, uint64_t tsize, fi_cloud_entry* h
                      int64_t* written, hipStream_t s);
 
 constexpr int kGraphLMaxR = 64;
-constexpr int kGraphLBlocks = 1024;
+constexpr int kGraphLBlocks = 2048;
+constexpr int kCountBlocks = 4096;  // workgroups of the exact count (max)
 constexpr int kGLHeavy = 256;   // graphL rows longer than this are cut into items
 constexpr int kGLMid = 48;      // and rows longer than this take a wave each
 constexpr int kGLChunk = 1024;  // CSR entries per item of a long graphL row
@@ -256,9 +258,9 @@ hipError_t launch_multi(fi_graph* g, const SweepArgs& a, int words, hipStream_t 
 int multi_words(const fi_graph* g, uint64_t trees);
 // exact count of up to 64 states given as one word per vertex (bit b = the
 // vertex's state in state b, set = -1; uint32 words for up to 32 states,
-// else uint64): counts[b] += frustrated edges
-hipError_t launch_count(const DevGraph& dg, const void* st, int32_t nstates, uint64_t* counts,
-                        hipStream_t s);
+// else uint64): counts[b] = frustrated edges; part: room for kCountBlocks x 64 words
+hipError_t launch_count(const DevGraph& dg, const void* st, int32_t nstates, uint64_t* part,
+                        uint64_t* counts, hipStream_t s);
 hipError_t graphl_setup(fi_graph* g, hipStream_t s);
 // distance sums to the highest-degree vertices, for the multi-tree path's
 // tree order (blocks; sets g->cent)

