@@ -64,6 +64,7 @@ struct BatchInfo {
   uint64_t tsize;
   int32_t n_max_small, n_max_large;
   int32_t n_small, n_large;
+  int64_t nnz_max;
   int per_cu[3][2];  // [block 256/512/1024][in LDS, in workspace]
   int mt_per_cu[3];  // multi-tree sweep, per block size
   int32_t n_max;
@@ -470,7 +471,8 @@ struct BatchMArgs {
   uint64_t* gctl;
   const int32_t* order;  // all graphs, largest first
   uint64_t* ticket;
-  int32_t G, groups;      // graphs; groups of 64 trees per graph
+  int32_t G, groups;      // graphs; groups of `per` trees per graph
+  int32_t per;            // at most 64
   int64_t trees;
   uint64_t seed;
   uint64_t tsize, cap;
@@ -485,8 +487,14 @@ struct BatchMArgs {
 // trees (rows of up to 64 edges: the wave pulls the unfinished vertices of
 // one 64-vertex word; longer rows: one per wave), separated by workgroup
 // barriers.
+//
+// Bound by the walk's vector instructions (93 % of 1.9e9 on 1,000 graphs of up
+// to 10,000 vertices, 64 trees: 3.7 ms of issue) and the latency of each
+// graph's levels.  1,024-thread workgroups are held to 64 registers, so that
+// two share a CU and hide one another's waits: 5.8 ms there, 6.4 with one per
+// CU, 7.3 with 512 threads, 9.9 with 256.
 template <int NT>
-__global__ void __launch_bounds__(NT) k_batch_multi(BatchMArgs B) {
+__global__ void __launch_bounds__(NT, NT == 1024 ? 8 : 1) k_batch_multi(BatchMArgs B) {
   constexpr int NW = NT / 64;
   constexpr int kPlanes = 8;
   const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
@@ -513,7 +521,7 @@ __global__ void __launch_bounds__(NT) k_batch_multi(BatchMArgs B) {
     __syncthreads();
     if (item >= nitems) break;
     const int32_t gi = B.order[item / B.groups];
-    const int64_t tb = (item % B.groups) * 64;
+    const int64_t tb = (item % B.groups) * B.per;
     const BatchGraph b = B.meta[gi];
     DevGraph G{};
     G.n = b.n;
@@ -531,7 +539,7 @@ __global__ void __launch_bounds__(NT) k_batch_multi(BatchMArgs B) {
     const int32_t n = b.n, nw = b.nwords;
     const int32_t* rp = G.row_ptr;
     const int32_t* cix = B.cidx + b.vo;
-    const int nvalid = (int)min<int64_t>(64, B.trees - tb);
+    const int nvalid = (int)min<int64_t>(B.per, B.trees - tb);
     const uint64_t valid = nvalid == 64 ? ~0ull : ((1ull << nvalid) - 1);
     const bool vlane = lane < nvalid;
     const KeyMix km = key_mix(tree_salt(B.seed, (uint64_t)(tb + lane)));
@@ -707,8 +715,53 @@ void launch_mt_batch(fi_graph* h, const BatchMArgs& a, hipStream_t s) {
   int64_t grid = (int64_t)std::max(1, bi->mt_per_cu[nt_index(NT)]) * h->cu_count;
   if (h->sched.grid > 0) grid = std::min<int64_t>(grid, h->sched.grid);
   grid = std::min<int64_t>(grid, (int64_t)bi->L.nmslots);
-  grid = std::max<int64_t>(1, std::min<int64_t>(grid, (int64_t)a.G * a.groups));
+  const int64_t items = (int64_t)a.G * a.groups;
+  // two items per workgroup or more before a CU holds a second one, which
+  // slows the largest graphs' (512 graphs of up to 40,000 vertices: 16.7 ms
+  // on 256 workgroups, 22.6 on 512)
+  grid = std::min<int64_t>(grid, std::max<int64_t>(h->cu_count, items / 2));
+  grid = std::max<int64_t>(1, std::min<int64_t>(grid, items));
   hipLaunchKernelGGL((k_batch_multi<NT>), dim3((int)grid), dim3(NT), 0, s, a);
+}
+
+// How a batch's trees are laid on the GPU: path 4, up to 64 trees of a graph
+// per workgroup, or path 1, one tree per workgroup.
+struct BatchPlan {
+  bool multi;
+  int block;
+  int32_t groups, per;  // path 4: groups of up to `per` trees of a graph
+};
+BatchPlan plan_batch(const fi_graph* h, int64_t trees) {
+  const BatchInfo* bi = (const BatchInfo*)h->batch;
+  BatchPlan p{};
+  p.groups = (int32_t)((trees + 63) / 64);
+  p.per = 64;
+  p.block = h->sched.block;
+  p.multi = h->sched.path == 4;
+  if (h->sched.path == 0) {
+    // Path 4 takes the longest graph's levels plus its share of the edge walks,
+    // path 1 the walks of every tree alone, slower past the graphs of which a
+    // CU holds several trees in LDS (us, fitted on uneven batches: 64 graphs of
+    // up to 1,000 vertices and 16 trees 311 and 93; 300 of up to 3,000 and 64
+    // trees 1,040 and 1,510; 64 of up to 10,000 and 64 trees 3,220 and 3,320;
+    // 1,000 of up to 10,000 and 64 trees 6,380 and 57,300).
+    const double walks = (double)trees * (double)bi->nnz_total;
+    const double t4 = 0.015 * (double)bi->nnz_max + 2e-6 * walks;
+    const double t1 = 60.0 + (bi->n_max > 4000 ? 1.8e-5 : 5e-6) * walks;
+    p.multi = trees >= 16 && t4 <= t1;
+    const size_t lds = 12 * (size_t)bi->n_max_small;
+    p.block = p.multi ? 1024
+              : lds > 65536 || trees * bi->G <= h->cu_count ? 1024
+              : lds <= 24576 && trees * bi->G > 16 * (int64_t)h->cu_count ? 256 : 512;
+    // few graphs: their trees are cut into smaller groups, down to eight, until
+    // every CU has one
+    while (p.multi && (int64_t)bi->G * p.groups * 2 <= h->cu_count && p.per > 8) {
+      p.groups *= 2;
+      p.per = (int32_t)((trees + p.groups - 1) / p.groups);
+      p.groups = (int32_t)((trees + p.per - 1) / p.per);  // none of them empty
+    }
+  }
+  return p;
 }
 
 bool host_offsets_ok(int32_t G, const int64_t* vo, const int64_t* no, int32_t* n_max) {
@@ -830,6 +883,9 @@ int fi_batch_create(int32_t G, const int64_t* h_vertex_offsets, const int64_t* h
   bi->n_max_large = n_max_large;
   bi->n_small = (int32_t)small.size();
   bi->n_large = (int32_t)large.size();
+  bi->nnz_max = 0;
+  for (int32_t g = 0; g < G; ++g)
+    bi->nnz_max = std::max(bi->nnz_max, h_nnz_offsets[g + 1] - h_nnz_offsets[g]);
   bi->L = L;
   h->ws = ws;
   h->ws_bytes = ws_bytes;
@@ -996,15 +1052,14 @@ int fi_batch_sweep(fi_graph* h, int64_t trees_per_graph, uint64_t seed, uint64_t
   a.cap = (uint64_t)bi->cap;
   a.slots = ws + L.slots;
   a.slot_stride = L.slot_stride;
-  const int nt = h->sched.block;
   // clouds, per-graph minima and counters, error bits and both tickets
   hipLaunchKernelGGL(k_b_reset, dim3(grid_for((int64_t)bi->tsize * bi->G, 256)), dim3(256), 0, s,
                      (CloudSlot*)(ws + L.clouds), (int64_t)bi->tsize * bi->G, (uint64_t*)(ws + L.gctl),
                      bi->G, ctl);
   hipError_t e = hipGetLastError();
-  // 64 trees of a graph per workgroup pass, unless a per-tree schedule is
-  // asked for or there are too few trees per graph to share a pass
-  const bool multi = h->sched.path == 4 || (h->sched.path == 0 && trees_per_graph >= 16);
+  const BatchPlan plan = plan_batch(h, trees_per_graph);
+  const bool multi = plan.multi;
+  const int nt = plan.block;
   if (multi && e == hipSuccess) {
     BatchMArgs m{};
     m.meta = a.meta;
@@ -1018,7 +1073,8 @@ int fi_batch_sweep(fi_graph* h, int64_t trees_per_graph, uint64_t seed, uint64_t
     m.order = (const int32_t*)(ws + L.order);
     m.ticket = ctl + kTicket0;
     m.G = bi->G;
-    m.groups = (int32_t)((trees_per_graph + 63) / 64);
+    m.groups = plan.groups;
+    m.per = plan.per;
     m.trees = trees_per_graph;
     m.seed = seed;
     m.tsize = bi->tsize;

@@ -687,9 +687,9 @@ class BatchGraph:
                         dtype=np.uint64).reshape(-1, 5)
 
     def set_schedule(self, block=256, grid=0, path=0):
-        """path 0: 64 trees of a graph per workgroup pass when at least 16 trees
-        per graph are swept, else one workgroup per tree; 1: one workgroup per
-        tree; 4: 64 trees per pass."""
+        """path 0: up to 64 trees of a graph per workgroup pass or one workgroup
+        per tree, by the graphs' sizes and the trees per graph (the block is
+        chosen too); 1: one workgroup per tree; 4: 64 trees per pass."""
         s = Schedule(path, block, grid, 512, 1)
         _check(self.lib.fi_set_schedule(self.handle, ctypes.byref(s)), "set_schedule")
 

@@ -108,3 +108,22 @@ def test_automatic_schedule_on_a_deep_graph():
     assert np.array_equal(sw, ref.trees[:, 0])
     assert np.array_equal(G.cloud(), ref.cloud)
     G.close()
+
+
+@pytest.mark.parametrize("graphs,n_hi,trees", [(3, 400, 15), (3, 4000, 33), (5, 4000, 100), (40, 4000, 65),
+                                               (140, 4000, 17)])
+def test_batch_automatic_schedule(graphs, n_hi, trees):
+    # one tree per workgroup, trees of few graphs cut into groups (33 trees:
+    # the last group shorter), whole groups of 64, and more graphs than half
+    # the CUs
+    from paper_2311_00869_amd import frustration as fr
+    gs = synth.config_batch(graphs, seed=6, n_lo=20, n_hi=n_hi)
+    seed = 77
+    B = fr.BatchGraph(gs, cloud_capacity_per_graph=trees)
+    mn, ds = B.sweep(trees, seed)
+    mn, ds = mn.cpu().numpy(), ds.cpu().numpy()
+    for i in range(0, graphs, max(1, graphs // 12)):
+        r = oracle.sweep(gs[i], seed, 0, trees, checks=False)
+        assert tuple(mn[i]) == r.best and ds[i] == len(r.cloud), i
+        assert np.array_equal(B.cloud(i), r.cloud), i
+    B.close()
