@@ -7,6 +7,8 @@
 #include <stdint.h>
 #include <stddef.h>
 
+#include <mutex>
+
 #include "frustration.h"
 
 struct fi_graph;
@@ -301,6 +303,9 @@ struct fi_graph {
   double prof_ms[2];
   int64_t prof_n[2];
   void* prof_events;  // std::vector of pending (start, stop, kernel)
+  // the automatic schedule's multi-tree sweeps of a graph whose trees fit LDS
+  std::mutex ms_lock;
+  hipEvent_t ms_done = nullptr;
   // batch mode
   bool is_batch;
   void* batch;        // fi::BatchInfo*

@@ -943,6 +943,7 @@ void fi_graph_destroy(fi_graph* g) {
     delete ev;
   }
   if (g->batch) batch_info_free(g->batch);
+  if (g->ms_done) (void)hipEventDestroy(g->ms_done);
   delete g;
 }
 

@@ -98,9 +98,25 @@ hipError_t launch_wg(fi_graph* g, const SweepArgs& a, int path, hipStream_t s) {
 // Trees per CU from which a small graph's sweep goes to the multi-tree path.
 constexpr uint64_t kMultiTreesPerCu = 3;
 
-int pick_path(fi_graph* g, uint64_t trees) {
+bool tree_fits_lds(const fi_graph* g) {
+  return wg_lds_bytes(g->dg.n, g->sampler) + 32768 <= (size_t)g->max_shared;
+}
+
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+    (void)hipGetLastError();  // (the null stream beside another stream's capture)
+    return true;
+  }
+  return st != hipStreamCaptureStatusNone;
+}
+
+// path 0: what the graph and the trees ask for; a sweep that is being captured
+// keeps to one tree per workgroup, in ordinary launches, where a tree fits LDS
+// and up to kDeepWork beyond.
+int pick_path(fi_graph* g, uint64_t trees, hipStream_t s) {
   const int32_t n = g->dg.n;
-  const bool fits = wg_lds_bytes(n, g->sampler) + 32768 <= (size_t)g->max_shared;
+  const bool fits = tree_fits_lds(g);
   if (g->sampler != kSamplerBfs) {
     // the other samplers run one tree per workgroup only
     if (g->sched.path == 1 && fits) return 1;
@@ -116,11 +132,12 @@ int pick_path(fi_graph* g, uint64_t trees) {
   // 556; 4,000 / 20,000: 1,000 trees 277 and 389), but on a deep graph it
   // pays its barriers at every level.
   const bool many = trees >= kMultiTreesPerCu * (uint64_t)g->cu_count && work >= kMultiMinWork;
-  if (fits && (!many || g->deep)) return 1;
+  const bool plain = g->deep || ((fits ? many : work <= kDeepWork) && capturing(s));
+  if (fits && (!many || plain)) return 1;
   // One tree per workgroup in workspace memory costs about m per tree (30,000
   // / 150,000: 1.5 ms for 100 trees, 7.3 ms for 1,000; the multi-tree path 0.4
   // and 0.77), but a level of it needs no grid barrier.
-  if (g->deep && work <= kDeepWork && g->L.nslots > 0) return 2;
+  if (plain && work <= kDeepWork && g->L.nslots > 0) return 2;
   return multi_words(g, trees) == 1 ? 4 : 5;
 }
 
@@ -145,7 +162,7 @@ int auto_block(fi_graph* g, int path, uint64_t trees) {
 
 hipError_t launch_sweep(fi_graph* g, const SweepArgs& a, hipStream_t s) {
   if (a.t1 <= a.t0) return hipSuccess;
-  int path = pick_path(g, a.t1 - a.t0);
+  int path = pick_path(g, a.t1 - a.t0, s);
   if (path == 0) return hipErrorInvalidValue;  // a sampler other than BFS above 1M vertices
   // the multi-tree path keeps no per-tree state words to hand out; it alone
   // gathers the cloud statistics
@@ -155,7 +172,16 @@ hipError_t launch_sweep(fi_graph* g, const SweepArgs& a, hipStream_t s) {
   void* tok = nullptr;
   if (prof_begin(g, s, &tok)) return hipErrorUnknown;
   hipError_t e;
-  if (path == 4 || path == 5) {
+  if ((path == 4 || path == 5) && g->sched.path == 0 && tree_fits_lds(g)) {
+    // Sweeps in LDS share no scratch memory, so those of one handle may overlap
+    // on several streams; here they take turns with it.
+    std::lock_guard<std::mutex> lock(g->ms_lock);
+    e = hipSuccess;
+    if (!g->ms_done) e = hipEventCreateWithFlags(&g->ms_done, hipEventDisableTiming);
+    else e = hipStreamWaitEvent(s, g->ms_done, 0);
+    if (e == hipSuccess) e = launch_multi(g, a, path == 5 ? 2 : 1, s);
+    if (e == hipSuccess) e = hipEventRecord(g->ms_done, s);
+  } else if (path == 4 || path == 5) {
     e = launch_multi(g, a, path == 5 ? 2 : 1, s);
   } else if (path == 3) {
     e = launch_grid(g, a, s);
