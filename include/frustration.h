@@ -333,7 +333,8 @@ int fi_batch_cloud_read(fi_graph* b, int32_t graph, fi_cloud_entry* h_out, int64
  *      of the SplitMix64 finalizer of salt xor (u << 32 | v); ties go to the
  *      earlier edge of the sorted edge list; the tree is the unique minimum
  *      spanning forest (computed here by Boruvka rounds).
- * Samplers other than BFS run one tree per workgroup (schedule paths 1 and
+ * Samplers other than BFS run one tree per workgroup (Kruskal) or per wave
+ * (the randomized DFS), whose threads `block` does not set (schedule paths 1 and
  * 2, whatever fi_set_schedule chose), so they need the tree in LDS (n up to
  * about 8,000 for Kruskal, 10,000 for DFS) or a workspace slot (n <= 10^6):
  * FI_ERANGE otherwise.  fi_sweep_stats takes BFS only (FI_EINVAL). */

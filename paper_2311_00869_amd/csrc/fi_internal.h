@@ -166,8 +166,7 @@ struct SweepArgs {
   // state puts it at -1; per upper-triangle edge, trees that switch it
   uint64_t* vminus;
   uint64_t* eswitch;
-  int sampler;              // kSampler*: the tree sampler (paths 1 and 2)
-  const int32_t* cptr;      // component offsets (randomized DFS stacks)
+  int sampler;              // kSampler*: the tree sampler
   // one-workgroup-per-tree scratch in workspace memory: [slots][slot_stride bytes]
   uint64_t* pw;
   size_t slot_stride;
@@ -255,6 +254,9 @@ void prof_end(fi_graph* g, hipStream_t s, void* token, int kernel);
 // launchers implemented in the .hip files
 hipError_t launch_sweep(fi_graph* g, const SweepArgs& a, hipStream_t s);
 hipError_t launch_grid(fi_graph* g, const SweepArgs& a, hipStream_t s);
+hipError_t launch_kruskal(fi_graph* g, const SweepArgs& a, int path, int nt, hipStream_t s);
+bool kruskal_forest_fits(const fi_graph* g);  // a workgroup's forest in LDS
+hipError_t launch_rdfs(fi_graph* g, const SweepArgs& a, int path, hipStream_t s);
 hipError_t launch_multi(fi_graph* g, const SweepArgs& a, int words, hipStream_t s);
 // words per vertex (1 or 2) of the automatic schedule's multi-tree pass over `trees` trees
 int multi_words(const fi_graph* g, uint64_t trees);

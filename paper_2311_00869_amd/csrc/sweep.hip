@@ -13,6 +13,7 @@
 //   k_sweep_multi - sweep_multi.hip: the whole grid sweeps 64 or 128 trees
 //                  at once with one bit per tree in the fields of each
 //                  vertex's record.
+// The samplers other than BFS are in sampler.hip.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -27,12 +28,8 @@ namespace fi {
 namespace {
 
 using wg::WgShared;
-using wg::wg_tree_sampled;
 
-// SMP: the sampler family the kernel is built for (BFS, Kruskal, or the
-// randomized DFS with the hybrid), so that each sampler's code is compiled
-// and register-allocated on its own.
-template <int NT, bool IN_LDS, int SMP>
+template <int NT, bool IN_LDS>
 __global__ void __launch_bounds__(NT) k_sweep_wg(DevGraph G, SweepArgs A) {
   __shared__ WgShared<NT> sh;
   extern __shared__ uint64_t dyn[];
@@ -46,53 +43,47 @@ __global__ void __launch_bounds__(NT) k_sweep_wg(DevGraph G, SweepArgs A) {
     pw = (uint64_t*)slot;
     q = (int32_t*)(slot + 8 * (size_t)G.n);
   }
-  int32_t* d = q + G.n;  // Kruskal's hooks (its LDS and slots have room)
-  for (uint64_t t = A.t0 + blockIdx.x; t < A.t1; t += gridDim.x)
-    wg_tree_sampled<NT, SMP>(G, A, t, pw, q, d, sh);
+  for (uint64_t t = A.t0 + blockIdx.x; t < A.t1; t += gridDim.x) {
+    // (the hybrid's other trees are randomized DFS)
+    if (A.sampler == kSamplerHybrid && wg::hybrid_coin(tree_salt(A.seed, t))) continue;
+    wg::wg_tree<NT>(G, A, t, pw, q, sh);
+  }
 }
 
-// tree words and queue; Kruskal also keeps a hook per vertex
+// tree words and queue; Kruskal also keeps a root list
 size_t wg_lds_bytes(int32_t n, int sampler = kSamplerBfs) {
   return (sampler == kSamplerKruskal ? 16 : 12) * (size_t)n;
 }
 
-template <int NT, int SMP>
-hipError_t launch_wg_smp(fi_graph* g, const SweepArgs& a, int path, hipStream_t s) {
+template <int NT>
+hipError_t launch_wg(fi_graph* g, const SweepArgs& a, int path, hipStream_t s) {
   const uint64_t ntrees = a.t1 - a.t0;
   const DevGraph& G = g->dg;
   int grid = g->sched.grid;
   if (path == 1) {
-    const size_t lds = wg_lds_bytes(G.n, a.sampler);
-    hipError_t ea = hipFuncSetAttribute((const void*)k_sweep_wg<NT, true, SMP>,
+    const size_t lds = wg_lds_bytes(G.n);
+    hipError_t ea = hipFuncSetAttribute((const void*)k_sweep_wg<NT, true>,
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (ea != hipSuccess) return ea;
     int per_cu = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_sweep_wg<NT, true, SMP>, NT, lds);
+    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_sweep_wg<NT, true>, NT, lds);
     if (e != hipSuccess) return e;
     if (per_cu < 1) per_cu = 1;
-    // at most six resident workgroups per CU: on a 1,000-vertex graph every
-    // sampler ran a quarter slower at eight (the limit its registers allow)
+    // at most six resident workgroups per CU: a 1,000-vertex graph ran a
+    // quarter slower at eight (the limit its registers allow)
     if (per_cu > 6) per_cu = 6;
     if (grid <= 0) grid = per_cu * g->cu_count;
     grid = (int)std::min<uint64_t>((uint64_t)grid, ntrees);
-    hipLaunchKernelGGL((k_sweep_wg<NT, true, SMP>), dim3(grid), dim3(NT), lds, s, G, a);
+    hipLaunchKernelGGL((k_sweep_wg<NT, true>), dim3(grid), dim3(NT), lds, s, G, a);
   } else {
     SweepArgs b = a;
     b.pw = (uint64_t*)(g->ws + g->L.slots);
     b.slot_stride = g->L.slot_stride;
     if (grid <= 0) grid = 8 * g->cu_count;
     grid = (int)std::min<uint64_t>(std::min<uint64_t>((uint64_t)grid, ntrees), g->L.nslots);
-    hipLaunchKernelGGL((k_sweep_wg<NT, false, SMP>), dim3(grid), dim3(NT), 0, s, G, b);
+    hipLaunchKernelGGL((k_sweep_wg<NT, false>), dim3(grid), dim3(NT), 0, s, G, b);
   }
   return hipGetLastError();
-}
-
-template <int NT>
-hipError_t launch_wg(fi_graph* g, const SweepArgs& a, int path, hipStream_t s) {
-  if (a.sampler == kSamplerKruskal) return launch_wg_smp<NT, kSamplerKruskal>(g, a, path, s);
-  if (a.sampler == kSamplerRdfs || a.sampler == kSamplerHybrid)
-    return launch_wg_smp<NT, kSamplerRdfs>(g, a, path, s);
-  return launch_wg_smp<NT, kSamplerBfs>(g, a, path, s);
 }
 
 // Trees per CU from which a small graph's sweep goes to the multi-tree path.
@@ -148,9 +139,14 @@ int pick_path(fi_graph* g, uint64_t trees, hipStream_t s) {
 // are few, a tree's own time counts, so up to one tree per CU takes 1,024
 // threads (n = 1,000: 43 us for 100 trees, 70 with 256; n = 4,000: 90 and
 // 213) and up to three per CU 512 (n = 1,000, 300 trees: 60 us, 78 with 256,
-// 74 with 1,024).  (BFS and Kruskal; the randomized DFS keeps most waves idle
-// and takes 256.)
+// 74 with 1,024).  (BFS and Kruskal; the randomized DFS has its own rule and
+// the hybrid's BFS trees take 256.)
 int auto_block(fi_graph* g, int path, uint64_t trees) {
+  // (Kruskal on 20,000 vertices, 100,000 edges: 100 trees 889 us with 1,024
+  // threads, 1,007 with 512; 500 trees 2,330 and 1,932.  With the forest in
+  // memory, 100,000 / 500,000: 512 trees 21.4 ms and 23.3)
+  if (path == 2 && g->sampler == kSamplerKruskal)
+    return trees <= (uint64_t)g->cu_count || !kruskal_forest_fits(g) ? 1024 : 512;
   if (path == 2) return g->dg.m <= 5 * (int64_t)g->dg.n ? 256 : 1024;
   if (path != 1 || g->sampler == kSamplerRdfs || g->sampler == kSamplerHybrid) return 256;
   const size_t lds = wg_lds_bytes(g->dg.n, g->sampler);
@@ -185,9 +181,14 @@ hipError_t launch_sweep(fi_graph* g, const SweepArgs& a, hipStream_t s) {
     e = launch_multi(g, a, path == 5 ? 2 : 1, s);
   } else if (path == 3) {
     e = launch_grid(g, a, s);
+  } else if (a.sampler == kSamplerKruskal) {
+    e = launch_kruskal(g, a, path, nt, s);
+  } else if (a.sampler == kSamplerRdfs) {
+    e = launch_rdfs(g, a, path, s);
   } else {
     e = nt == 1024 ? launch_wg<1024>(g, a, path, s) : nt == 512 ? launch_wg<512>(g, a, path, s)
                                                                  : launch_wg<256>(g, a, path, s);
+    if (e == hipSuccess && a.sampler == kSamplerHybrid) e = launch_rdfs(g, a, path, s);
   }
   prof_end(g, s, tok, 0);
   return e;
@@ -202,7 +203,6 @@ SweepArgs base_args(fi_graph* g, uint64_t seed) {
   SweepArgs a{};
   a.seed = seed;
   a.sampler = g->sampler;
-  a.cptr = (const int32_t*)(g->ws + g->L.cptr);
   return a;
 }
 }  // namespace
