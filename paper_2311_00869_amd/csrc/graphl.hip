@@ -201,8 +201,10 @@ struct GLPlan {
   const int32_t* heavy;  // rows of more than kGLHeavy entries, cut into items
   const int2* items;     // (place in heavy, chunk)
   float* part;           // [nitems][kGraphLMaxR]
-  const int32_t* mid;    // rows of kGLMid + 1 .. kGLHeavy entries
+  const int32_t* mid;    // rows of mid_len + 1 .. kGLHeavy entries
   uint32_t nitems, nmid;
+  int32_t mid_len;
+  uint32_t mid_at, short_at;  // the first block of the mid rows and of the short ones
 };
 
 constexpr int kGLBatch = 8;  // gathers of a row in flight per lane
@@ -210,25 +212,33 @@ constexpr int kGLBatch = 8;  // gathers of a row in flight per lane
 // Entries a[k] = e0 + k step (k < 8) that lie below e1, and y[k] = G[j] for the
 // lane's restarts, zero past e1.  All entries are loaded before the gathers
 // and all gathers are in flight together, those of the last few entries of a
-// row too.  With P >= 8 lanes to a row each lane loads one of the eight
-// entries and they are exchanged.
+// row too.  Of fewer than eight, with P >= 8 lanes to a row, each lane loads
+// one and they are exchanged.
 template <int P, int V>
-__device__ __forceinline__ void gather8(const uint32_t* adj, int64_t e0, int64_t e1, int64_t step,
+__device__ __forceinline__ void gather8(const uint32_t* adj, int32_t e0, int32_t e1, int32_t step,
                                         const float* gamma, int R, int sub, bool active,
                                         uint32_t* a, Lane<V>* y) {
+  if (e1 - e0 > (kGLBatch - 1) * step) {  // eight: nothing to mask
+    const int r0 = active ? V * sub : 0;
+#pragma unroll
+    for (int k = 0; k < kGLBatch; ++k) a[k] = adj[e0 + k * step];
+#pragma unroll
+    for (int k = 0; k < kGLBatch; ++k) y[k] = load_lane<V>(gamma + (size_t)(a[k] & kVertexMask) * R + r0);
+    return;
+  }
   if constexpr (P >= kGLBatch) {
     const int base = lane_id() & ~(P - 1);
-    const uint32_t mine = adj[min(e0 + (sub & (kGLBatch - 1)) * step, e1 - 1)];
+    const uint32_t mine = adj[e0 + min((sub & (kGLBatch - 1)) * step, e1 - e0 - 1)];
 #pragma unroll
     for (int k = 0; k < kGLBatch; ++k) a[k] = (uint32_t)__shfl((int)mine, base + k);
   } else {
 #pragma unroll
-    for (int k = 0; k < kGLBatch; ++k) a[k] = adj[min(e0 + k * step, e1 - 1)];
+    for (int k = 0; k < kGLBatch; ++k) a[k] = adj[e0 + min(k * step, e1 - e0 - 1)];
   }
 #pragma unroll
   for (int k = 0; k < kGLBatch; ++k) {
     y[k] = Lane<V>{};
-    if (active && e0 + k * step < e1)
+    if (active && k * step < e1 - e0)
       y[k] = load_lane<V>(gamma + (size_t)(a[k] & kVertexMask) * R + V * sub);
   }
 }
@@ -247,26 +257,26 @@ __device__ __forceinline__ void sign_scale(const uint32_t* a, const Lane<V>& sc,
   }
 }
 
-// Sum over entries e0, e0 + step, ... < e1, added in that order.  The scale is
-// asked for once the first gathers are in flight, so that its own loads do not
-// go before them.
+// Sum over entries e0, e0 + step, ... < e1, added in that order (the zeros past
+// e1 change no sum).  The scale is asked for once the first gathers are in
+// flight, so that its own loads do not go before them.
 template <int P, int V, class Scale>
-__device__ __forceinline__ Lane<V> row_sum(const uint32_t* adj, int64_t e0, int64_t e1, int64_t step,
+__device__ __forceinline__ Lane<V> row_sum(const uint32_t* adj, int32_t e0, int32_t e1, int32_t step,
                                            const float* gamma, int R, int sub, bool active,
                                            Scale scale) {
   Lane<V> acc{};
   Lane<V> sc{};
-  for (int64_t e = e0; e < e1; e += kGLBatch * step) {
+  for (int32_t left = e1 - e0; left > 0; left -= kGLBatch * step) {
+    const int32_t e = e1 - left;
     uint32_t a[kGLBatch];
     Lane<V> y[kGLBatch];
     gather8<P, V>(adj, e, e1, step, gamma, R, sub, active, a, y);
-    if (e == e0) sc = scale();
+    if (left == e1 - e0) sc = scale();
     sign_scale<V>(a, sc, y);
 #pragma unroll
     for (int k = 0; k < kGLBatch; ++k)
-      if (e + k * step < e1)
 #pragma unroll
-        for (int q = 0; q < V; ++q) acc.x[q] += y[k].x[q];
+      for (int q = 0; q < V; ++q) acc.x[q] += y[k].x[q];
   }
   return acc;
 }
@@ -277,51 +287,52 @@ __device__ __forceinline__ Lane<V> row_sum(const uint32_t* adj, int64_t e0, int6
 //   long rows (more than kGLHeavy entries): items of up to kGLChunk entries,
 //     one per workgroup, its groups striding over the item and their sums added
 //     in group order into part[item][r]; k_gl_combine adds a row's items in order
-//   rows of kGLMid + 1 .. kGLHeavy entries: one wave each, eight entries per
-//     group at a time, laid in LDS and added there in the row's order
+//   rows of mid_len + 1 .. kGLHeavy entries: one wave each, eight entries per
+//     group at a time, their sum carried from group to group in the row's order
 //   shorter rows: one group each
-// Longest first, so that no long chain starts last.  Every row but the long
+// Longest first, each kind from the block after the last one's, so that no long
+// chain starts last and a small graph's blocks have one each.  Every row but the long
 // ones is summed in its own order whatever P and V are, so the variants agree
 // bit for bit.  Bound by the rate of random line fetches (52 to 59 G/s of 128
 // bytes here; R = 32 gathers one line per entry), as long as a row's gathers
 // are in flight together: with a row's last few entries gathered one by one
 // and long rows in a launch of their own, 4M vertices and 16M edges at R = 32
-// took 3.28 ms per step (2.1 of it the maxima, raise_max), now 0.95 (0.72 for
-// a gradient); 100,000 / 500,000 took 76 us with rows up to 256 entries on one
-// group each, now 51.
-template <int P, int V>
-__global__ void __launch_bounds__(kGLBlock) k_gl_pass(const int32_t* rp, const uint32_t* adj,
+// took 3.28 ms per step (2.1 of it the maxima, raise_max), now 0.96 (0.73 for
+// a gradient); a gradient of 100,000 / 500,000 took 82 us with rows up to 256
+// entries on one group each, now 22, of 5,000 / 20,000 29 us, now 15.  SCALED keeps
+// the registers of the overflow policy out of gradients, four and five waves per
+// SIMD (200,000 / 2M at R = 64: 100 us; one kernel of 134 registers, three: 128).
+template <int P, int V, bool SCALED>
+__global__ void __launch_bounds__(kGLBlock, P * V < 16 ? 1 : SCALED ? 4 : 5) k_gl_pass(const int32_t* rp, const uint32_t* adj,
                                                       int32_t n, GLPlan L, const float* gamma, int R,
                                                       RowArgs A, float* out) {
   constexpr int kGroups = kGLBlock / P, kWaveGroups = 64 / P, NW = kGLBlock / 64;
-  constexpr int kStage = kWaveGroups * kGLBatch;  // entries a wave lays down at a time
-  __shared__ Lane<V> s_y[NW][kStage * P];
+  constexpr int kStage = kWaveGroups * kGLBatch;  // entries a wave takes at a time
   __shared__ float s_mx[kGLBlock * V];
   const int sub = threadIdx.x % P, grp = threadIdx.x / P;
   const int wave = threadIdx.x >> 6, wgrp = grp % kWaveGroups;
   const int r0 = V * sub;
   const bool active = r0 < R;
-  const bool scaled = A.max_in != nullptr;
-  const int32_t main_label = scaled && A.main_slot >= 0 ? A.anchors[A.main_slot] : -1;
+  const int32_t main_label = SCALED && A.main_slot >= 0 ? A.anchors[A.main_slot] : -1;
   Lane<V> wr, scm, mx;
 #pragma unroll
   for (int k = 0; k < V; ++k) {
     wr.x[k] = (A.w && active) ? (float)A.w[r0 + k] : 1.0f;
-    scm.x[k] = scaled && active ? pair_scale(A, A.main_slot, R, r0 + k) : 1.0f;
+    scm.x[k] = SCALED && active ? pair_scale(A, A.main_slot, R, r0 + k) : 1.0f;
     mx.x[k] = 0.0f;
   }
-  if (scaled)
+  if constexpr (SCALED)
     for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < A.ncr;
          k += (int64_t)gridDim.x * blockDim.x)
       A.max_clear[k] = 0;
   auto slot_of = [&](int32_t label) {
-    return !scaled ? -1 : label == main_label ? A.main_slot : A.aslot[label];
+    return !SCALED ? -1 : label == main_label ? A.main_slot : A.aslot[label];
   };
   auto scale_of = [&](int32_t c) {
     Lane<V> sc;
 #pragma unroll
     for (int k = 0; k < V; ++k)
-      sc.x[k] = !scaled || !active || c < 0 ? 1.0f
+      sc.x[k] = !SCALED || !active || c < 0 ? 1.0f
                 : c == A.main_slot          ? scm.x[k]
                                             : pair_scale(A, c, R, r0 + k);
     return sc;
@@ -339,7 +350,7 @@ __global__ void __launch_bounds__(kGLBlock) k_gl_pass(const int32_t* rp, const u
       v.x[k] = A.update ? self.x[k] * sc.x[k] - A.alpha * g : g;
     }
     store_lane<V>(out + o, v);
-    if (scaled)
+    if constexpr (SCALED)
 #pragma unroll
       for (int k = 0; k < V; ++k) note_row(A, i, c, R, r0 + k, sc.x[k], v.x[k], mx.x[k]);
   };
@@ -348,11 +359,11 @@ __global__ void __launch_bounds__(kGLBlock) k_gl_pass(const int32_t* rp, const u
   for (uint32_t it = blockIdx.x; it < L.nitems; it += gridDim.x) {
     const int2 hc = L.items[it];
     const int64_t i = L.heavy[hc.x];
-    const int64_t b0 = rp[i], b1 = rp[i + 1];
-    const int64_t e0 = b0 + (int64_t)hc.y * kGLChunk;
-    const int64_t e1 = min(b1, e0 + kGLChunk);
+    const int32_t b0 = rp[i], b1 = rp[i + 1];
+    const int32_t e0 = b0 + hc.y * kGLChunk;
+    const int32_t e1 = e0 + min(b1 - e0, kGLChunk);
     const Lane<V> acc = row_sum<P, V>(adj, e0 + grp, e1, kGroups, gamma, R, sub, active, [&] {
-      return scale_of(scaled ? row_slot(A, i, b0, b1, main_label) : -1);
+      return scale_of(SCALED ? row_slot(A, i, b0, b1, main_label) : -1);
     });
 #pragma unroll
     for (int k = 0; k < V; ++k) s_mx[threadIdx.x * V + k] = acc.x[k];
@@ -366,46 +377,47 @@ __global__ void __launch_bounds__(kGLBlock) k_gl_pass(const int32_t* rp, const u
   }
 
   // rows of one wave each
-  const int64_t gwave = (int64_t)blockIdx.x * NW + wave, nwaves = (int64_t)gridDim.x * NW;
-  for (int64_t m = gwave; m < (int64_t)L.nmid; m += nwaves) {
+  auto block_from = [&](uint32_t at) {
+    return (int64_t)(blockIdx.x >= at ? blockIdx.x - at : blockIdx.x + gridDim.x - at);
+  };
+  const int64_t nwaves = (int64_t)gridDim.x * NW;
+  for (int64_t m = block_from(L.mid_at) * NW + wave; m < (int64_t)L.nmid; m += nwaves) {
     const int64_t i = L.mid[m];
-    const int64_t b0 = rp[i], b1 = rp[i + 1];
-    const int32_t label = scaled ? A.comp[i] : -1;
+    const int32_t b0 = rp[i], b1 = rp[i + 1];
+    const int32_t label = SCALED ? A.comp[i] : -1;
     const Lane<V> self = load_self(i);
     int32_t c = -1;
     Lane<V> acc{}, sc{};
-    for (int64_t e = b0; e < b1; e += kStage) {
-      const int64_t eg = e + wgrp * kGLBatch;
+    for (int32_t left = b1 - b0; left > 0; left -= kStage) {
+      const int32_t mine = left - wgrp * kGLBatch;  // entries from the group's first on
       uint32_t a[kGLBatch];
-      Lane<V> y[kGLBatch];
-      if (eg < b1) gather8<P, V>(adj, eg, b1, 1, gamma, R, sub, active, a, y);
-      if (e == b0) {
+      Lane<V> y[kGLBatch] = {};
+      if (mine > 0) gather8<P, V>(adj, b1 - mine, b1, 1, gamma, R, sub, active, a, y);
+      if (left == b1 - b0) {
         c = slot_of(label);
         sc = scale_of(c);
       }
-      if (eg < b1) sign_scale<V>(a, sc, y);
+      if (mine > 0) sign_scale<V>(a, sc, y);
 #pragma unroll
-      for (int k = 0; k < kGLBatch; ++k)
-        if (eg + k < b1) s_y[wave][(wgrp * kGLBatch + k) * P + sub] = y[k];
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      const int cnt = (int)min<int64_t>(kStage, b1 - e);
-      if (wgrp == 0) {
-        for (int k = 0; k < cnt; ++k) {
-          const Lane<V> t = s_y[wave][k * P + sub];
+      for (int w = 0; w < kWaveGroups; ++w) {
+        // (past the row's end y is zero)
+        Lane<V> t = acc;
 #pragma unroll
-          for (int q = 0; q < V; ++q) acc.x[q] += t.x[q];
-        }
+        for (int k = 0; k < kGLBatch; ++k)
+#pragma unroll
+          for (int q = 0; q < V; ++q) t.x[q] += y[k].x[q];
+#pragma unroll
+        for (int q = 0; q < V; ++q) acc.x[q] = __shfl(t.x[q], w * P + sub);
       }
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
     if (wgrp == 0 && active) finish(i, c, sc, self, acc);
   }
 
   // short rows
-  for (int64_t i = (int64_t)blockIdx.x * kGroups + grp; i < n; i += (int64_t)gridDim.x * kGroups) {
-    const int64_t e0 = rp[i], e1 = rp[i + 1];
-    if (e1 - e0 > kGLMid) continue;
-    const int32_t label = scaled ? A.comp[i] : -1;
+  for (int64_t i = block_from(L.short_at) * kGroups + grp; i < n; i += (int64_t)gridDim.x * kGroups) {
+    const int32_t e0 = rp[i], e1 = rp[i + 1];
+    if (e1 - e0 > L.mid_len) continue;
+    const int32_t label = SCALED ? A.comp[i] : -1;
     const Lane<V> self = load_self(i);
     int32_t c = -1;
     Lane<V> sc = scale_of(-1);  // (of a row without entries)
@@ -417,7 +429,7 @@ __global__ void __launch_bounds__(kGLBlock) k_gl_pass(const int32_t* rp, const u
     if (active) finish(i, c, sc, self, acc);
   }
 
-  if (scaled) {
+  if constexpr (SCALED) {
 #pragma unroll
     for (int k = 0; k < V; ++k) s_mx[threadIdx.x * V + k] = mx.x[k];
     __syncthreads();
@@ -657,15 +669,15 @@ __global__ void k_gl_scales(const int32_t* rp, const int32_t* comp, const int32_
   }
 }
 
-// Rows longer than kGLHeavy and rows longer than kGLMid, in any order (each is
+// Rows longer than kGLHeavy and rows longer than mid_len, in any order (each is
 // summed on its own).
-__global__ void k_gl_heavy_list(const int32_t* rp, int32_t n, int32_t* list, int32_t* mid,
-                                uint32_t* ctl) {
+__global__ void k_gl_heavy_list(const int32_t* rp, int32_t n, int32_t mid_len, int32_t* list,
+                                int32_t* mid, uint32_t* ctl) {
   for (int64_t b = (int64_t)blockIdx.x * blockDim.x; b < n; b += (int64_t)gridDim.x * blockDim.x) {
     const int64_t i = b + threadIdx.x;
     const int32_t d = i < n ? rp[i + 1] - rp[i] : 0;
     wave_append(d > kGLHeavy, (int32_t)i, list, ctl);
-    wave_append(d > kGLMid && d <= kGLHeavy, (int32_t)i, mid, ctl + 2);
+    wave_append(d > mid_len && d <= kGLHeavy, (int32_t)i, mid, ctl + 2);
   }
 }
 
@@ -778,11 +790,22 @@ int grid_for_gl(int64_t work, int block) {
   return (int)std::max<int64_t>(1, std::min<int64_t>((work + block - 1) / block, 65536));
 }
 
-// Workgroups of a pass whose rows take P lanes: a few rounds of short rows per
-// workgroup, so that its start and its share of the maxima cost little.
+// Rows longer than this take a wave each: those that would hold up the other
+// rows of a wave, so it follows the mean length (us per gradient, R = 32: 1M /
+// 4M 172 with 48 or 256 and 160 with 64; 200,000 / 3M, 85 with 48, 94 with 256,
+// 82 with 90; 200,000 / 6M without skew 227 with 48, 196 with 180), unless there
+// are too few rows to fill the chip (4,000 / 100,000: 8.7 with 48, 10.4 with 150).
+int32_t mid_len(const fi_graph* g) {
+  const int64_t mean = g->dg.nnz / std::max<int32_t>(g->dg.n, 1);
+  return g->dg.n <= 8192 ? kGLMid : (int32_t)std::max<int64_t>(64, std::min<int64_t>(3 * mean, kGLHeavy));
+}
+
+// Workgroups of a pass's short rows, P lanes to a row: a few rounds each, so
+// that a workgroup's start and its share of the maxima cost little.
+constexpr int64_t kGLPassBlocks = 4096;
 int pass_grid(int32_t n, int P) {
   const int gpb = kGLBlock / P;
-  return (int)std::max<int64_t>(1, std::min<int64_t>(((int64_t)n + gpb - 1) / gpb, 4096));
+  return (int)std::max<int64_t>(1, std::min<int64_t>(((int64_t)n + gpb - 1) / gpb, kGLPassBlocks));
 }
 
 // graphL control words in the workspace: heavy rows, their items, mid rows
@@ -834,10 +857,21 @@ hipError_t launch_rows(fi_graph* g, const float* gin, int R, const RowArgs& A, f
   plan.mid = (const int32_t*)(g->ws + L.glmid);
   plan.nitems = (uint32_t)g->gl_nitems;
   plan.nmid = (uint32_t)g->gl_nmid;
+  plan.mid_len = mid_len(g);
+  constexpr int NW = kGLBlock / 64;
   with_lanes(R, (uintptr_t)gin % 16 == 0 && (uintptr_t)out % 16 == 0, [&](auto p, auto v) {
     constexpr int P = decltype(p)::value, V = decltype(v)::value;
-    hipLaunchKernelGGL((k_gl_pass<P, V>), dim3(pass_grid(g->dg.n, P)), dim3(kGLBlock), 0, s,
-                       g->dg.row_ptr, g->dg.adj, g->dg.n, plan, gin, R, A, out);
+    // (so that the blocks of a small graph have one kind of row each)
+    const int64_t mid = (plan.nmid + NW - 1) / NW;
+    const int grid = (int)std::min<int64_t>(plan.nitems + mid + pass_grid(g->dg.n, P), kGLPassBlocks);
+    plan.mid_at = plan.nitems % grid;
+    plan.short_at = (plan.nitems + mid) % grid;
+    if (A.max_in)
+      hipLaunchKernelGGL((k_gl_pass<P, V, true>), dim3(grid), dim3(kGLBlock), 0, s, g->dg.row_ptr,
+                         g->dg.adj, g->dg.n, plan, gin, R, A, out);
+    else
+      hipLaunchKernelGGL((k_gl_pass<P, V, false>), dim3(grid), dim3(kGLBlock), 0, s, g->dg.row_ptr,
+                         g->dg.adj, g->dg.n, plan, gin, R, A, out);
   });
   if (g->gl_nheavy == 0) return hipGetLastError();
   const uint32_t nheavy = (uint32_t)g->gl_nheavy, rows_per_block = kGLBlock / lanes_for(R);
@@ -860,7 +894,7 @@ hipError_t graphl_setup(fi_graph* g, hipStream_t s) {
   if (g->dg.n > 0) {
     const int grid =
         (int)std::max<int64_t>(1, std::min<int64_t>(((int64_t)g->dg.n + 255) / 256, 16384));
-    hipLaunchKernelGGL(k_gl_heavy_list, dim3(grid), dim3(256), 0, s, g->dg.row_ptr, g->dg.n, list,
+    hipLaunchKernelGGL(k_gl_heavy_list, dim3(grid), dim3(256), 0, s, g->dg.row_ptr, g->dg.n, mid_len(g), list,
                        (int32_t*)(g->ws + L.glmid), ctl);
     hipLaunchKernelGGL(k_gl_plan, dim3(1), dim3(1024), 0, s, g->dg.row_ptr, list, ctl, first, items);
   }
