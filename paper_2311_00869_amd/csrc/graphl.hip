@@ -518,142 +518,221 @@ __global__ void __launch_bounds__(1024) k_gl_plan(const int32_t* rp, const int32
   }
 }
 
-// The whole descent on a small graph without long rows: one workgroup per
-// restart, Gamma's column in LDS (ping-pong), and the per-component maxima
-// and scales of the overflow policy in LDS too, so the steps run with no
-// launch between them.  Same rows, same order, same operations as the
-// per-step kernels.  LDS: 8n (Gamma) + 4n (component slots) + 16 C bytes,
-// plus the CSR itself (4(n+1) + 4 nnz) when it fits, so that a step touches
-// no global memory.
+// The whole descent on a small graph: one workgroup per
+// restart, Gamma's column in LDS (ping-pong), and the per-component overflow
+// flags and scales in LDS too, so the steps run with no launch between them.
+// Same rows, same order, same operations as the per-step kernels; a row of more
+// than kGLHeavy entries by a wave, whose lanes are the `groups` of k_gl_pass.
+//
+// A step is bound by the CU's LDS gathers and by the instructions around them
+// (a wave's instruction counts its longest row), so each value is kept beside
+// its negation and an entry is the LDS offset of the one it adds: a gather and
+// a multiply-add.  The leading entries of a row sit in registers, missing ones
+// point at a zero, and rows are dealt by length so that a wave's are alike.
+// The overflow policy compares a component's maximum with one threshold, so a
+// value that reaches it sets a flag.  500 steps at R = 32, us: 1,000 vertices,
+// 5,000 edges 475 (the row's entries decoded in every step, the CSR in LDS: 755),
+// 300 / 1,200 262 (485), 4,096 / 12,000 1,180 (2,425); with hubs, 1,000 / 5,000
+// 3,420 (a launch per step: 6,930).
 constexpr int kSmallDescentN = 4096;
-constexpr int kSmallRows = kSmallDescentN / 1024;  // rows per thread of the fused descent
-constexpr int kHeldEntries = 8;  // leading entries of each row kept in registers
-constexpr size_t kSmallDescentLds = 128 * 1024;
+constexpr size_t kSmallDescentLds = 152 * 1024;
+// Beyond, a restart's one CU takes longer than a launch per step (500 steps, us:
+// 4,000 / 60,000 4,770 and 6,300, 1,000 / 60,000 5,990 and 5,380, 1,000 / 200,000
+// 28,600 and 6,000); with long rows from half as many (4,000 / 30,000 6,120 and
+// 8,090, 4,000 / 60,000 9,900 and 8,100).
+constexpr int64_t kSmallEntries = 1 << 17;
+constexpr int kSmallLens = 64;  // row lengths told apart (the last: over kGLHeavy)
+struct SmallHeavy {  // a long row
+  int32_t row, begin, end, slot;
+};
 
-template <bool CSR_IN_LDS>
-__global__ void __launch_bounds__(1024) k_gl_descend_small(const int32_t* rp_g,
-                                                           const uint32_t* adj_g,
+// leading entries of a row in registers, for so many rows per thread
+constexpr int held_entries(int q) { return q == 1 ? 32 : q == 2 ? 24 : 16; }
+// LDS bytes of the two columns: n pairs (value, negation), then a zero
+constexpr size_t small_column(int q) { return 8 * ((size_t)1024 * q + 1); }
+
+template <int Q>
+__global__ void __launch_bounds__(1024) k_gl_descend_small(const int32_t* rp, const uint32_t* adj,
                                                            const int32_t* comp,
                                                            const int32_t* aslot, int32_t n,
-                                                           int32_t ncomp, int R, float alpha,
-                                                           int64_t steps, int shift,
+                                                           int32_t ncomp, int32_t nheavy, int groups, int R,
+                                                           float alpha, int64_t steps, int shift,
                                                            const float* start, float* gamma,
                                                            int32_t* exps) {
+  constexpr int H = held_entries(Q), kBatch = Q == 4 ? 4 : 8, kTail = 8;
+  constexpr uint32_t kCol = (uint32_t)small_column(Q), kZero = 8 * 1024 * Q;
   extern __shared__ uint32_t sm[];
-  float* G0 = (float*)sm;
-  float* G1 = G0 + n;
-  int32_t* cs = (int32_t*)(G1 + n);
-  uint32_t* mx = (uint32_t*)(cs + n);  // [3][ncomp]
+  __shared__ uint32_t lens[kSmallLens];
+  char* const lds = (char*)sm;
+  uint32_t* mx = (uint32_t*)(lds + 2 * kCol);  // [3][ncomp]
   int32_t* ex = (int32_t*)(mx + 3 * ncomp);
-  const int32_t* rp = rp_g;
-  const uint32_t* adj = adj_g;
-  if (CSR_IN_LDS) {
-    int32_t* rp_l = ex + ncomp;
-    uint32_t* adj_l = (uint32_t*)(rp_l + n + 1);
-    const int32_t nnz = rp_g[n];
-    for (int32_t i = threadIdx.x; i <= n; i += blockDim.x) rp_l[i] = rp_g[i];
-    for (int32_t e = threadIdx.x; e < nnz; e += blockDim.x) adj_l[e] = adj_g[e];
-    rp = rp_l;
-    adj = adj_l;
-    __syncthreads();
-  }
-  const int r = blockIdx.x;
+  SmallHeavy* heavy = (SmallHeavy*)(ex + ncomp);
+  uint32_t* perm = (uint32_t*)(lds + kCol);  // (until the first step)
+  const int tid = threadIdx.x, r = blockIdx.x;
   const uint32_t thresh = (uint32_t)(127 + shift) << 23;
   const float down = __uint_as_float((uint32_t)(127 - shift) << 23);
-  for (int32_t i = threadIdx.x; i < n; i += blockDim.x) {
-    G0[i] = start[(size_t)i * R + r];
-    cs[i] = rp[i + 1] > rp[i] ? aslot[comp[i]] : -1;
+  auto offset = [](uint32_t a) { return 8 * (a & kVertexMask) + (a >> 31) * 4; };
+  auto len_of = [&](int32_t i) {
+    const int32_t d = rp[i + 1] - rp[i];
+    return d > kGLHeavy ? kSmallLens - 1 : min(d, kSmallLens - 2);
+  };
+  // the offsets of entries e .. e + kTail - 1, as far as below end (those behind a
+  // row are read with it: the edge list lies behind the last one)
+  auto entries = [&](int32_t e, int32_t end, uint32_t* o) {
+#pragma unroll
+    for (int t = 0; t < kTail; ++t) o[t] = adj[e + t];
+#pragma unroll
+    for (int t = 0; t < kTail; ++t) o[t] = e + t < end ? offset(o[t]) : kZero;
+  };
+
+  if (tid < kSmallLens) lens[tid] = 0;
+  for (int32_t c = tid; c < 3 * ncomp; c += 1024) mx[c] = 0;
+  for (int32_t c = tid; c < ncomp; c += 1024) ex[c] = 0;
+  if (tid < 2) *(float2*)(lds + tid * kCol + kZero) = make_float2(0.0f, 0.0f);
+  for (int32_t i = tid; i < n; i += 1024) {
+    const float v = start[(size_t)i * R + r];
+    *(float2*)(lds + 8 * i) = make_float2(v, -v);
   }
-  for (int32_t c = threadIdx.x; c < 3 * ncomp; c += blockDim.x) mx[c] = 0;
-  for (int32_t c = threadIdx.x; c < ncomp; c += blockDim.x) ex[c] = 0;
   __syncthreads();
-  float* gin = G0;
-  float* gout = G1;
-  // each thread's rows (at most kSmallRows of them, n <= kSmallRows * 1024)
-  // keep their bounds, component slot and anchor flag in registers
-  // and the first kHeldEntries entries of each row
-  int32_t rb[kSmallRows], re[kSmallRows], rc[kSmallRows];
-  bool ra[kSmallRows];
-  uint32_t held[kSmallRows][kHeldEntries];
-#pragma unroll
-  for (int q = 0; q < kSmallRows; ++q) {
-    const int32_t i = q * (int32_t)blockDim.x + (int32_t)threadIdx.x;
-    const bool in = i < n;
-    rb[q] = in ? rp[i] : 0;
-    re[q] = in ? rp[i + 1] : 0;
-    rc[q] = in ? cs[i] : -1;
-    ra[q] = in && comp[i] == i;
-#pragma unroll
-    for (int t = 0; t < kHeldEntries; ++t) held[q][t] = rb[q] + t < re[q] ? adj[rb[q] + t] : 0u;
+  // rows by length, longest first
+  for (int32_t i = tid; i < n; i += 1024) atomicAdd(&lens[len_of(i)], 1u);
+  __syncthreads();
+  if (tid < 64) {
+    uint32_t mine = lens[63 - tid], upto = mine;
+    for (int d = 1; d < 64; d *= 2) {
+      const uint32_t below = __shfl_up(upto, d);
+      if (tid >= d) upto += below;
+    }
+    lens[63 - tid] = upto - mine;
   }
-  int k3 = 0;  // step mod 3: which maxima buffer is read, written, cleared
-  for (int64_t k = 0; k < steps; ++k) {
+  __syncthreads();
+  for (int32_t i = tid; i < n; i += 1024) perm[atomicAdd(&lens[len_of(i)], 1u)] = (uint32_t)i;
+  __syncthreads();
+
+  // each thread's rows: their vertex, end, component slot, anchor flag, value
+  // and leading entries in registers, and the wave's longest (in an SGPR)
+  int32_t row[Q], rb[Q], re[Q], rc[Q], longest[Q];
+  bool ra[Q];
+  float own[Q];
+  uint32_t held[Q][H];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    // (every other thousand runs backwards, so that waves share the long ones)
+    const int32_t p = q * 1024 + (q & 1 ? 1023 - tid : tid);
+    row[q] = p < n && p >= nheavy ? (int32_t)perm[p] : -1;
+    const int32_t i = max(row[q], 0);
+    rb[q] = row[q] >= 0 ? rp[i] : 0;
+    re[q] = row[q] >= 0 ? rp[i + 1] : 0;
+    rc[q] = re[q] > rb[q] ? aslot[comp[i]] : -1;
+    ra[q] = row[q] >= 0 && comp[i] == i;
+    own[q] = row[q] >= 0 ? *(float*)(lds + 8 * i) : 0.0f;
+    longest[q] = (int32_t)__builtin_amdgcn_readfirstlane((int)wave_max_u32((uint32_t)(re[q] - rb[q])));
+#pragma unroll
+    for (int t = 0; t < H; ++t) held[q][t] = rb[q] + t < re[q] ? offset(adj[rb[q] + t]) : kZero;
+  }
+  for (int32_t h = tid; h < nheavy; h += 1024) {
+    const int32_t i = (int32_t)perm[h];
+    heavy[h] = SmallHeavy{i, rp[i], rp[i + 1], aslot[comp[i]]};
+  }
+  __syncthreads();
+
+  int k3 = 0;  // step mod 3: which flags are read, written, cleared
+  // one step from the column at `from` into the one at `to`
+  auto step = [&](auto from, auto to) {
     const uint32_t* min_ = mx + k3 * ncomp;
     uint32_t* mout = mx + (k3 == 2 ? 0 : k3 + 1) * ncomp;
     uint32_t* mclr = mx + (k3 == 0 ? 2 : k3 - 1) * ncomp;
+    const char* gin = lds + decltype(from)::value;
+    char* gout = lds + decltype(to)::value;
 #pragma unroll
-    for (int q = 0; q < kSmallRows; ++q) {
-      if (q * (int32_t)blockDim.x >= n) break;
-      const int32_t i = q * (int32_t)blockDim.x + (int32_t)threadIdx.x;
+    for (int q = 0; q < Q; ++q) {
+      if (q * 1024 >= n) break;
       const int32_t c = rc[q];
-      float v = 0.0f;
-      if (i < n) {
-        const float sc = (c >= 0 && min_[c] >= thresh) ? down : 1.0f;
-        float acc = 0.0f;
-        // the held entries' loads all in flight, then four at a time; the
-        // sum keeps the row's order
-        const int32_t e1 = re[q];
-        float xh[kHeldEntries];
+      const uint32_t over = c >= 0 ? min_[c] : 0u;
+      float acc = 0.0f;
+      const float sc = over ? down : 1.0f;
 #pragma unroll
-        for (int t = 0; t < kHeldEntries; ++t) xh[t] = gin[held[q][t] & kVertexMask];
+      for (int t0 = 0; t0 < H; t0 += kBatch) {
+        if (longest[q] <= t0) break;
+        float x[kBatch];
 #pragma unroll
-        for (int t = 0; t < kHeldEntries; ++t) {
-          if (rb[q] + t < e1) {
-            const float gt = xh[t] * sc;
-            acc += (held[q][t] >> 31) ? -gt : gt;
-          }
-        }
-        int32_t e = rb[q] + kHeldEntries;
-        for (; e + 3 < e1; e += 4) {
-          const uint32_t a0 = adj[e], a1 = adj[e + 1], a2 = adj[e + 2], a3 = adj[e + 3];
-          const float x0 = gin[a0 & kVertexMask], x1 = gin[a1 & kVertexMask];
-          const float x2 = gin[a2 & kVertexMask], x3 = gin[a3 & kVertexMask];
-          const float g0 = x0 * sc, g1 = x1 * sc, g2 = x2 * sc, g3 = x3 * sc;
-          acc += (a0 >> 31) ? -g0 : g0;
-          acc += (a1 >> 31) ? -g1 : g1;
-          acc += (a2 >> 31) ? -g2 : g2;
-          acc += (a3 >> 31) ? -g3 : g3;
-        }
-        for (; e < e1; ++e) {
-          const uint32_t a = adj[e];
-          const float gj = gin[a & kVertexMask] * sc;
-          acc += (a >> 31) ? -gj : gj;
-        }
-        const float g = -0.5f * acc * 1.0f;
-        v = gin[i] * sc - alpha * g;
-        gout[i] = v;
-        if (sc != 1.0f && ra[q]) ex[c] += shift;
+        for (int t = 0; t < kBatch; ++t) x[t] = *(const float*)(gin + held[q][t0 + t]);
+#pragma unroll
+        for (int t = 0; t < kBatch; ++t) acc += x[t] * sc;
       }
-      // the component maxima: one atomic per wave when its lanes share one
-      // component (the maximum does not depend on the order)
-      uint32_t m = c >= 0 ? __float_as_uint(fabsf(v)) : 0u;
-      const int32_t c0 = __builtin_amdgcn_readfirstlane(c);
-      if (__ballot(c != c0) == 0) {
-        m = wave_max_u32(m);
-        if (c0 >= 0 && (threadIdx.x & 63) == 0) atomicMax(mout + c0, m);
-      } else if (c >= 0) {
-        atomicMax(mout + c, m);
+      if (longest[q] > H) {
+        // (a lane past its row's end stays there)
+        uint32_t a[kTail];
+        entries(min(rb[q] + H, re[q]), re[q], a);
+        for (int32_t t0 = H; t0 < longest[q]; t0 += kTail) {
+          float x[kTail];
+#pragma unroll
+          for (int t = 0; t < kTail; ++t) x[t] = *(const float*)(gin + a[t]);
+          entries(min(rb[q] + t0 + kTail, re[q]), re[q], a);
+#pragma unroll
+          for (int t = 0; t < kTail; ++t) acc += x[t] * sc;
+        }
+      }
+      if (row[q] >= 0) {
+        const float g = -0.5f * acc * 1.0f;
+        const float v = own[q] * sc - alpha * g;
+        own[q] = v;
+        *(float2*)(gout + 8 * row[q]) = make_float2(v, -v);
+        if (sc != 1.0f && ra[q]) ex[c] += shift;
+        if (c >= 0 && __float_as_uint(fabsf(v)) >= thresh) mout[c] = 1u;
+      }
+    }
+    for (int32_t h = tid >> 6; h < nheavy; h += 16) {
+      const SmallHeavy w = heavy[h];
+      const float sc = min_[w.slot] ? down : 1.0f;
+      float acc = 0.0f;
+      for (int32_t e0 = w.begin; e0 < w.end; e0 += kGLChunk) {
+        const int32_t len = min(kGLChunk, w.end - e0);
+        float item = 0.0f;
+        for (int g0 = 0; g0 < groups; g0 += 64) {
+          const int grp = g0 + (tid & 63);
+          float sum = 0.0f;
+          for (int32_t at = grp < groups ? grp : len; at < len; at += groups * kBatch) {
+            uint32_t a[kBatch];
+            float x[kBatch];
+#pragma unroll
+            for (int t = 0; t < kBatch; ++t) a[t] = adj[e0 + min(at + groups * t, len - 1)];
+#pragma unroll
+            for (int t = 0; t < kBatch; ++t)
+              x[t] = *(const float*)(gin + (at + groups * t < len ? offset(a[t]) : kZero));
+#pragma unroll
+            for (int t = 0; t < kBatch; ++t) sum += x[t] * sc;
+          }
+          for (int k = 0; k < min(64, groups - g0); ++k)
+            item += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sum), k));
+        }
+        acc += item;
+      }
+      if ((tid & 63) == 0) {
+        const float g = -0.5f * acc * 1.0f;
+        const float v = *(const float*)(gin + 8 * w.row) * sc - alpha * g;
+        *(float2*)(gout + 8 * w.row) = make_float2(v, -v);
+        if (sc != 1.0f && comp[w.row] == w.row) ex[w.slot] += shift;
+        if (__float_as_uint(fabsf(v)) >= thresh) mout[w.slot] = 1u;
       }
     }
     k3 = k3 == 2 ? 0 : k3 + 1;
-    for (int32_t c = threadIdx.x; c < ncomp; c += blockDim.x) mclr[c] = 0;
+    for (int32_t c = tid; c < ncomp; c += 1024) mclr[c] = 0;
     __syncthreads();
-    float* t = gin;
-    gin = gout;
-    gout = t;
+  };
+  using Col0 = std::integral_constant<uint32_t, 0>;
+  using Col1 = std::integral_constant<uint32_t, kCol>;
+  for (int64_t k = 0; k + 1 < steps; k += 2) {
+    step(Col0{}, Col1{});
+    step(Col1{}, Col0{});
   }
-  for (int32_t i = threadIdx.x; i < n; i += blockDim.x) gamma[(size_t)i * R + r] = gin[i];
-  for (int32_t c = threadIdx.x; c < ncomp; c += blockDim.x) exps[(size_t)c * R + r] = ex[c];
+  if (steps & 1) step(Col0{}, Col1{});
+#pragma unroll
+  for (int q = 0; q < Q; ++q)
+    if (row[q] >= 0) gamma[(size_t)row[q] * R + r] = own[q];
+  for (int32_t h = tid; h < nheavy; h += 1024)
+    gamma[(size_t)heavy[h].row * R + r] = *(const float*)(lds + (steps & 1) * kCol + 8 * heavy[h].row);
+  for (int32_t c = tid; c < ncomp; c += 1024) exps[(size_t)c * R + r] = ex[c];
 }
 
 // Per-vertex log2 scales of a descent: out[i][r] = the scale of (component
@@ -971,6 +1050,25 @@ int fi_graphl_aux_size(fi_graph* g, int32_t R, size_t* out_bytes) {
 
 namespace {
 
+template <int Q>
+size_t small_lds(const fi_graph* g, int32_t ncomp) {
+  return 2 * small_column(Q) + 16 * ((size_t)ncomp + (size_t)g->gl_nheavy);
+}
+
+// The fused descent, Q rows per thread (n <= 1024 Q).
+template <int Q>
+hipError_t descend_small(fi_graph* g, int32_t ncomp, int groups, int32_t R, float alpha, int64_t steps,
+                         int32_t shift, const float* start, float* gamma, int32_t* exps, hipStream_t s) {
+  const size_t lds = small_lds<Q>(g, ncomp);
+  const hipError_t e = hipFuncSetAttribute((const void*)k_gl_descend_small<Q>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_gl_descend_small<Q>, dim3(R), dim3(1024), lds, s, g->dg.row_ptr, g->dg.adj,
+                     g->dg.comp, (const int32_t*)(g->ws + g->L.aslot), g->dg.n, ncomp, g->gl_nheavy, groups, (int)R,
+                     alpha, steps, (int)shift, start, gamma, exps);
+  return hipGetLastError();
+}
+
 // The descent from `start` (d_gamma itself, or another buffer, which is only
 // read) into d_gamma, with d_work as the other buffer.
 int descend(fi_graph* g, const float* start, float* d_gamma, float* d_work, int32_t R, float alpha,
@@ -992,24 +1090,15 @@ int descend(fi_graph* g, const float* start, float* d_gamma, float* d_work, int3
     FI_HIP(hipMemcpyAsync(d_gamma, start, bytes, hipMemcpyDeviceToDevice, s));
   if (g->dg.n == 0 || steps == 0) return hipGetLastError() == hipSuccess ? FI_OK : FI_EDEVICE;
   const int32_t ncomp = std::max<int32_t>(g->nanch, 1);
-  const size_t lds = 12 * (size_t)g->dg.n + 16 * (size_t)ncomp;
-  const size_t lds_csr = lds + 4 * ((size_t)g->dg.n + 1) + 4 * (size_t)g->dg.nnz;
-  if (g->dg.n <= kSmallDescentN && g->gl_nheavy == 0 && lds <= kSmallDescentLds) {
-    const int32_t* aslot = (const int32_t*)(g->ws + g->L.aslot);
-    if (lds_csr <= kSmallDescentLds) {
-      FI_HIP(hipFuncSetAttribute((const void*)k_gl_descend_small<true>,
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_csr));
-      hipLaunchKernelGGL(k_gl_descend_small<true>, dim3(R), dim3(1024), lds_csr, s, g->dg.row_ptr,
-                         g->dg.adj, g->dg.comp, aslot, g->dg.n, ncomp, (int)R, alpha, steps,
-                         (int)rescale_log2, start, d_gamma, (int32_t*)aux);
-    } else {
-      FI_HIP(hipFuncSetAttribute((const void*)k_gl_descend_small<false>,
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-      hipLaunchKernelGGL(k_gl_descend_small<false>, dim3(R), dim3(1024), lds, s, g->dg.row_ptr,
-                         g->dg.adj, g->dg.comp, aslot, g->dg.n, ncomp, (int)R, alpha, steps,
-                         (int)rescale_log2, start, d_gamma, (int32_t*)aux);
-    }
-    return hipGetLastError() == hipSuccess ? FI_OK : FI_EDEVICE;
+  if (g->dg.n <= kSmallDescentN && g->dg.nnz <= (g->gl_nheavy ? kSmallEntries / 2 : kSmallEntries) &&
+      small_lds<4>(g, ncomp) <= kSmallDescentLds) {
+    const auto f = g->dg.n <= 1024 ? descend_small<1> : g->dg.n <= 2048 ? descend_small<2> : descend_small<4>;
+    int groups = 0;
+    with_lanes(R, ((uintptr_t)start | (uintptr_t)d_gamma | (uintptr_t)d_work) % 16 == 0,
+               [&](auto p, auto) { groups = kGLBlock / decltype(p)::value; });
+    return f(g, ncomp, groups, R, alpha, steps, rescale_log2, start, d_gamma, (int32_t*)aux, s) == hipSuccess
+               ? FI_OK
+               : FI_EDEVICE;
   }
   // steps alternate between the buffers; from another start the last one ends
   // in d_gamma, from d_gamma an odd number of steps ends in d_work
