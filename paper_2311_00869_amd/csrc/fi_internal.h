@@ -254,6 +254,8 @@ void prof_end(fi_graph* g, hipStream_t s, void* token, int kernel);
 // launchers implemented in the .hip files
 hipError_t launch_sweep(fi_graph* g, const SweepArgs& a, hipStream_t s);
 hipError_t launch_grid(fi_graph* g, const SweepArgs& a, hipStream_t s);
+// trees in LDS (path 1), BFS and the hybrid's BFS trees
+hipError_t launch_edges(fi_graph* g, const SweepArgs& a, int nt, hipStream_t s);
 hipError_t launch_kruskal(fi_graph* g, const SweepArgs& a, int path, int nt, hipStream_t s);
 bool kruskal_forest_fits(const fi_graph* g);  // a workgroup's forest in LDS
 hipError_t launch_rdfs(fi_graph* g, const SweepArgs& a, int path, hipStream_t s);

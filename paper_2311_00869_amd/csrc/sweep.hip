@@ -2,11 +2,12 @@
 // the min-key parent rule and fused state propagation, the exact frustration
 // count, the canonical-state key, and the cloud insert.
 //
-// Three kernel families compute identical results:
+// Four kernel families compute identical results:
+//   k_sweep_edges - sweep_edges.hip: one workgroup per tree, the tree in LDS.
 //   k_sweep_wg   - here: one workgroup per tree; the tree words and the BFS
-//                  queue live in LDS (small graphs) or in a per-workgroup
-//                  slice of the workspace.  Trees are spread over workgroups,
-//                  so one launch runs thousands of trees with no grid barrier.
+//                  queue live in a per-workgroup slice of the workspace.
+//                  Trees are spread over workgroups, so one launch runs
+//                  thousands of trees with no grid barrier.
 //   k_sweep_grid - sweep_grid.hip: the whole grid works on a few trees at a
 //                  time (persistent cooperative kernel), for graphs far
 //                  beyond one workgroup.
@@ -29,20 +30,12 @@ namespace {
 
 using wg::WgShared;
 
-template <int NT, bool IN_LDS>
+template <int NT>
 __global__ void __launch_bounds__(NT) k_sweep_wg(DevGraph G, SweepArgs A) {
   __shared__ WgShared<NT> sh;
-  extern __shared__ uint64_t dyn[];
-  uint64_t* pw;
-  int32_t* q;
-  if (IN_LDS) {
-    pw = dyn;
-    q = (int32_t*)(dyn + G.n);
-  } else {
-    char* slot = (char*)A.pw + (size_t)blockIdx.x * A.slot_stride;
-    pw = (uint64_t*)slot;
-    q = (int32_t*)(slot + 8 * (size_t)G.n);
-  }
+  char* slot = (char*)A.pw + (size_t)blockIdx.x * A.slot_stride;
+  uint64_t* pw = (uint64_t*)slot;
+  int32_t* q = (int32_t*)(slot + 8 * (size_t)G.n);
   for (uint64_t t = A.t0 + blockIdx.x; t < A.t1; t += gridDim.x) {
     // (the hybrid's other trees are randomized DFS)
     if (A.sampler == kSamplerHybrid && wg::hybrid_coin(tree_salt(A.seed, t))) continue;
@@ -50,44 +43,27 @@ __global__ void __launch_bounds__(NT) k_sweep_wg(DevGraph G, SweepArgs A) {
   }
 }
 
-// tree words and queue; Kruskal also keeps a root list
+// bound of a tree's LDS: tree words and levels; Kruskal also keeps its roots
 size_t wg_lds_bytes(int32_t n, int sampler = kSamplerBfs) {
   return (sampler == kSamplerKruskal ? 16 : 12) * (size_t)n;
 }
 
 template <int NT>
-hipError_t launch_wg(fi_graph* g, const SweepArgs& a, int path, hipStream_t s) {
-  const uint64_t ntrees = a.t1 - a.t0;
-  const DevGraph& G = g->dg;
+hipError_t launch_wg(fi_graph* g, const SweepArgs& a, hipStream_t s) {
+  SweepArgs b = a;
+  b.pw = (uint64_t*)(g->ws + g->L.slots);
+  b.slot_stride = g->L.slot_stride;
   int grid = g->sched.grid;
-  if (path == 1) {
-    const size_t lds = wg_lds_bytes(G.n);
-    hipError_t ea = hipFuncSetAttribute((const void*)k_sweep_wg<NT, true>,
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (ea != hipSuccess) return ea;
-    int per_cu = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_sweep_wg<NT, true>, NT, lds);
-    if (e != hipSuccess) return e;
-    if (per_cu < 1) per_cu = 1;
-    // at most six resident workgroups per CU: a 1,000-vertex graph ran a
-    // quarter slower at eight (the limit its registers allow)
-    if (per_cu > 6) per_cu = 6;
-    if (grid <= 0) grid = per_cu * g->cu_count;
-    grid = (int)std::min<uint64_t>((uint64_t)grid, ntrees);
-    hipLaunchKernelGGL((k_sweep_wg<NT, true>), dim3(grid), dim3(NT), lds, s, G, a);
-  } else {
-    SweepArgs b = a;
-    b.pw = (uint64_t*)(g->ws + g->L.slots);
-    b.slot_stride = g->L.slot_stride;
-    if (grid <= 0) grid = 8 * g->cu_count;
-    grid = (int)std::min<uint64_t>(std::min<uint64_t>((uint64_t)grid, ntrees), g->L.nslots);
-    hipLaunchKernelGGL((k_sweep_wg<NT, false>), dim3(grid), dim3(NT), 0, s, G, b);
-  }
+  if (grid <= 0) grid = 8 * g->cu_count;
+  grid = (int)std::min<uint64_t>(std::min<uint64_t>((uint64_t)grid, a.t1 - a.t0), g->L.nslots);
+  hipLaunchKernelGGL(k_sweep_wg<NT>, dim3(grid), dim3(NT), 0, s, g->dg, b);
   return hipGetLastError();
 }
 
-// Trees per CU from which a small graph's sweep goes to the multi-tree path.
-constexpr uint64_t kMultiTreesPerCu = 3;
+// Edges, and edges times trees, from which a small graph's sweep goes to the
+// multi-tree path.
+constexpr int64_t kMultiMinEdges = 65536;
+constexpr uint64_t kMultiMinTreeEdges = 80000000;
 
 bool tree_fits_lds(const fi_graph* g) {
   return wg_lds_bytes(g->dg.n, g->sampler) + 32768 <= (size_t)g->max_shared;
@@ -117,12 +93,13 @@ int pick_path(fi_graph* g, uint64_t trees, hipStream_t s) {
   }
   if (g->sched.path != 0) return g->sched.path;
   const int64_t work = (int64_t)n + g->dg.m / 2;
-  // A tree in LDS is swept alone in 40 to 160 us, as many at once as the CUs
-  // hold; the multi-tree pass needs 300 us and up whatever its trees (n =
-  // 6,000, m = 50,000: 1,000 trees 531 us and 424 on it, 300 trees 276 and
-  // 556; 4,000 / 20,000: 1,000 trees 277 and 389), but on a deep graph it
-  // pays its barriers at every level.
-  const bool many = trees >= kMultiTreesPerCu * (uint64_t)g->cu_count && work >= kMultiMinWork;
+  // A tree in LDS is swept alone in 20 to 130 us, as many at once as the CUs
+  // hold, in proportion to its edges; the multi-tree pass needs 300 us and up
+  // whatever its trees (us: n = 6,000, m = 50,000: 1,000 trees 289 and 363 on it,
+  // 4,000 1,090 and 1,281; 10,000 / 80,000: 1,000 446 and 442; 3,000 / 300,000: 100
+  // 222 and 224, 300 512 and 338), but on a deep graph it pays its barriers at
+  // every level.
+  const bool many = g->dg.m >= kMultiMinEdges && trees * (uint64_t)g->dg.m >= kMultiMinTreeEdges;
   const bool plain = g->deep || ((fits ? many : work <= kDeepWork) && capturing(s));
   if (fits && (!many || plain)) return 1;
   // One tree per workgroup in workspace memory costs about m per tree (30,000
@@ -186,8 +163,10 @@ hipError_t launch_sweep(fi_graph* g, const SweepArgs& a, hipStream_t s) {
   } else if (a.sampler == kSamplerRdfs) {
     e = launch_rdfs(g, a, path, s);
   } else {
-    e = nt == 1024 ? launch_wg<1024>(g, a, path, s) : nt == 512 ? launch_wg<512>(g, a, path, s)
-                                                                 : launch_wg<256>(g, a, path, s);
+    e = path == 1   ? launch_edges(g, a, nt, s)
+        : nt == 1024 ? launch_wg<1024>(g, a, s)
+        : nt == 512  ? launch_wg<512>(g, a, s)
+                     : launch_wg<256>(g, a, s);
     if (e == hipSuccess && a.sampler == kSamplerHybrid) e = launch_rdfs(g, a, path, s);
   }
   prof_end(g, s, tok, 0);

@@ -18,8 +18,8 @@ def _switches(g, seed):
     return oracle.sweep(g, seed, 0, K, checks=False).trees[:, 0]
 
 
-# trees in LDS; trees in workspace memory
-@pytest.mark.parametrize("n,m", [(6000, 30000), (20000, 60000)])
+# trees in LDS, of few edges and of many; trees in workspace memory
+@pytest.mark.parametrize("n,m", [(6000, 30000), (5000, 110000), (20000, 60000)])
 def test_captured_sweep_replays_match_oracle(n, m):
     g = synth.erdos_renyi_connected(n, m, 0.8, 3)
     ref = _switches(g, 11)
@@ -43,8 +43,9 @@ def test_captured_sweep_replays_match_oracle(n, m):
     G.close()
 
 
-def test_sweeps_of_one_handle_on_two_streams():
-    g = synth.erdos_renyi_connected(6000, 30000, 0.8, 4)
+@pytest.mark.parametrize("n,m", [(6000, 30000), (5000, 110000)])
+def test_sweeps_of_one_handle_on_two_streams(n, m):
+    g = synth.erdos_renyi_connected(n, m, 0.8, 4)
     refs = [_switches(g, s) for s in (21, 22)]
     G = fr.Graph(g.row_ptr, g.col, g.sign, cloud_capacity=4 * K)
     streams = [torch.cuda.Stream() for _ in range(2)]
