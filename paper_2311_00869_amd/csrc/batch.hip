@@ -1118,7 +1118,7 @@ int fi_batch_cloud_read(fi_graph* h, int32_t graph, fi_cloud_entry* h_out, int64
   const int e = fi_graph_status(h, stream);
   if (e) return e;
   const CloudSlot* table = (const CloudSlot*)(h->ws + bi->L.clouds) + (size_t)graph * bi->tsize;
-  return read_cloud_table(table, bi->tsize, h_out, cap, written, (hipStream_t)stream);
+  return read_cloud_table(table, bi->tsize, nullptr, h_out, cap, written, (hipStream_t)stream);
 }
 
 }  // extern "C"

@@ -460,9 +460,7 @@ int fi_bcloud_read(fi_bcloud* c, fi_cloud_entry* h_out, int64_t cap, int64_t* wr
   std::vector<fi_cloud_entry> rows;
   rows.reserve(nb);
   for (const BEntry& x : e) rows.push_back(fi_cloud_entry{x.khi, x.klo, x.freq, x.S, x.first});
-  std::sort(rows.begin(), rows.end(), [](const fi_cloud_entry& a, const fi_cloud_entry& b) {
-    return a.key_hi != b.key_hi ? a.key_hi < b.key_hi : a.key_lo < b.key_lo;
-  });
+  sort_entries(rows);
   const int64_t k = std::min<int64_t>(cap, nb);
   if (k > 0) std::memcpy(h_out, rows.data(), sizeof(fi_cloud_entry) * k);
   if (written) *written = nb;

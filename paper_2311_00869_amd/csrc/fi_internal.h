@@ -8,6 +8,7 @@
 #include <stddef.h>
 
 #include <mutex>
+#include <vector>
 
 #include "frustration.h"
 
@@ -234,9 +235,11 @@ Layout make_layout(int32_t n, int64_t nnz, int64_t cloud_capacity, uint64_t tabl
 int64_t switch_tiles(int64_t m);  // tiles of the switch-list compaction over m edges
 uint64_t table_size_for(int64_t cloud_capacity);
 // a cloud table (tsize slots of device memory) to host entries sorted by key
-// (blocks); FI_ECOLLISION if a slot met two key_hi or two switch counts
-int read_cloud_table(const CloudSlot* d_table, uint64_t tsize, fi_cloud_entry* h_out, int64_t cap,
-                     int64_t* written, hipStream_t s);
+// (blocks); the error of the control words behind it (null: none), else
+// FI_ECOLLISION if a slot met two key_hi or two switch counts
+int read_cloud_table(const CloudSlot* d_table, uint64_t tsize, const uint64_t* d_ctl, fi_cloud_entry* h_out,
+                     int64_t cap, int64_t* written, hipStream_t s);
+void sort_entries(std::vector<fi_cloud_entry>& rows);  // by key
 
 constexpr int kGraphLMaxR = 64;
 constexpr int kGraphLBlocks = 2048;

@@ -299,13 +299,11 @@ class Graph:
 
     def cloud(self, stream=None) -> np.ndarray:
         """uint64 [E, 5]: key_hi, key_lo, freq, switches, first_tree (sorted by key)."""
-        size = self.cloud_size(stream)
-        buf = (CloudEntry * max(size, 1))()
+        buf = np.empty((max(self.cloud_capacity, 1), 5), np.uint64)
         written = ctypes.c_int64()
-        _check(self.lib.fi_cloud_read(self.handle, buf, size, ctypes.byref(written),
-                                      _stream_ptr(stream)), "cloud_read")
-        arr = np.ctypeslib.as_array(buf).view(np.uint64).reshape(-1, 5)[:size].copy()
-        return arr
+        _check(self.lib.fi_cloud_read(self.handle, buf.ctypes.data_as(ctypes.c_void_p), buf.shape[0],
+                                      ctypes.byref(written), _stream_ptr(stream)), "cloud_read")
+        return buf[: written.value].copy()
 
     def sweep_bounded(self, cloud: "BoundedCloud", t0: int, t1: int, seed: int, chunk: int = 0,
                       stream=None):
