@@ -13,6 +13,7 @@
 #include <numeric>
 #include <vector>
 
+#include "fi_edges.h"
 #include "fi_internal.h"
 #include "fi_prims.h"
 #include "fi_wg.h"
@@ -26,7 +27,7 @@ constexpr size_t kAlign = 256;
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 constexpr int kCtlPerGraph = 32;       // err, best, distinct count, trees; own 256-byte line
 constexpr int32_t kMaxBatchN = 1000000;
-constexpr int kLdsMaxN = 6144;         // graphs up to this size keep their tree in LDS
+constexpr int kLdsMaxN = 15000;        // graphs up to this size keep their tree in LDS (10 bytes a vertex)
 // item tickets of the two size classes, each on its own 128-byte line of the
 // batch control block
 constexpr int kTicket0 = C_UNIT;
@@ -323,7 +324,8 @@ struct BatchArgs {
   uint64_t* gctl;
   uint64_t* ticket;     // next work item of this size class
   const int32_t* order; // graph ids of this size class, largest first
-  int64_t nitems;       // graphs in the class * trees per graph
+  int64_t nitems;       // items: a graph of the class and up to `per` of its trees
+  int64_t per;
   int64_t trees;
   uint64_t seed;
   uint64_t tsize;
@@ -332,49 +334,87 @@ struct BatchArgs {
   size_t slot_stride;
 };
 
-template <int NT, bool IN_LDS>
+// The next work item, or -1: a graph and the first of its next `per` trees.
+struct BatchItem {
+  int32_t graph;
+  int64_t tree;
+};
+__device__ __forceinline__ BatchItem next_item(const BatchArgs& B, int64_t* s_item) {
+  if (threadIdx.x == 0) *s_item = (int64_t)atomicAdd((unsigned long long*)B.ticket, 1ull);
+  __syncthreads();
+  // (the same for all threads: its graph's fields go to scalar registers)
+  const uint64_t it = (uint64_t)*s_item;
+  const int64_t item = (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(it >> 32)) << 32 |
+                                 (uint32_t)__builtin_amdgcn_readfirstlane((int)it));
+  __syncthreads();
+  if (item >= B.nitems) return BatchItem{-1, 0};
+  const int64_t groups = (B.trees + B.per - 1) / B.per;
+  return BatchItem{B.order[item / groups], item % groups * B.per};
+}
+__device__ __forceinline__ DevGraph batch_graph(const BatchArgs& B, int32_t gi) {
+  const BatchGraph b = B.meta[gi];
+  DevGraph G{};
+  G.n = b.n;
+  G.nwords = b.nwords;
+  G.nnz = b.nnz;
+  G.m = b.m;
+  G.row_ptr = B.row_ptr + b.ro;
+  G.adj = B.adj + b.no;
+  G.edges = B.edges + b.me;
+  G.comp = B.comp + b.vo;
+  G.cloud = B.clouds + (size_t)gi * B.tsize;
+  G.cloud_mask = B.tsize - 1;
+  G.cloud_cap = B.cap;
+  G.ctl = B.gctl + (size_t)gi * kCtlPerGraph;
+  return G;
+}
+__device__ __forceinline__ SweepArgs batch_sweep_args(const BatchArgs& B) {
+  SweepArgs A{};
+  A.seed = B.seed;
+  A.t0 = 0;
+  A.t1 = (uint64_t)B.trees;
+  A.insert = 1;
+  return A;
+}
+
+// Graphs whose trees fit LDS: a few trees per item, so that a thread's edges
+// are read once for them.
+template <int NT>
+__global__ void __launch_bounds__(NT, 4) k_batch_edges(BatchArgs B) {
+  __shared__ wg::EShared<NT> sh;
+  __shared__ int64_t s_item;
+  __shared__ uint32_t s_later;
+  extern __shared__ uint64_t dyn[];
+  while (true) {
+    const BatchItem item = next_item(B, &s_item);
+    if (item.graph < 0) break;
+    const DevGraph G = batch_graph(B, item.graph);
+    if (threadIdx.x == 0) s_later = 0;
+    __syncthreads();
+    uint32_t later = 0;
+    for (int32_t v = threadIdx.x; v < G.n; v += NT)
+      later += G.row_ptr[v + 1] > G.row_ptr[v] && G.comp[v] != v;
+    later = wave_reduce<false>(later, [](uint32_t a, uint32_t b) { return a + b; });
+    if (lane_id() == 0 && later) atomicAdd(&s_later, later);
+    __syncthreads();
+    wg::edges_trees<NT>(G, batch_sweep_args(B), (uint64_t)item.tree,
+                        (uint64_t)min(item.tree + B.per, B.trees), 1, (int32_t)s_later, sh, dyn);
+    __syncthreads();
+  }
+}
+
+template <int NT>
 __global__ void __launch_bounds__(NT) k_batch_wg(BatchArgs B) {
   __shared__ wg::WgShared<NT> sh;
   __shared__ int64_t s_item;
-  extern __shared__ uint64_t dyn[];
+  char* slot = B.slots + (size_t)blockIdx.x * B.slot_stride;
   while (true) {
-    if (threadIdx.x == 0) s_item = (int64_t)atomicAdd((unsigned long long*)B.ticket, 1ull);
-    __syncthreads();
-    const int64_t item = s_item;
-    __syncthreads();
-    if (item >= B.nitems) break;
-    const int32_t gi = B.order[item / B.trees];
-    const uint64_t t = (uint64_t)(item % B.trees);
-    const BatchGraph b = B.meta[gi];
-    DevGraph G{};
-    G.n = b.n;
-    G.nwords = b.nwords;
-    G.nnz = b.nnz;
-    G.m = b.m;
-    G.row_ptr = B.row_ptr + b.ro;
-    G.adj = B.adj + b.no;
-    G.edges = B.edges + b.me;
-    G.comp = B.comp + b.vo;
-    G.cloud = B.clouds + (size_t)gi * B.tsize;
-    G.cloud_mask = B.tsize - 1;
-    G.cloud_cap = B.cap;
-    G.ctl = B.gctl + (size_t)gi * kCtlPerGraph;
-    SweepArgs A{};
-    A.seed = B.seed;
-    A.t0 = 0;
-    A.t1 = (uint64_t)B.trees;
-    A.insert = 1;
-    uint64_t* pw;
-    int32_t* q;
-    if (IN_LDS) {
-      pw = dyn;
-      q = (int32_t*)(dyn + b.n);
-    } else {
-      char* slot = B.slots + (size_t)blockIdx.x * B.slot_stride;
-      pw = (uint64_t*)slot;
-      q = (int32_t*)(slot + 8 * (size_t)b.n);
-    }
-    wg::wg_tree<NT>(G, A, t, pw, q, sh);
+    const BatchItem item = next_item(B, &s_item);
+    if (item.graph < 0) break;
+    const DevGraph G = batch_graph(B, item.graph);
+    const SweepArgs A = batch_sweep_args(B);
+    for (int64_t t = item.tree; t < min(item.tree + B.per, B.trees); ++t)
+      wg::wg_tree<NT>(G, A, (uint64_t)t, (uint64_t*)slot, (int32_t*)(slot + 8 * (size_t)G.n), sh);
   }
 }
 
@@ -385,29 +425,31 @@ inline int nt_index(int nt) { return nt == 1024 ? 2 : nt == 512 ? 1 : 0; }
 template <int NT>
 hipError_t batch_occupancy(BatchInfo* bi) {
   const int k = nt_index(NT);
-  const size_t bytes = 12 * (size_t)bi->n_max_small;
-  hipError_t e = hipFuncSetAttribute((const void*)k_batch_wg<NT, true>,
+  const size_t bytes = 10 * (size_t)bi->n_max_small;
+  hipError_t e = hipFuncSetAttribute((const void*)k_batch_edges<NT>,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
   if (e != hipSuccess) return e;
-  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&bi->per_cu[k][0], k_batch_wg<NT, true>, NT, bytes);
+  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&bi->per_cu[k][0], k_batch_edges<NT>, NT, bytes);
   if (e != hipSuccess) return e;
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(&bi->per_cu[k][1], k_batch_wg<NT, false>, NT, 0);
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(&bi->per_cu[k][1], k_batch_wg<NT>, NT, 0);
 }
 
+// One size class: count graphs of a.order.
 template <int NT>
-void launch_class(fi_graph* h, const BatchArgs& a, bool lds, hipStream_t s) {
+void launch_class(fi_graph* h, BatchArgs a, int32_t count, bool lds, hipStream_t s) {
   const BatchInfo* bi = (const BatchInfo*)h->batch;
   int64_t grid = (int64_t)std::max(1, bi->per_cu[nt_index(NT)][lds ? 0 : 1]) * h->cu_count;
   if (h->sched.grid > 0) grid = std::min<int64_t>(grid, h->sched.grid);
   if (!lds) grid = std::min<int64_t>(grid, (int64_t)bi->L.nslots);
+  // in LDS up to 16 trees to an item, while every workgroup has four items
+  a.per = lds ? std::max<int64_t>(1, std::min<int64_t>(16, count * a.trees / (4 * grid))) : 1;
+  a.nitems = count * ((a.trees + a.per - 1) / a.per);
   grid = std::max<int64_t>(1, std::min<int64_t>(grid, a.nitems));
   if (lds)
-    hipLaunchKernelGGL((k_batch_wg<NT, true>), dim3((int)grid), dim3(NT), 12 * (size_t)bi->n_max_small,
-                       s, a);
+    hipLaunchKernelGGL(k_batch_edges<NT>, dim3((int)grid), dim3(NT), 10 * (size_t)bi->n_max_small, s, a);
   else
-    hipLaunchKernelGGL((k_batch_wg<NT, false>), dim3((int)grid), dim3(NT), 0, s, a);
+    hipLaunchKernelGGL(k_batch_wg<NT>, dim3((int)grid), dim3(NT), 0, s, a);
 }
-
 
 // Anchors (each component's smallest vertex with an edge), global ids.
 __global__ void k_b_anchors(const int32_t* rp, const BatchGraph* meta, const int64_t* vo, int32_t G,
@@ -740,19 +782,22 @@ BatchPlan plan_batch(const fi_graph* h, int64_t trees) {
   p.multi = h->sched.path == 4;
   if (h->sched.path == 0) {
     // Path 4 takes the longest graph's levels plus its share of the edge walks,
-    // path 1 the walks of every tree alone, slower past the graphs of which a
-    // CU holds several trees in LDS (us, fitted on uneven batches: 64 graphs of
-    // up to 1,000 vertices and 16 trees 311 and 93; 300 of up to 3,000 and 64
-    // trees 1,040 and 1,510; 64 of up to 10,000 and 64 trees 3,220 and 3,320;
-    // 1,000 of up to 10,000 and 64 trees 6,380 and 57,300).
+    // path 1 the walks of every tree alone, slower past the graphs whose trees
+    // fit LDS (us, fitted on uneven batches, paths 4 and 1: 64 graphs of up to
+    // 1,000 vertices and 16 trees 321 and 77; 334 of up to 1,850 and 26 trees 616
+    // and 325; 300 of up to 6,000 and 32 trees 1,730 and 980, 600 and 64 trees
+    // 2,770 and 3,600; 200 of up to 10,000 and 20 trees 2,820 and 840, 1,000 and 64
+    // trees 5,700 and 11,400).
     const double walks = (double)trees * (double)bi->nnz_total;
-    const double t4 = 0.015 * (double)bi->nnz_max + 2e-6 * walks;
-    const double t1 = 60.0 + (bi->n_max > 4000 ? 1.8e-5 : 5e-6) * walks;
+    const double t4 = 180.0 + 0.0125 * (double)bi->nnz_max + 1.2e-6 * walks;
+    const double t1 = 40.0 + (bi->n_max > kLdsMaxN ? 1.8e-5 : 3.2e-6) * walks;
     p.multi = trees >= 16 && t4 <= t1;
-    const size_t lds = 12 * (size_t)bi->n_max_small;
+    // path 1: as many threads as a CU's registers hold in two workgroups, unless
+    // LDS holds only one or the trees are few; small graphs' in four
+    const int32_t n = bi->n_max_small;
     p.block = p.multi ? 1024
-              : lds > 65536 || trees * bi->G <= h->cu_count ? 1024
-              : lds <= 24576 && trees * bi->G > 16 * (int64_t)h->cu_count ? 256 : 512;
+              : n > 7500 || trees * bi->G <= h->cu_count ? 1024
+              : n <= 2048 && trees * bi->G > 16 * (int64_t)h->cu_count ? 256 : 512;
     // few graphs: their trees are cut into smaller groups, down to eight, until
     // every CU has one
     while (p.multi && (int64_t)bi->G * p.groups * 2 <= h->cu_count && p.per > 8) {
@@ -1093,14 +1138,14 @@ int fi_batch_sweep(fi_graph* h, int64_t trees_per_graph, uint64_t seed, uint64_t
   for (int cls = 0; cls < 2 && e == hipSuccess && !multi; ++cls) {
     const bool lds = cls == 0;
     a.order = (const int32_t*)(ws + (lds ? L.small : L.large));
-    a.nitems = (int64_t)(lds ? bi->n_small : bi->n_large) * trees_per_graph;
+    const int32_t count = lds ? bi->n_small : bi->n_large;
     a.ticket = ctl + (lds ? kTicket0 : kTicket1);
-    if (a.nitems == 0) continue;
+    if (count == 0) continue;
     void* tok = nullptr;
     if (prof_begin(h, s, &tok)) return FI_EDEVICE;
-    if (nt == 1024) launch_class<1024>(h, a, lds, s);
-    else if (nt == 512) launch_class<512>(h, a, lds, s);
-    else launch_class<256>(h, a, lds, s);
+    if (nt == 1024) launch_class<1024>(h, a, count, lds, s);
+    else if (nt == 512) launch_class<512>(h, a, count, lds, s);
+    else launch_class<256>(h, a, count, lds, s);
     e = hipGetLastError();
     prof_end(h, s, tok, 0);
   }
