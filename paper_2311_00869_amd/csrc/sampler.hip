@@ -352,13 +352,16 @@ struct KShared {
   uint32_t count, next, hooked;
 };
 
-constexpr int kKBatch = 4;  // edges per thread in flight
+// edges per thread in flight (with the trees in LDS, 1,000 of 8,000 / 40,000 476 us
+// with four, 510 with two; else 500 of 20,000 / 100,000 1,996 and 1,933)
+constexpr int k_batch(int mode) { return mode == 0 ? 4 : 2; }
 
 // MODE 0: lightest edges and forest in LDS, a round touches every vertex; 1:
 // the forest in LDS; 2: none.
 template <int NT, int MODE>
 __global__ void __launch_bounds__(NT) k_sweep_kruskal(DevGraph G, SweepArgs A, KruskalArgs K) {
   constexpr uint32_t kPar = 0x80000000u, kPtr = 0x7FFFFFFFu;
+  constexpr int kKBatch = k_batch(MODE);
   __shared__ KShared<NT> sh;
   extern __shared__ uint64_t dyn[];
   const int tid = threadIdx.x;
@@ -432,6 +435,11 @@ __global__ void __launch_bounds__(NT) k_sweep_kruskal(DevGraph G, SweepArgs A, K
             ru[k] = q[uv[k].x] & kPtr;
             rv[k] = q[uv[k].y & kVertexMask] & kPtr;
           }
+          // (in the last rounds most edges lie inside a tree)
+          bool any = false;
+#pragma unroll
+          for (int k = 0; k < kKBatch; ++k) any |= e[k] >= 0 && ru[k] != rv[k];
+          if (!__ballot(any)) return;
 #pragma unroll
           for (int k = 0; k < kKBatch; ++k) {
             const bool out = e[k] >= 0 && ru[k] != rv[k];
@@ -458,6 +466,17 @@ __global__ void __launch_bounds__(NT) k_sweep_kruskal(DevGraph G, SweepArgs A, K
           }
 #pragma unroll
           for (int k = 0; k < kKBatch; ++k) e[k] = i0 + k * NT + tid < nroot ? edge_of(r[k]) : ~0u;
+          if constexpr (MODE == 0) {  // (and most vertices are no roots)
+            bool any = false;
+#pragma unroll
+            for (int k = 0; k < kKBatch; ++k) any |= e[k] != ~0u;
+            if (!__ballot(any)) {
+#pragma unroll
+              for (int k = 0; k < kKBatch; ++k)
+                if (i0 + k * NT + tid < nroot) decided(r[k]) = ~0u;
+              continue;
+            }
+          }
 #pragma unroll
           for (int k = 0; k < kKBatch; ++k)
             uv[k] = e[k] != ~0u ? G.edges[e[k]] : make_uint2(0u, 0u);
