@@ -28,6 +28,7 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 constexpr int kCtlPerGraph = 32;       // err, best, distinct count, trees; own 256-byte line
 constexpr int32_t kMaxBatchN = 1000000;
 constexpr int kLdsMaxN = 15000;        // graphs up to this size keep their tree in LDS (10 bytes a vertex)
+static_assert(kLdsMaxN <= wg::kEMaxN, "packed edges");
 // item tickets of the two size classes, each on its own 128-byte line of the
 // batch control block
 constexpr int kTicket0 = C_UNIT;

@@ -20,6 +20,7 @@ __global__ void __launch_bounds__(NT) k_sweep_edges(DevGraph G, SweepArgs A, int
 
 template <int NT>
 hipError_t edges_launch(fi_graph* g, const SweepArgs& a, hipStream_t s) {
+  if (g->dg.n > wg::kEMaxN) return hipErrorInvalidValue;
   const size_t lds = 10 * (size_t)g->dg.n;
   hipError_t e = hipFuncSetAttribute((const void*)k_sweep_edges<NT>,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
