@@ -13,6 +13,7 @@ import threading
 
 import numpy as np
 import torch
+from torch.autograd import forward_ad
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libfrustration.so")
@@ -405,12 +406,12 @@ class Graph:
         work = torch.empty_like(g)
         # a plain Gamma_0 that nothing else writes during the call is read where
         # it lies; any other (another type, layout, device or stream, a negation
-        # not carried out yet, under autograd, or sharing memory with the
-        # result) is copied first
+        # not carried out yet, under autograd in either direction, or sharing
+        # memory with the result) is copied first
         direct = (type(gamma0) is torch.Tensor and gamma0.dtype == torch.float32
                   and gamma0.shape == g.shape and gamma0.device == g.device and gamma0.is_contiguous()
                   and g.is_contiguous() and not gamma0.is_neg() and not gamma0.requires_grad
-                  and stream is None
+                  and forward_ad.unpack_dual(gamma0).tangent is None and stream is None
                   and gamma0.untyped_storage().data_ptr() != g.untyped_storage().data_ptr())
         if not direct:
             g.copy_(gamma0)

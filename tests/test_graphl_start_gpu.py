@@ -31,3 +31,15 @@ def test_start_that_is_a_lazy_negation(graph, steps):
     want, _ = graph.graphl_descend(-gamma, steps)
     got, _ = graph.graphl_descend(lazy, steps)
     assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("steps", [0, 3])
+def test_start_with_a_forward_tangent(graph, steps):
+    import torch.autograd.forward_ad as ad
+    gamma = _start(graph)
+    tangent = torch.ones_like(gamma)
+    want, _ = graph.graphl_descend(gamma, steps)
+    with ad.dual_level():
+        got, _ = graph.graphl_descend(ad.make_dual(gamma, tangent), steps)
+        primal, kept = ad.unpack_dual(got)
+        assert torch.equal(primal, want) and kept is not None and torch.equal(kept, tangent)
