@@ -405,13 +405,15 @@ class Graph:
                                                     device=self.device)
         work = torch.empty_like(g)
         # a plain Gamma_0 that nothing else writes during the call is read where
-        # it lies; any other (another type, layout, device or stream, a negation
-        # not carried out yet, under autograd in either direction, or sharing
-        # memory with the result) is copied first
+        # it lies; any other (another type, layout, alignment, device or stream,
+        # a negation not carried out yet, under autograd in either direction, or
+        # sharing memory with the result) is copied first.  (Off a float4's
+        # alignment long rows are summed in another order, and slower.)
         direct = (type(gamma0) is torch.Tensor and gamma0.dtype == torch.float32
                   and gamma0.shape == g.shape and gamma0.device == g.device and gamma0.is_contiguous()
-                  and g.is_contiguous() and not gamma0.is_neg() and not gamma0.requires_grad
-                  and forward_ad.unpack_dual(gamma0).tangent is None and stream is None
+                  and gamma0.data_ptr() % 16 == 0 and g.is_contiguous() and not gamma0.is_neg()
+                  and not gamma0.requires_grad and forward_ad.unpack_dual(gamma0).tangent is None
+                  and stream is None
                   and gamma0.untyped_storage().data_ptr() != g.untyped_storage().data_ptr())
         if not direct:
             g.copy_(gamma0)

@@ -43,3 +43,17 @@ def test_start_with_a_forward_tangent(graph, steps):
         got, _ = graph.graphl_descend(ad.make_dual(gamma, tangent), steps)
         primal, kept = ad.unpack_dual(got)
         assert torch.equal(primal, want) and kept is not None and torch.equal(kept, tangent)
+
+
+@pytest.mark.parametrize("R", [4, 32])
+def test_start_off_the_vector_alignment(graph, R):
+    # rows of several items are summed by the lane layout, which the alignment
+    # chooses: a start off it gives the same bits as one on it
+    gamma = _start(graph, R)
+    flat = torch.empty(gamma.numel() + 1, device="cuda")
+    shifted = flat[1:].view(gamma.shape)
+    shifted.copy_(gamma)
+    assert shifted.data_ptr() % 16 and shifted.is_contiguous()
+    want, _ = graph.graphl_descend(gamma, 3)
+    got, _ = graph.graphl_descend(shifted, 3)
+    assert torch.equal(got, want)
