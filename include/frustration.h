@@ -370,7 +370,8 @@ int fi_switch_list(fi_graph* g, const uint64_t* d_bits, int32_t* d_uv_out, int64
  * number of trees whose balanced state switches edge e (fi_edge_list
  * order).  The trees also enter the cloud, as with fi_sweep_range.  Runs on
  * the multi-tree schedule whatever fi_set_schedule chose (results are the
- * same on every schedule). */
+ * same on every schedule).  May be captured; a replay must not overlap another
+ * sweep of the handle. */
 int fi_sweep_stats(fi_graph* g, int64_t t0, int64_t t1, uint64_t seed, uint64_t* d_vertex_minus,
                    uint64_t* d_edge_switched, void* stream);
 
