@@ -177,6 +177,7 @@ struct SweepArgs {
 enum : int { kSamplerBfs = 0, kSamplerRdfs = 1, kSamplerHybrid = 2, kSamplerKruskal = 3 };
 
 // ----------------------------------------------------------------- layout
+constexpr int32_t kLinksMaxN = 12288;  // above the graphs whose trees fit LDS
 constexpr int kGridSlots = 8;  // trees in flight on the whole-grid path (max)
 constexpr int kGridCtlWords = 128;          // control words per tree slot
 constexpr int kGridBarWords = 32;             // barrier words per tree slot (group_sync)
@@ -193,6 +194,7 @@ struct Layout {
   size_t gwstride;     // per-slot bitmap stride (words rounded up to 32)
   size_t slots;        // one-workgroup-per-tree scratch in workspace memory
   size_t nslots, slot_stride;
+  size_t links, nlinks;  // randomized DFS with its trees in LDS: entries with their neighbours' rows
   // multi-tree path: vertices listed by component, root-finding tasks, and
   // `msets` sets of a pass's working state, mset_stride bytes apart
   size_t aslot, cverts, ccount, cptr, mtasks, mtcap, mhcap, nbigcap;

@@ -633,6 +633,11 @@ Layout make_layout(int32_t n, int64_t nnz, int64_t cloud_capacity, uint64_t tabl
     L.nslots = std::min<size_t>(2048, std::max<size_t>(1, budget / L.slot_stride));
   }
   L.slots = take(L.slot_stride * L.nslots);
+  // the randomized DFS's entries with their neighbours' rows, where its trees
+  // lie in LDS: not in the slots, which sweeps on other streams may be using
+  // (past the slots' size it reads the rows themselves)
+  L.nlinks = n <= kLinksMaxN && 8 * (size_t)nnz <= L.slot_stride * L.nslots ? (size_t)nnz : 0;
+  L.links = take(8 * L.nlinks);
   L.aslot = take(4 * nn);
   L.cverts = take(4 * nn);
   L.ccount = take(4 * (nn / 2 + 1));

@@ -636,20 +636,27 @@ hipError_t launch_rdfs(fi_graph* g, const SweepArgs& a, int path, hipStream_t s)
   // the CSR in LDS while it leaves room for them
   if (csr + want * (marks + stack) <= most)
     return rdfs_launch<true, false, true, true>(g, a, r, (int)want, csr + want * (marks + stack), 0, s);
-  // else one wave per workgroup, the links in the slots' region, in front of
-  // the slots, where they leave room for four waves per CU
+  // else one wave per workgroup, with links: on path 1, whose sweeps may overlap
+  // others of the handle, in a region of their own (every launch writes the same
+  // bytes there); on path 2 in the slots' region, in front of the slots, where
+  // they leave room for four waves per CU
   size_t region = g->L.slot_stride * g->L.nslots;
   const bool stk_lds = path == 1 || (g->dg.n <= kStackMaxN && (marks + stack) * want <= most);
   const bool marks_lds = marks * want <= most;
   r.slot_stride = ((stk_lds ? 0 : 4 * n) + (stk_lds || marks_lds ? 0 : marks) + 255) & ~(size_t)255;
   const size_t links = (8 * (size_t)g->dg.nnz + 255) & ~(size_t)255;
-  if (g->dg.n <= kLinkMaxN && links + r.slot_stride * std::min<uint64_t>(trees, 4 * cus) <= region) {
-    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((g->dg.nnz + 255) / 256, 16384));
-    hipLaunchKernelGGL(k_rdfs_links, dim3(grid), dim3(256), 0, s, g->dg.row_ptr, g->dg.adj, g->dg.nnz,
-                       (uint2*)r.slots);
-    r.links = (const uint2*)r.slots;
+  uint2* at = nullptr;
+  if (path == 1) {
+    if (g->L.nlinks == (size_t)g->dg.nnz) at = (uint2*)(g->ws + g->L.links);
+  } else if (g->dg.n <= kLinkMaxN && links + r.slot_stride * std::min<uint64_t>(trees, 4 * cus) <= region) {
+    at = (uint2*)r.slots;
     r.slots += links;
     region -= links;
+  }
+  if (at) {
+    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((g->dg.nnz + 255) / 256, 16384));
+    hipLaunchKernelGGL(k_rdfs_links, dim3(grid), dim3(256), 0, s, g->dg.row_ptr, g->dg.adj, g->dg.nnz, at);
+    r.links = at;
   }
   const size_t slots = r.slot_stride ? region / r.slot_stride : 0;
   const size_t lds = (stk_lds ? stack : 0) + (stk_lds || marks_lds ? marks : 0);
