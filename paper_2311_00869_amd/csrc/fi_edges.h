@@ -11,8 +11,11 @@
 // m = 5,000: 47 us (through a queue of each level's vertices: 82), 100 of them 16
 // (30); 760 of 4,709 / 16,129 105 (216), 300 of 10,000 / 80,000 238 (451).  110
 // registers: with 24 edges held 96 and the same times, with 16 80 and 5 to 15% more.
-// On a deep graph with few edges to a level the queue does less (100 trees of a
-// 100 by 100 grid: 440 us, here 500).
+// On a deep graph few edges lie in a level and all are looked at in each, so once
+// the vertices left are more than kEFew levels like the last, a tree goes on
+// through a queue, lanes spread over the frontier's rows (deep_levels).  100 trees
+// of a 100 by 100 grid 195 us (over the edges to the end 496, through a queue alone
+// 409), of a ring of 10,000 with 10 neighbours on either side 539 (7,760, 1,039).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -30,6 +33,10 @@ constexpr int kEBatch = 8;   // edges in flight
 constexpr uint32_t kEMask = 0x7FFF;   // a vertex as its byte offset in the 16-bit levels
 constexpr int32_t kEMaxN = 1 << 14;
 constexpr uint32_t kELast = 0xFFFF;   // level of a vertex not yet reached
+// levels that go over the edges in any case (a random graph's largest level comes
+// by then; the first 16 of the ring above take 140 us more than the first 6)
+constexpr uint32_t kEDeep = 6;
+constexpr int32_t kEFew = 16;
 
 template <int NT>
 struct EShared {
@@ -39,6 +46,51 @@ struct EShared {
 
 __device__ __forceinline__ uint32_t pack_edge(uint2 e) {
   return 2 * e.x | (2 * (e.y & kVertexMask)) << 15 | (e.y & 0x80000000u);
+}
+
+// The levels after level L of a tree with `left` vertices to reach, through a
+// queue in the place of the levels (16 bits a vertex too).  A word gets the
+// number of the level in front of its parent key, those of vertices reached
+// before 0, so that no later level changes it.  Each row of the frontier is
+// read by as many lanes, a power of two up to 64, as the threads give it.
+template <int NT>
+__device__ __forceinline__ void deep_levels(const DevGraph& G, const KeyMix& km, uint32_t L, int32_t left,
+                                            EShared<NT>& sh, uint64_t* pw, uint16_t* lev) {
+  const int tid = threadIdx.x;
+  for (int32_t v = tid; v < G.n; v += NT) {
+    const uint64_t w = pw[v];
+    if (w != ~0ull) pw[v] = (w & 1) | (uint64_t)(lev[v] == L) << 33;
+  }
+  __syncthreads();
+  if (tid < 3) sh.found[tid] = 0;
+  __syncthreads();
+  uint16_t* q = lev;
+  for (int32_t v = tid; v < G.n; v += NT)
+    if (pw[v] >> 33 == 1) q[atomicAdd(&sh.found[0], 1u)] = (uint16_t)v;
+  __syncthreads();
+  uint32_t lo = 0, hi = sh.found[0];
+  for (uint32_t k = 2; left > 0 && lo < hi; ++k) {
+    uint32_t* found = &sh.found[(k - 1) % 3];
+    int lg = 0;
+    while (lg < 6 && (hi - lo) << (lg + 1) <= (uint32_t)NT) ++lg;
+    const int32_t lane = tid & ((1 << lg) - 1);
+    for (uint32_t i = lo + ((uint32_t)tid >> lg); i < hi; i += (uint32_t)NT >> lg) {
+      const int32_t u = q[i];
+      const int32_t e1 = G.row_ptr[u + 1];
+      const uint64_t w0 = (uint64_t)k << 33 | (uint64_t)vkey(km, (uint32_t)u) << 1 | (pw[u] & 1);
+      for (int32_t e = G.row_ptr[u] + lane; e < e1; e += 1 << lg) {
+        const uint32_t a = G.adj[e], v = a & kVertexMask;
+        const uint64_t w = w0 ^ (uint64_t)(a >> 31);
+        if (pw[v] > w && amin64(pw + v, w) == ~0ull) q[hi + atomicAdd(found, 1u)] = (uint16_t)v;
+      }
+    }
+    __syncthreads();
+    const uint32_t f = *found;
+    if (tid == 0) sh.found[(k + 1) % 3] = 0;
+    lo = hi;
+    hi += f;
+    left -= (int32_t)f;
+  }
 }
 
 // Trees t0, t0 + step, ... below t1 of G; `later`: its vertices that are not a
@@ -152,6 +204,10 @@ __device__ __forceinline__ void edges_trees(const DevGraph& G, const SweepArgs& 
       if (tid == 0) sh.found[(L + 2) % 3] = 0;
       if (f == 0) break;  // (no component runs out before its last vertex)
       left -= (int32_t)f;
+      if (L + 1 >= kEDeep && left > kEFew * (int32_t)f) {
+        deep_levels<NT>(G, km, L + 1, left, sh, pw, lev);
+        break;
+      }
     }
 
     // the states in place of the levels

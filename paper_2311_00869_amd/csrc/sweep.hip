@@ -147,9 +147,9 @@ hipError_t launch_sweep(fi_graph* g, const SweepArgs& a, hipStream_t s) {
   hipError_t e;
   if ((path == 4 || path == 5) && g->sched.path == 0 && tree_fits_lds(g) && !capturing(s)) {
     // Sweeps in LDS share no scratch memory that they do not all fill alike
-    // (launch_rdfs), so those of one handle may overlap on several streams; here they take turns with it.  (Not a captured one,
-    // statistics: its event would be the graph's, and the next sweep would not
-    // wait for the last one.)
+    // (launch_rdfs), so those of one handle may overlap on several streams; here
+    // they take turns with it.  (Not a captured one, statistics: its event would
+    // be the graph's, and the next sweep would not wait for the last one.)
     std::lock_guard<std::mutex> lock(g->ms_lock);
     e = hipSuccess;
     if (!g->ms_done) e = hipEventCreateWithFlags(&g->ms_done, hipEventDisableTiming);
