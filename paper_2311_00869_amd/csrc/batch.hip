@@ -794,11 +794,15 @@ BatchPlan plan_batch(const fi_graph* h, int64_t trees) {
     const double t1 = 40.0 + (bi->n_max > kLdsMaxN ? 1.8e-5 : 3.2e-6) * walks;
     p.multi = trees >= 16 && t4 <= t1;
     // path 1: as many threads as a CU's registers hold in two workgroups, unless
-    // LDS holds only one or the trees are few; small graphs' in four
+    // LDS holds only one or the trees are few; small graphs' in four, from fewer
+    // trees the smaller they are (us with 256 and 512 threads, 300 graphs: 1,000
+    // vertices 111 and 104 with 4 trees, 147 and 161 with 8; rings of 1,000 with 8,
+    // which take 100 levels, 367 and 565; 2,000 / 12,000 with 8 270 and 236)
     const int32_t n = bi->n_max_small;
+    const int64_t all = trees * bi->G, cus = h->cu_count;
     p.block = p.multi ? 1024
-              : n > 7500 || trees * bi->G <= h->cu_count ? 1024
-              : n <= 2048 && trees * bi->G > 16 * (int64_t)h->cu_count ? 256 : 512;
+              : n > 7500 || all <= cus ? 1024
+              : (n <= 1024 && all > 6 * cus) || (n <= 2048 && all > 16 * cus) ? 256 : 512;
     // few graphs: their trees are cut into smaller groups, down to eight, until
     // every CU has one
     while (p.multi && (int64_t)bi->G * p.groups * 2 <= h->cu_count && p.per > 8) {

@@ -121,3 +121,25 @@ def test_a_deep_tree_in_lds_is_no_slower_than_in_memory():
     lds, memory = (_sweep_ms(G, 100, path=p, block=1024) for p in (1, 2))
     assert lds <= memory
     G.close()
+
+
+def test_automatic_block_of_a_batch_of_deep_graphs():
+    # eight trees of 300 small rings: little to do in a level, so narrow
+    # workgroups, four to a CU
+    B = fr.BatchGraph([_ring(1000, 5)] * 300, cloud_capacity_per_graph=8)
+
+    def ms(**schedule):
+        B.set_schedule(**schedule)
+        best = float("inf")
+        mn = torch.empty((B.G, 2), dtype=torch.int64, device="cuda")
+        for _ in range(4):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            B.sweep_into(8, 5, mn)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+
+    assert ms(path=0) <= 1.25 * ms(path=1, block=256)
+    B.close()
