@@ -224,10 +224,14 @@ constexpr int kOrderMax = 16384;
 
 // multi-tree path constants shared by create and the kernel
 constexpr int kMSplit = 2048;     // rows longer than this are split into units of this many edges
-// The automatic schedule, by work = n + m/2: the multi-tree path from
-// kMultiMinWork on; on a deep graph only past kDeepWork
+// The automatic schedule, by work = n + m/2 and the levels of a BFS from the
+// hubs: a deep graph of up to kDeepWork is swept one tree per workgroup.  Where
+// trees fit LDS the levels are counted, and trees ordered, from kMultiMinWork on.
 constexpr int64_t kMultiMinWork = 20000;
 constexpr int64_t kDeepWork = 135000;
+constexpr int32_t kDeepLevels = 64;   // deep whatever the work
+constexpr int32_t kDeepPerLevel = 1000;  // deep with less work than this per level,
+constexpr uint64_t kDeepManyTrees = 192;  // than half of it from so many trees
 constexpr int kMSets = 8;         // passes in flight on the multi-tree path (max)
 constexpr int kMCtlWords = 1024;  // control words of a pass
 constexpr int kBigComp = 1024;    // components larger than this find their roots in chunks
@@ -301,7 +305,8 @@ struct fi_graph {
   int32_t main_begin, main_end;  // its vertices in cverts
   int32_t main_big;       // its row of big-component root minima (-1: not a big component)
   bool cent;              // distance sums for the tree order are in the workspace
-  bool deep;              // a BFS of the main component takes more than kDeepLevels levels
+  int32_t levels;         // of a BFS from the hubs, and of every component's up to kDeepWork
+                          // (a few past those that make it deep at most; 0: not counted)
   uint64_t* plog;         // phase log of the multi-tree kernel (null: off)
   int64_t pcap;           // its length in words
   fi_schedule sched;
@@ -319,3 +324,20 @@ struct fi_graph {
   bool is_batch;
   void* batch;        // fi::BatchInfo*
 };
+
+namespace fi {
+// a BFS tree's words and levels fit LDS (path 1)
+inline bool bfs_fits_lds(const fi_graph* g) {
+  return 12 * (size_t)g->dg.n + 32768 <= (size_t)g->max_shared;
+}
+// The levels past which a graph is deep.  100 trees of 13,000 vertices take 567 us on
+// the multi-tree path and 683 one per workgroup at 17 levels (18,000 edges), 870
+// and 606 at 27 (a tree), of 30,000 1,560 and 1,550 at 46 (33,000 edges), of 60,000
+// 1,940 and 3,210 at 55 (66,000); from about one tree per CU on, one per workgroup
+// takes twice as long (1,000 of the 13,000: 1,180 and 1,650 at 27 levels, 3,630 and
+// 1,870 at 96).
+inline int64_t deep_levels(const fi_graph* g, uint64_t trees) {
+  const int64_t per = ((int64_t)g->dg.n + g->dg.m / 2) / kDeepPerLevel * (trees < kDeepManyTrees ? 1 : 2);
+  return per < kDeepLevels ? per : kDeepLevels;
+}
+}  // namespace fi

@@ -12,7 +12,8 @@
 // only on (graph, seed, tree), and the cloud combines trees with
 // commutative atomics, so the order changes the speed and nothing else.
 //
-// At upload: the distance sums (one multi-source BFS, one bit per hub).
+// At upload: the distance sums (one multi-source BFS, one bit per hub) and, from
+// the same BFS, the levels that the automatic schedule goes by.
 // Per block of trees: the root of each tree in the component with the most
 // vertices (its minimum-key vertex, the root rule of the sampler), then the
 // sort; the pass reads these roots instead of searching that component again.
@@ -33,7 +34,6 @@ constexpr int kChunkMax = 4096;               // vertices per root-search task (
 constexpr int kRootTasks = 4096;              // that leaves less than this many tasks)
 constexpr int32_t kInvertMin = 1 << 17;       // main components from this size invert the key
 constexpr int kCentBatch = 8;                 // BFS levels launched per look at their flags
-constexpr uint32_t kDeepLevels = 64;          // a BFS from the hubs of more levels is deep
 constexpr int kInvPerLane = 4;                // candidate keys per lane and step
 constexpr int32_t kCentWide = 256;            // rows longer than this take a wave each
 
@@ -73,16 +73,28 @@ struct Hubs {
   int32_t count;
 };
 
-// Empty bytes, but hub h starts its BFS: bit h of its visit and frontier bytes.
-__global__ void k_cent_seed(int32_t n, Hubs hubs, uint8_t* vis, uint8_t* front, uint16_t* dsum,
-                            uint32_t* any) {
-  if (blockIdx.x == 0 && threadIdx.x < kCentBatch) any[threadIdx.x] = 0;
+// Empty bytes, but hub h, if it lies in the main component, starts its BFS: bit
+// h of its visit and frontier bytes.  Without such a hub the main component's
+// anchor takes bit 0, and with `others` so does every other component's: the
+// levels are then those of all components.  any[kCentBatch]: the bits in use in
+// the main component.
+__global__ void k_cent_seed(const int32_t* rp, const int32_t* comp, int32_t n, Hubs hubs,
+                            const int32_t* main_anchor, bool others, uint8_t* vis, uint8_t* front,
+                            uint16_t* dsum, uint32_t* any) {
+  const int32_t main = main_anchor ? *main_anchor : -1;
+  uint32_t in_main = 0;
+#pragma unroll
+  for (int h = 0; h < kHubs; ++h)
+    if (h < hubs.count && comp[hubs.v[h]] == main) in_main |= 1u << h;
+  if (blockIdx.x == 0 && threadIdx.x <= kCentBatch)
+    any[threadIdx.x] = threadIdx.x < kCentBatch ? 0u : in_main ? in_main : 1u;
   for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n;
        v += (int64_t)gridDim.x * blockDim.x) {
     uint8_t m = 0;
 #pragma unroll
     for (int h = 0; h < kHubs; ++h)
-      if (h < hubs.count && hubs.v[h] == v) m |= (uint8_t)(1u << h);
+      if ((in_main >> h & 1) && hubs.v[h] == v) m |= (uint8_t)(1u << h);
+    if (comp[v] == v && rp[v + 1] > rp[v] && (v == main ? in_main == 0 : others)) m = 1;
     vis[v] = m;
     front[v] = m;
     dsum[v] = 0;
@@ -91,8 +103,7 @@ __global__ void k_cent_seed(int32_t n, Hubs hubs, uint8_t* vis, uint8_t* front, 
 
 // One BFS level for all hubs at once: a vertex not yet reached by every hub
 // takes the hubs that reached one of its neighbours at the previous level,
-// and adds `level` for each of them to its distance sum.  Rows longer than
-// kCentWide are left to k_cent_wide.
+// and adds `level` for each of them to its distance sum.
 __device__ __forceinline__ void cent_take(int32_t v, uint8_t have, uint8_t nb, uint8_t* next,
                                           uint8_t* vis, uint16_t* dsum, uint32_t level, bool& grew) {
   const uint8_t fresh = (uint8_t)(nb & ~have);
@@ -106,17 +117,24 @@ __device__ __forceinline__ void cent_take(int32_t v, uint8_t have, uint8_t nb, u
 
 // Workgroups 0 .. row_blocks - 1 take the short rows, a thread each; the
 // others the rows longer than kCentWide (rows[0, nrows)), a wave each with its
-// lanes over the row's entries.
-__global__ void k_cent_level(const int32_t* rp, const uint32_t* adj, int32_t n, const int32_t* rows,
-                             int32_t nrows, uint32_t row_blocks, uint8_t full, const uint8_t* front,
-                             uint8_t* next, uint8_t* vis, uint16_t* dsum, uint32_t level,
-                             uint32_t* any) {
+// lanes over the row's entries.  A vertex has all it can get with the bits of
+// *seeds in the main component and with bit 0, or none, beside it.
+__global__ void k_cent_level(const int32_t* rp, const uint32_t* adj, const int32_t* comp, int32_t n,
+                             const int32_t* rows, int32_t nrows, uint32_t row_blocks,
+                             const uint32_t* seeds, const int32_t* main_anchor, bool others,
+                             const uint8_t* front, uint8_t* next, uint8_t* vis, uint16_t* dsum,
+                             uint32_t level, uint32_t* any) {
   bool grew = false;
+  const int32_t main = main_anchor ? *main_anchor : -1;
+  const uint8_t full_main = (uint8_t)*seeds;
+  auto full_of = [&](int64_t v, uint8_t have) -> uint8_t {
+    return have == full_main || comp[v] == main ? full_main : others ? 1 : 0;
+  };
   if (blockIdx.x < row_blocks) {
     for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n;
          v += (int64_t)row_blocks * blockDim.x) {
       if (rp[v + 1] - rp[v] > kCentWide) continue;
-      const uint8_t have = vis[v];
+      const uint8_t have = vis[v], full = full_of(v, have);
       uint8_t nb = 0;
       if (have != full) {
         for (int32_t e = rp[v]; e < rp[v + 1]; ++e) {
@@ -133,7 +151,7 @@ __global__ void k_cent_level(const int32_t* rp, const uint32_t* adj, int32_t n, 
     const int64_t nwaves = ((int64_t)(gridDim.x - row_blocks) * blockDim.x) >> 6;
     for (int64_t k = wave; k < nrows; k += nwaves) {
       const int32_t v = rows[k];
-      const uint8_t have = vis[v];
+      const uint8_t have = vis[v], full = full_of(v, have);
       uint32_t nb = 0;
       if (have != full) {
         const int32_t e1 = rp[v + 1];
@@ -281,9 +299,13 @@ __global__ void __launch_bounds__(kSortThreads) k_order(const uint64_t* oroot, c
 
 int centrality_setup(fi_graph* g, hipStream_t s) {
   g->cent = false;
-  g->deep = false;
+  g->levels = 0;
   const int32_t n = g->dg.n;
-  if (g->main_big < 0 || (int64_t)n + g->dg.m / 2 < kMultiMinWork) return FI_OK;
+  const int64_t work = (int64_t)n + g->dg.m / 2;
+  // Beyond LDS every graph that is small enough for path 2 has its levels
+  // counted, whatever its components.
+  const bool main = g->main_big >= 0, small = work <= kDeepWork;
+  if (bfs_fits_lds(g) ? !main || work < kMultiMinWork : !main && !small) return FI_OK;
   // the kHubs vertices of highest degree (ties to the smaller id)
   std::vector<int32_t> rp((size_t)n + 1);
   if (hipMemcpyAsync(rp.data(), g->dg.row_ptr, 4 * ((size_t)n + 1), hipMemcpyDeviceToHost, s) !=
@@ -316,8 +338,9 @@ int centrality_setup(fi_graph* g, hipStream_t s) {
   const int32_t nwide = (int32_t)wide.size();
   const unsigned row_blocks = (unsigned)grid_for(n, 256);
   const unsigned blocks = row_blocks + (nwide > 0 ? (unsigned)grid_for((int64_t)nwide * 64, 256) : 0u);
-  hipLaunchKernelGGL(k_cent_seed, dim3(row_blocks), dim3(256), 0, s, n, hubs, vis, front, dsum, any);
-  const uint8_t full = (uint8_t)((1u << nh) - 1);
+  const int32_t* anchor = main ? g->dg.anchors + g->gl_main_slot : nullptr;
+  hipLaunchKernelGGL(k_cent_seed, dim3(row_blocks), dim3(256), 0, s, g->dg.row_ptr, g->dg.comp, n, hubs,
+                     anchor, small, vis, front, dsum, any);
   // kCentBatch levels per look at their flags (a level past the last one
   // finds an empty frontier and changes nothing)
   bool grows = true;
@@ -327,23 +350,23 @@ int centrality_setup(fi_graph* g, hipStream_t s) {
       hipLaunchKernelGGL(k_fill64, dim3(1), dim3(64), 0, s, (uint64_t*)any, (int64_t)kCentBatch / 2,
                          (uint64_t)0);
     for (int k = 0; k < kCentBatch; ++k, ++level) {
-      hipLaunchKernelGGL(k_cent_level, dim3(blocks), dim3(256), 0, s, g->dg.row_ptr, g->dg.adj, n,
-                         (const int32_t*)rows, nwide, row_blocks, full, (const uint8_t*)front, next,
-                         vis, dsum, level, any + k);
+      hipLaunchKernelGGL(k_cent_level, dim3(blocks), dim3(256), 0, s, g->dg.row_ptr, g->dg.adj, g->dg.comp,
+                         n, (const int32_t*)rows, nwide, row_blocks, (const uint32_t*)any + kCentBatch, anchor,
+                         small, (const uint8_t*)front, next, vis, dsum, level, any + k);
       std::swap(front, next);
     }
     if (hipMemcpyAsync(grew, any, sizeof(grew), hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
       return FI_EDEVICE;
-    for (int k = 0; k < kCentBatch; ++k) grows = grows && grew[k];
-    if (grows && level > kDeepLevels) {
-      g->deep = true;
-      // below kDeepWork such a graph is swept one tree per workgroup, in any order
-      if ((int64_t)n + g->dg.m / 2 <= kDeepWork) return FI_OK;
+    for (int k = 0; k < kCentBatch; ++k) {
+      grows = grows && grew[k];
+      if (grows) ++g->levels;
     }
+    // up to kDeepWork such a graph is swept one tree per workgroup, in any order
+    if (g->levels > deep_levels(g, kDeepManyTrees) && small) return FI_OK;
   }
   if (hipGetLastError() != hipSuccess) return FI_EDEVICE;
-  g->cent = true;
+  g->cent = main;
   return FI_OK;
 }
 

@@ -143,3 +143,73 @@ def test_automatic_block_of_a_batch_of_deep_graphs():
 
     assert ms(path=0) <= 1.25 * ms(path=1, block=256)
     B.close()
+
+
+def _ladder(L):
+    a = np.arange(L)
+    return _csr(2 * L, [a[:-1], a[:-1] + L, a], [a[1:], a[1:] + L, a + L])
+
+
+def _paths(c, L):
+    a = np.arange(c * L).reshape(c, L)
+    return _csr(c * L, [a[:, :-1].ravel()], [a[:, 1:].ravel()])
+
+
+def _star_and_paths():
+    """A star, the main component, and long paths beside it."""
+    u, v, n = [np.zeros(12999, np.int64)], [np.arange(1, 13000)], 13000
+    for _ in range(3):
+        u.append(n + np.arange(1999))
+        v.append(n + 1 + np.arange(1999))
+        n += 2000
+    return _csr(n, u, v)
+
+
+def _path_and_stars():
+    """A path, the main component, and stars beside it, whose hubs are the
+    vertices of highest degree."""
+    u, v, n = [np.arange(11999)], [np.arange(1, 12000)], 12000
+    for _ in range(10):
+        u.append(np.full(99, n))
+        v.append(n + 1 + np.arange(99))
+        n += 100
+    return _csr(n, u, v)
+
+
+# past LDS: the trees as deep as the graph's diameter, in its main component or
+# beside it, above and below 20,000 in n + m / 2, with and without a component
+# of more than 1,024 vertices
+PAST_LDS = {
+    "ladder": lambda: _ladder(5500), "cycle": lambda: synth.cycle_graph(13000, (0,)),
+    "paths": lambda: _paths(20, 1000), "star_and_paths": _star_and_paths,
+    "path_and_stars": _path_and_stars, "ring": lambda: _ring(12000, 6),
+}
+SHALLOW = {
+    "er": lambda: synth.erdos_renyi_connected(11000, 30000, 0.8, 3),
+    "stars": lambda: _csr(20000, [np.repeat(np.arange(0, 20000, 500), 499)],
+                          [np.setdiff1d(np.arange(20000), np.arange(0, 20000, 500))]),
+}
+
+
+def _multi_passes(G, K):
+    """Records of the multi-tree kernel's phase log over a sweep (0: another ran)."""
+    log = G.phase_log(2048)
+    G.cloud_reset()
+    sw = G.sweep_range(0, K, 29, tree_switches=True).cpu().numpy().astype(np.uint64)
+    records = int(log[0])
+    G.phase_log(0)
+    return records, sw
+
+
+@pytest.mark.parametrize("name", [*PAST_LDS, *SHALLOW])
+def test_deep_graphs_past_lds_keep_off_the_grid_barriers(name):
+    deep = name in PAST_LDS
+    g = (PAST_LDS if deep else SHALLOW)[name]()
+    K = 40
+    ref = oracle.sweep(g, 29, 0, K, checks=False)
+    G = fr.Graph(g.row_ptr, g.col, g.sign, cloud_capacity=K)
+    records, sw = _multi_passes(G, K)
+    assert (records == 0) == deep
+    assert np.array_equal(sw, ref.trees[:, 0])
+    assert np.array_equal(G.cloud(), ref.cloud)
+    G.close()
