@@ -35,6 +35,7 @@ constexpr int kRootTasks = 4096;              // that leaves less than this many
 constexpr int32_t kInvertMin = 1 << 17;       // main components from this size invert the key
 constexpr int kCentBatch = 8;                 // BFS levels launched per look at their flags
 constexpr int kInvPerLane = 4;                // candidate keys per lane and step
+constexpr int32_t kCentDeepVertices = 65536;  // a deep main component below this keeps tree order
 constexpr int32_t kCentWide = 256;            // rows longer than this take a wave each
 
 // Inverse of an odd a mod 2^32 by Newton's iteration x <- x (2 - a x): a is
@@ -362,8 +363,12 @@ int centrality_setup(fi_graph* g, hipStream_t s) {
       grows = grows && grew[k];
       if (grows) ++g->levels;
     }
-    // up to kDeepWork such a graph is swept one tree per workgroup, in any order
-    if (g->levels > deep_levels(g, kDeepManyTrees) && small) return FI_OK;
+    // up to kDeepWork such a graph is swept one tree per workgroup, in any order;
+    // beyond, a long BFS pays on large components only (a ring of 60,000 with
+    // four neighbours on either side: 7,500 levels, 74 ms of an upload's 80)
+    if (small ? g->levels > deep_levels(g, kDeepManyTrees)
+              : g->levels > kDeepLevels && g->main_end - g->main_begin < kCentDeepVertices)
+      return FI_OK;
   }
   if (hipGetLastError() != hipSuccess) return FI_EDEVICE;
   g->cent = main;

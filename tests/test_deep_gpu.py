@@ -1,5 +1,7 @@
 """Deep graphs: trees of many levels, of which each holds little, in LDS and
 beyond, alone and in a batch, against the oracle."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -213,3 +215,21 @@ def test_deep_graphs_past_lds_keep_off_the_grid_barriers(name):
     assert np.array_equal(sw, ref.trees[:, 0])
     assert np.array_equal(G.cloud(), ref.cloud)
     G.close()
+
+
+def test_a_deep_graph_uploads_without_its_whole_bfs():
+    # past 135,000 in n + m / 2, where levels are counted for the tree order only,
+    # that is made from 65,536 vertices on
+    def ms(g):
+        arrays = [torch.from_numpy(np.ascontiguousarray(x)).cuda() for x in (g.row_ptr, g.col, g.sign)]
+        best = float("inf")
+        for _ in range(4):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            G = fr.Graph(*arrays, cloud_capacity=16)
+            torch.cuda.synchronize()
+            best = min(best, 1e3 * (time.perf_counter() - t))
+            G.close()
+        return best
+
+    assert ms(_ring(60000, 4)) <= ms(_ring(70000, 4)) / 4
