@@ -30,15 +30,19 @@ using wg::amin64;
 // a neighbour's row bounds come with its entry (links).  A hub is scanned again
 // at every return to it, with eight loads per lane in flight.  Backing up looks
 // at four stack entries at a time, and the search ends with the last vertex
-// instead of unwinding.  1,000 trees of n = 1,000, m = 5,000: 0.46 ms, that is
-// 0.46 us a vertex (a workgroup per tree, its waves but one idle: 0.97);
-// 4,000 / 16,000: 2.2 ms (7.6); 500 trees of 20,000 / 100,000: 15.7 (36.7).
+// instead of unwinding.  Components are chains of their own, so while a CU has
+// few trees, a tree's components go to several waves.  1,000 trees of n = 1,000,
+// m = 5,000: 0.46 ms, that is 0.46 us a vertex (a workgroup per tree, its waves
+// but one idle: 0.97); 4,000 / 16,000: 2.2 ms (7.6); 500 trees of 20,000 /
+// 100,000: 15.7 (36.7).
 struct RdfsArgs {
   const int32_t* cptr;    // [components + 1] ranges of cverts
   const int32_t* cverts;  // vertices by component
   const uint2* links;     // [nnz] entries with their neighbour's row, or null
   char* slots;            // per resident wave, what does not fit LDS
   size_t slot_stride;
+  int share;              // waves to a tree, a power of two
+  uint32_t cus;
 };
 
 // 32-bit words of a wave's marks: two bits per vertex, visited and state.
@@ -46,6 +50,7 @@ __host__ __device__ constexpr int32_t mark_words(int32_t n) { return (n + 15) / 
 // and of its stack in LDS, of 16-bit vertices (so up to kStackMaxN of them)
 __host__ __device__ constexpr int32_t stack_words(int32_t n) { return (n + 1) / 2; }
 constexpr int32_t kStackMaxN = 1 << 16;
+constexpr size_t kRdfsStatic = 64;  // LDS bytes beside the trees'
 constexpr int kRdfsBatch = 8;  // loads of a long row in flight per lane
 
 // An adjacency entry together with its neighbour's row: x = vertex | its
@@ -76,12 +81,19 @@ __device__ __forceinline__ uint32_t least_key(uint32_t x, bool few) {
 }
 
 // CSR: the graph's row offsets and adjacency in LDS, once per workgroup; LINKS
-// (without CSR): entries read with their neighbour's row; STK: the wave's stack
-// in LDS; MARKS: its marks in LDS.
-template <bool CSR, bool LINKS, bool STK, bool MARKS>
+// (without CSR): entries read with their neighbour's row; STK: the tree's stack
+// in LDS; MARKS: its marks in LDS; SHARED (with MARKS): R.share waves to a tree.
+template <bool CSR, bool LINKS, bool STK, bool MARKS, bool SHARED>
 __global__ void __launch_bounds__(1024) k_sweep_rdfs(DevGraph G, SweepArgs A, RdfsArgs R) {
   extern __shared__ uint32_t sm[];
+  __shared__ uint32_t s_next[kRdfsStatic / 4];  // per tree of the workgroup: components handed out
+  // the wave's tree among the workgroup's `ntree`, and which of the tree's waves
+  // it is: the first takes the first component, mostly the longest, so those of
+  // the trees on a CU lie on different SIMDs
   const int lane = lane_id(), wave = threadIdx.x >> 6, nwv = blockDim.x >> 6;
+  const int share = SHARED ? R.share : 1, ntree = SHARED ? nwv / share : nwv;
+  const int tree = SHARED ? wave % ntree : wave;
+  const int part = SHARED ? (int)(wave / ntree + blockIdx.x / R.cus) % share : 0;
   const int32_t n = G.n, mw = mark_words(n);
   const int32_t* rp = G.row_ptr;
   const uint32_t* adj = G.adj;
@@ -94,11 +106,11 @@ __global__ void __launch_bounds__(1024) k_sweep_rdfs(DevGraph G, SweepArgs A, Rd
     at += n + 1 + G.nnz;
     __syncthreads();
   }
-  char* slot = R.slots + ((size_t)blockIdx.x * nwv + wave) * R.slot_stride;
+  char* slot = R.slots + ((size_t)blockIdx.x * ntree + tree) * R.slot_stride;
   uint32_t* mark;
   std::conditional_t<STK, uint16_t, int32_t>* stk;
   {
-    uint32_t* mine = at + (size_t)wave * ((MARKS ? mw : 0) + (STK ? stack_words(n) : 0));
+    uint32_t* mine = at + (size_t)tree * ((MARKS ? mw : 0) + (STK ? stack_words(n) : 0));
     if constexpr (MARKS) mark = mine;
     else mark = (uint32_t*)slot;
     if constexpr (STK) stk = (uint16_t*)(mine + (MARKS ? mw : 0));
@@ -119,15 +131,30 @@ __global__ void __launch_bounds__(1024) k_sweep_rdfs(DevGraph G, SweepArgs A, Rd
   };
   const int32_t ncomp = (int32_t)G.ctl[C_NANCH];
 
-  for (uint64_t t = A.t0 + (uint64_t)wave * gridDim.x + blockIdx.x; t < A.t1;
-       t += (uint64_t)nwv * gridDim.x) {
+  // between the waves of a tree (the trees of a workgroup go in step then)
+  auto together = [&] {
+    if constexpr (SHARED) __syncthreads();
+    else order(MARKS);
+  };
+  for (uint64_t t0 = A.t0 + blockIdx.x; t0 < A.t1; t0 += (uint64_t)ntree * gridDim.x) {
+    const uint64_t t = t0 + (uint64_t)tree * gridDim.x;
     const uint64_t salt = tree_salt(A.seed, t);
-    if (A.sampler == kSamplerHybrid && !wg::hybrid_coin(salt)) continue;  // a BFS tree
+    // (the hybrid's other trees are BFS)
+    const bool live = t < A.t1 && (A.sampler != kSamplerHybrid || wg::hybrid_coin(salt));
+    if (!SHARED && !live) continue;
     const KeyMix km = key_mix(salt);
-    for (int32_t i = lane; i < mw; i += 64) mark[i] = 0;
-    order(MARKS);
-    for (int32_t k = 0; k < ncomp; ++k) {
+    for (int32_t i = part * 64 + lane; i < mw; i += 64 * share) mark[i] = 0;
+    if (SHARED && part == 0 && lane == 0) s_next[tree] = (uint32_t)share;
+    together();
+    auto next = [&](int32_t k) {  // the wave's component after the k-th
+      if constexpr (!SHARED) return k + 1;
+      uint32_t x = 0;
+      if (lane == 0) x = atomicAdd(&s_next[tree], 1u);
+      return __builtin_amdgcn_readfirstlane((int)x);
+    };
+    for (int32_t k = live ? __builtin_amdgcn_readfirstlane(part) : ncomp; k < ncomp; k = next(k)) {
       const int32_t b = R.cptr[k], e = R.cptr[k + 1];
+      auto* stack = SHARED ? stk + b : stk;  // a component's part of it
       // the component's minimum-key vertex
       uint32_t bk = ~0u;
       int32_t bv = -1;
@@ -148,7 +175,7 @@ __global__ void __launch_bounds__(1024) k_sweep_rdfs(DevGraph G, SweepArgs A, Rd
       int32_t top = 0, left = e - b - 1;
       if (lane == 0) {
         visit(u, 0);
-        stk[0] = (std::remove_reference_t<decltype(*stk)>)u;
+        stack[0] = (std::remove_reference_t<decltype(*stk)>)u;
       }
       order(MARKS);
       while (left > 0) {
@@ -226,7 +253,7 @@ __global__ void __launch_bounds__(1024) k_sweep_rdfs(DevGraph G, SweepArgs A, Rd
           --left;
           if (lane == 0) {
             visit(u, bu);
-            stk[top] = (std::remove_reference_t<decltype(*stk)>)u;
+            stack[top] = (std::remove_reference_t<decltype(*stk)>)u;
           }
           order(MARKS);
           continue;
@@ -238,7 +265,7 @@ __global__ void __launch_bounds__(1024) k_sweep_rdfs(DevGraph G, SweepArgs A, Rd
         const int grp = lane >> 4, sub = lane & 15;
         while (true) {
           const int32_t i = top - 1 - grp;
-          const int32_t w = i >= 0 ? (int32_t)stk[i] : 0;
+          const int32_t w = i >= 0 ? (int32_t)stack[i] : 0;
           const int32_t f0 = rp[w], dw = rp[w + 1] - f0;
           bool may = false;
           if (i >= 0) {
@@ -263,58 +290,71 @@ __global__ void __launch_bounds__(1024) k_sweep_rdfs(DevGraph G, SweepArgs A, Rd
       }
     }
 
-    // ---- canonical words, key terms and the exact count
-    uint64_t khi = 0, klo = 0, S = 0, mine = 0;
-    for (int32_t i = 0; i < G.nwords; ++i) {
-      const int32_t v = i * 64 + lane;
-      const uint64_t W = __ballot(v < n && (state(min(v, n - 1)) ^ state(G.comp[min(v, n - 1)])));
-      if (lane == (i & 63)) mine = W;
-      if (lane == 0 && A.bits_out) A.bits_out[i] = W;
-      if ((i & 63) == 63 || i + 1 == G.nwords) {  // a word per lane
-        const int32_t i0 = i & ~63;
-        if (i0 + lane <= i) key_terms((uint64_t)(i0 + lane), mine, khi, klo);
+    together();
+
+    // ---- canonical words, key terms and the exact count (its first wave)
+    if (part == 0 && live) {
+      uint64_t khi = 0, klo = 0, S = 0, mine = 0;
+      for (int32_t i = 0; i < G.nwords; ++i) {
+        const int32_t v = i * 64 + lane;
+        const uint64_t W = __ballot(v < n && (state(min(v, n - 1)) ^ state(G.comp[min(v, n - 1)])));
+        if (lane == (i & 63)) mine = W;
+        if (lane == 0 && A.bits_out) A.bits_out[i] = W;
+        if ((i & 63) == 63 || i + 1 == G.nwords) {  // a word per lane
+          const int32_t i0 = i & ~63;
+          if (i0 + lane <= i) key_terms((uint64_t)(i0 + lane), mine, khi, klo);
+        }
+      }
+      for (int64_t b0 = 0; b0 < G.m; b0 += 64 * kRdfsBatch) {
+        uint2 uv[kRdfsBatch];
+#pragma unroll
+        for (int q = 0; q < kRdfsBatch; ++q) {
+          const int64_t e = b0 + 64 * q + lane;
+          uv[q] = e < G.m ? G.edges[e] : make_uint2(0u, 0u);  // (0, 0) is never frustrated
+        }
+#pragma unroll
+        for (int q = 0; q < kRdfsBatch; ++q)
+          S += (uv[q].y >> 31) ^ state((int32_t)uv[q].x) ^ state((int32_t)(uv[q].y & kVertexMask));
+      }
+      S = wave_sum_u64(S);
+      khi = wave_sum_u64(khi);
+      klo = wave_sum_u64(klo);
+      if (lane == 0) {
+        if (A.insert) cloud_insert(G, khi, klo, S, t);
+        if (A.tree_switches) A.tree_switches[t - A.t0] = S;
       }
     }
-    for (int64_t b0 = 0; b0 < G.m; b0 += 64 * kRdfsBatch) {
-      uint2 uv[kRdfsBatch];
-#pragma unroll
-      for (int q = 0; q < kRdfsBatch; ++q) {
-        const int64_t e = b0 + 64 * q + lane;
-        uv[q] = e < G.m ? G.edges[e] : make_uint2(0u, 0u);  // (0, 0) is never frustrated
-      }
-#pragma unroll
-      for (int q = 0; q < kRdfsBatch; ++q)
-        S += (uv[q].y >> 31) ^ state((int32_t)uv[q].x) ^ state((int32_t)(uv[q].y & kVertexMask));
-    }
-    S = wave_sum_u64(S);
-    khi = wave_sum_u64(khi);
-    klo = wave_sum_u64(klo);
-    if (lane == 0) {
-      if (A.insert) cloud_insert(G, khi, klo, S, t);
-      if (A.tree_switches) A.tree_switches[t - A.t0] = S;
-    }
-    order(MARKS);
+    together();
   }
 }
 
-template <bool CSR, bool LINKS, bool STK, bool MARKS>
-hipError_t rdfs_launch(fi_graph* g, const SweepArgs& a, const RdfsArgs& r, int waves, size_t lds,
+template <bool CSR, bool LINKS, bool STK, bool MARKS, bool SHARED>
+hipError_t rdfs_run(fi_graph* g, const SweepArgs& a, const RdfsArgs& r, int trees_per_wg, size_t lds,
                        size_t slots, hipStream_t s) {
-  const void* f = (const void*)k_sweep_rdfs<CSR, LINKS, STK, MARKS>;
+  const int waves = trees_per_wg * r.share;
+  const void* f = (const void*)k_sweep_rdfs<CSR, LINKS, STK, MARKS, SHARED>;
   hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   int per_cu = 0;
-  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_sweep_rdfs<CSR, LINKS, STK, MARKS>,
+  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_sweep_rdfs<CSR, LINKS, STK, MARKS, SHARED>,
                                                    64 * waves, lds);
   if (e != hipSuccess) return e;
   int64_t grid = (int64_t)std::max(1, per_cu) * g->cu_count;
   if (g->sched.grid > 0) grid = std::min<int64_t>(grid, g->sched.grid);
-  if (!(STK && MARKS)) grid = std::min<int64_t>(grid, (int64_t)slots / waves);
+  if (!(STK && MARKS)) grid = std::min<int64_t>(grid, (int64_t)slots / trees_per_wg);
   const uint64_t trees = a.t1 - a.t0;
-  grid = std::min<int64_t>(grid, (int64_t)((trees + waves - 1) / waves));
-  hipLaunchKernelGGL((k_sweep_rdfs<CSR, LINKS, STK, MARKS>), dim3((unsigned)std::max<int64_t>(grid, 1)),
-                     dim3(64 * waves), lds, s, g->dg, a, r);
+  grid = std::min<int64_t>(grid, (int64_t)((trees + trees_per_wg - 1) / trees_per_wg));
+  hipLaunchKernelGGL((k_sweep_rdfs<CSR, LINKS, STK, MARKS, SHARED>),
+                     dim3((unsigned)std::max<int64_t>(grid, 1)), dim3(64 * waves), lds, s, g->dg, a, r);
   return hipGetLastError();
+}
+
+template <bool CSR, bool LINKS, bool STK, bool MARKS>
+hipError_t rdfs_launch(fi_graph* g, const SweepArgs& a, const RdfsArgs& r, int trees_per_wg, size_t lds,
+                       size_t slots, hipStream_t s) {
+  if constexpr (MARKS)
+    if (r.share > 1) return rdfs_run<CSR, LINKS, STK, MARKS, true>(g, a, r, trees_per_wg, lds, slots, s);
+  return rdfs_run<CSR, LINKS, STK, MARKS, false>(g, a, r, trees_per_wg, lds, slots, s);
 }
 
 // ------------------------------------------------------------ Kruskal
@@ -625,7 +665,8 @@ hipError_t launch_kruskal(fi_graph* g, const SweepArgs& a, int path, int nt, hip
 hipError_t launch_rdfs(fi_graph* g, const SweepArgs& a, int path, hipStream_t s) {
   const size_t n = (size_t)g->dg.n, marks = 4 * (size_t)mark_words(g->dg.n);
   const size_t stack = 4 * (size_t)stack_words(g->dg.n);
-  const size_t csr = 4 * (n + 1) + 4 * (size_t)g->dg.nnz, most = (size_t)g->max_shared;
+  const size_t csr = 4 * (n + 1) + 4 * (size_t)g->dg.nnz;
+  const size_t most = (size_t)g->max_shared - kRdfsStatic;
   RdfsArgs r{};
   r.cptr = (const int32_t*)(g->ws + g->L.cptr);
   r.cverts = (const int32_t*)(g->ws + g->L.cverts);
@@ -633,16 +674,22 @@ hipError_t launch_rdfs(fi_graph* g, const SweepArgs& a, int path, hipStream_t s)
   // waves that the trees of a CU want
   const uint64_t trees = a.t1 - a.t0, cus = (uint64_t)g->cu_count;
   const size_t want = (size_t)std::max<uint64_t>(1, std::min<uint64_t>(16, (trees + cus - 1) / cus));
+  const bool marks_lds = marks * want <= most;
+  // waves to a tree, while a CU has few trees and the components beside the main
+  // one take more than an eighth of its time (starting one costs about four steps)
+  const int64_t main = g->main_end - g->main_begin;
+  const int64_t beside = (int64_t)g->dg.n - g->nisolated - main + 4 * (int64_t)(g->nanch - 1);
+  r.share = 8 * beside <= main || !marks_lds ? 1 : want <= 4 ? 4 : want <= 8 ? 2 : 1;
+  r.cus = (uint32_t)cus;
   // the CSR in LDS while it leaves room for them
   if (csr + want * (marks + stack) <= most)
     return rdfs_launch<true, false, true, true>(g, a, r, (int)want, csr + want * (marks + stack), 0, s);
-  // else one wave per workgroup, with links: on path 1, whose sweeps may overlap
+  // else one tree per workgroup, with links: on path 1, whose sweeps may overlap
   // others of the handle, in a region of their own (every launch writes the same
   // bytes there); on path 2 in the slots' region, in front of the slots, where
   // they leave room for four waves per CU
   size_t region = g->L.slot_stride * g->L.nslots;
   const bool stk_lds = path == 1 || (g->dg.n <= kStackMaxN && (marks + stack) * want <= most);
-  const bool marks_lds = marks * want <= most;
   r.slot_stride = ((stk_lds ? 0 : 4 * n) + (stk_lds || marks_lds ? 0 : marks) + 255) & ~(size_t)255;
   const size_t links = (8 * (size_t)g->dg.nnz + 255) & ~(size_t)255;
   uint2* at = nullptr;
