@@ -250,6 +250,7 @@ void sort_entries(std::vector<fi_cloud_entry>& rows);  // by key
 constexpr int kGraphLMaxR = 64;
 constexpr int kGraphLBlocks = 2048;
 constexpr int kCountBlocks = 4096;  // workgroups of the exact count (max)
+constexpr int kCountDirect = 64;    // up to so many add to the counts themselves
 constexpr int kGLHeavy = 256;   // graphL rows longer than this are cut into items
 constexpr int kGLMid = 48;      // and rows longer than this take a wave each
 constexpr int kGLChunk = 1024;  // CSR entries per item of a long graphL row
@@ -273,7 +274,8 @@ hipError_t launch_multi(fi_graph* g, const SweepArgs& a, int words, hipStream_t 
 int multi_words(const fi_graph* g, uint64_t trees);
 // exact count of up to 64 states given as one word per vertex (bit b = the
 // vertex's state in state b, set = -1; uint32 words for up to 32 states,
-// else uint64): counts[b] = frustrated edges; part: room for kCountBlocks x 64 words
+// else uint64): counts[b], zero before, = frustrated edges; part: room for
+// kCountBlocks x 64 words
 hipError_t launch_count(const DevGraph& dg, const void* st, int32_t nstates, uint64_t* part,
                         uint64_t* counts, hipStream_t s);
 hipError_t graphl_setup(fi_graph* g, hipStream_t s);

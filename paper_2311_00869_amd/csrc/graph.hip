@@ -397,7 +397,8 @@ __global__ void k_cloud_load(DevGraph G, const uint64_t* e, int64_t count) {
 // and state sums the block, whose totals go to part[block][64] and are added
 // by k_count_final.  (One global atomic per block and state instead: the
 // 32,000 of 1,000 blocks on four lines were most of the kernel's 96 us on 4M
-// edges and 32 states, now 41.)
+// edges and 32 states, now 41.)  Up to kCountDirect blocks do add to counts by
+// atomics: a second launch would take 3 us of their 15 to 20.
 constexpr int kCountBlock = 256;
 constexpr int kCountPlanes = 8;
 constexpr int kCountEdges = 4;
@@ -405,7 +406,7 @@ constexpr int kCountEdges = 4;
 // gathered bytes), uint64_t for up to 64.
 template <typename T>
 __global__ void __launch_bounds__(kCountBlock) k_count(const uint2* edges, int64_t m, const T* st,
-                                                     int nstates, uint64_t* part) {
+                                                     int nstates, uint64_t* part, uint64_t* counts) {
   __shared__ uint64_t s_acc[64];
   const int lane = lane_id();
   if (threadIdx.x < 64) s_acc[threadIdx.x] = 0;
@@ -465,7 +466,11 @@ __global__ void __launch_bounds__(kCountBlock) k_count(const uint2* edges, int64
   flush();
   if (mine) atomicAdd((unsigned long long*)&s_acc[lane], (unsigned long long)mine);
   __syncthreads();
-  if (threadIdx.x < nstates) part[(size_t)blockIdx.x * 64 + threadIdx.x] = s_acc[threadIdx.x];
+  if (threadIdx.x < nstates) {
+    const uint64_t x = s_acc[threadIdx.x];
+    if (part) part[(size_t)blockIdx.x * 64 + threadIdx.x] = x;
+    else if (x) atomicAdd((unsigned long long*)(counts + threadIdx.x), (unsigned long long)x);
+  }
 }
 
 // counts[b] = the sum of state b's block totals (one block per state).
@@ -481,10 +486,12 @@ __global__ void __launch_bounds__(256) k_count_final(const uint64_t* part, int n
 // States given as bitmaps (state b: words bits[b * nwords + i], vertex v is
 // bit v % 64 of word v / 64) turned into one word per vertex: bit b of st[v]
 // is v's bit in state b, for b < nstates (<= 8 sizeof(T)).  The 64 lanes of
-// a wave share each bitmap word, so every word is read once.
+// a wave share each bitmap word, so every word is read once.  Also sets the
+// states' counts to zero.
 template <typename T>
 __global__ void k_states_by_vertex(const uint64_t* bits, int32_t nwords, int32_t n, int nstates,
-                                   T* st) {
+                                   T* st, uint64_t* counts) {
+  if (blockIdx.x == 0 && (int)threadIdx.x < nstates) counts[threadIdx.x] = 0;
   for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n;
        v += (int64_t)gridDim.x * blockDim.x) {
     const int64_t i = v >> 6;
@@ -1080,10 +1087,10 @@ int fi_count(fi_graph* g, const uint64_t* d_bits, int32_t B, uint64_t* d_counts,
     const uint64_t* bits = d_bits + (size_t)b0 * g->dg.nwords;
     if (nb <= 32)
       hipLaunchKernelGGL(k_states_by_vertex<uint32_t>, dim3(grid_for(n, 256, 65536)), dim3(256), 0, s,
-                         bits, g->dg.nwords, n, nb, (uint32_t*)st);
+                         bits, g->dg.nwords, n, nb, (uint32_t*)st, d_counts + b0);
     else
       hipLaunchKernelGGL(k_states_by_vertex<uint64_t>, dim3(grid_for(n, 256, 65536)), dim3(256), 0, s,
-                         bits, g->dg.nwords, n, nb, (uint64_t*)st);
+                         bits, g->dg.nwords, n, nb, (uint64_t*)st, d_counts + b0);
     hipError_t e = launch_count(g->dg, st, nb, (uint64_t*)(g->ws + g->L.cntpart), d_counts + b0, s);
     if (e != hipSuccess) return FI_EDEVICE;
   }
@@ -1180,15 +1187,17 @@ hipError_t launch_count(const DevGraph& dg, const void* st, int32_t nstates, uin
   // a few rounds of kCountEdges edges per lane (64M edges: 16 per lane)
   const int gx = dg.m == 0 ? 0
                            : grid_for((dg.m + kCountEdges - 1) / kCountEdges, kCountBlock, kCountBlocks);
+  uint64_t* sums = gx > kCountDirect ? part : nullptr;
   if (gx > 0) {
     if (nstates <= 32)
       hipLaunchKernelGGL(k_count<uint32_t>, dim3(gx), dim3(kCountBlock), 0, s, dg.cedges, dg.m,
-                         (const uint32_t*)st, (int)nstates, part);
+                         (const uint32_t*)st, (int)nstates, sums, counts);
     else
       hipLaunchKernelGGL(k_count<uint64_t>, dim3(gx), dim3(kCountBlock), 0, s, dg.cedges, dg.m,
-                         (const uint64_t*)st, (int)nstates, part);
+                         (const uint64_t*)st, (int)nstates, sums, counts);
   }
-  hipLaunchKernelGGL(k_count_final, dim3((unsigned)nstates), dim3(256), 0, s, part, gx, counts);
+  if (sums)
+    hipLaunchKernelGGL(k_count_final, dim3((unsigned)nstates), dim3(256), 0, s, part, gx, counts);
   return hipGetLastError();
 }
 

@@ -771,9 +771,10 @@ __global__ void k_fill_u32(uint32_t* p, int64_t len, uint32_t v) {
 // 32 restarts, else uint64_t).  When R divides 64 a wave reads 64
 // consecutive floats of Gamma (64 / R whole vertices) and one ballot gives
 // all their words, so Gamma streams through once, coalesced; otherwise each
-// thread reads its own vertex's R floats.
+// thread reads its own vertex's R floats.  Also sets the R counts to zero.
 template <typename T>
-__global__ void k_gl_round(const float* gamma, int32_t n, int R, T* st) {
+__global__ void k_gl_round(const float* gamma, int32_t n, int R, T* st, uint64_t* counts) {
+  if (blockIdx.x == 0 && (int)threadIdx.x < R) counts[threadIdx.x] = 0;
   const int lane = lane_id();
   const int64_t tid = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   const int64_t nthr = (int64_t)gridDim.x * blockDim.x;
@@ -815,7 +816,8 @@ __device__ __forceinline__ uint64_t spread4(uint64_t x) {
 // j's bits from them into its word.  Each wave takes two chunks per step, so
 // two 16-byte loads per lane are in flight.
 template <typename T>
-__global__ void k_gl_round4(const float4* gamma4, int32_t n, int R, T* st) {
+__global__ void k_gl_round4(const float4* gamma4, int32_t n, int R, T* st, uint64_t* counts) {
+  if (blockIdx.x == 0 && (int)threadIdx.x < R) counts[threadIdx.x] = 0;
   const int lane = lane_id();
   const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
   const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
@@ -1159,9 +1161,10 @@ int fi_round_count(fi_graph* g, const float* d_gamma, int32_t R, uint64_t* d_cou
                    uint64_t* d_bits_out, void* stream) {
   if (!g || g->is_batch || R < 1 || R > kGraphLMaxR || !d_counts) return FI_EINVAL;
   hipStream_t s = (hipStream_t)stream;
-  uint64_t* cpart = (uint64_t*)(g->ws + g->L.cntpart);
-  if (g->dg.n == 0)
-    return launch_count(g->dg, nullptr, R, cpart, d_counts, s) == hipSuccess ? FI_OK : FI_EDEVICE;
+  if (g->dg.n == 0) {
+    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(128), 0, s, (uint32_t*)d_counts, (int64_t)2 * R, 0u);
+    return hipGetLastError() == hipSuccess ? FI_OK : FI_EDEVICE;
+  }
   if (!d_gamma) return FI_EINVAL;
   void* tok = nullptr;
   if (prof_begin(g, s, &tok)) return FI_EDEVICE;
@@ -1176,25 +1179,25 @@ int fi_round_count(fi_graph* g, const float* d_gamma, int32_t R, uint64_t* d_cou
   if (R <= 32) {
     if (wide)
       hipLaunchKernelGGL(k_gl_round4<uint32_t>, dim3(wgrid), dim3(256), 0, s, (const float4*)d_gamma,
-                         g->dg.n, (int)R, (uint32_t*)st);
+                         g->dg.n, (int)R, (uint32_t*)st, d_counts);
     else
       hipLaunchKernelGGL(k_gl_round<uint32_t>, dim3(grid_for_gl(work, 256)), dim3(256), 0, s, d_gamma,
-                         g->dg.n, (int)R, (uint32_t*)st);
+                         g->dg.n, (int)R, (uint32_t*)st, d_counts);
     if (d_bits_out)
       hipLaunchKernelGGL(k_gl_unpack<uint32_t>, dim3(ugrid), dim3(256), 0, s, (const uint32_t*)st,
                          g->dg.n, g->dg.nwords, (int)R, d_bits_out);
   } else {
     if (wide)
       hipLaunchKernelGGL(k_gl_round4<uint64_t>, dim3(wgrid), dim3(256), 0, s, (const float4*)d_gamma,
-                         g->dg.n, (int)R, (uint64_t*)st);
+                         g->dg.n, (int)R, (uint64_t*)st, d_counts);
     else
       hipLaunchKernelGGL(k_gl_round<uint64_t>, dim3(grid_for_gl(work, 256)), dim3(256), 0, s, d_gamma,
-                         g->dg.n, (int)R, (uint64_t*)st);
+                         g->dg.n, (int)R, (uint64_t*)st, d_counts);
     if (d_bits_out)
       hipLaunchKernelGGL(k_gl_unpack<uint64_t>, dim3(ugrid), dim3(256), 0, s, (const uint64_t*)st,
                          g->dg.n, g->dg.nwords, (int)R, d_bits_out);
   }
-  hipError_t e = launch_count(g->dg, st, R, cpart, d_counts, s);
+  hipError_t e = launch_count(g->dg, st, R, (uint64_t*)(g->ws + g->L.cntpart), d_counts, s);
   prof_end(g, s, tok, 1);
   return e == hipSuccess ? FI_OK : FI_EDEVICE;
 }
