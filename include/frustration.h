@@ -289,8 +289,9 @@ int fi_round_count(fi_graph* g, const float* d_gamma, int32_t R, uint64_t* d_cou
  * for bad offsets, sizes or row_ptr, the fi_graph_create codes for a graph
  * that breaks the contract, FI_EWORKSPACE for a short workspace.  The handle
  * serves fi_batch_sweep, fi_graph_status, fi_set_schedule (path 0, 1 or 4,
- * block and grid; path 0 chooses the path and the block), fi_get_schedule, fi_prof_enable / fi_prof_read and
- * fi_graph_destroy; the single-graph calls return FI_EINVAL on it. */
+ * block and grid; path 0 chooses the path, and the block if it is the default
+ * 256), fi_get_schedule, fi_prof_enable / fi_prof_read and fi_graph_destroy;
+ * the single-graph calls return FI_EINVAL on it. */
 int fi_batch_workspace_size(int32_t G, const int64_t* h_vertex_offsets, const int64_t* h_nnz_offsets,
                             int64_t cloud_capacity_per_graph, size_t* out_bytes);
 int fi_batch_create(int32_t G, const int64_t* h_vertex_offsets, const int64_t* h_nnz_offsets,

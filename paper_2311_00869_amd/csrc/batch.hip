@@ -767,6 +767,8 @@ void launch_mt_batch(fi_graph* h, const BatchMArgs& a, hipStream_t s) {
   hipLaunchKernelGGL((k_batch_multi<NT>), dim3((int)grid), dim3(NT), 0, s, a);
 }
 
+constexpr int32_t kDefaultBlock = 256;  // a batch handle's; on path 0 it stands for the choice made here
+
 // How a batch's trees are laid on the GPU: path 4, up to 64 trees of a graph
 // per workgroup, or path 1, one tree per workgroup.
 struct BatchPlan {
@@ -803,6 +805,7 @@ BatchPlan plan_batch(const fi_graph* h, int64_t trees) {
     p.block = p.multi ? 1024
               : n > 7500 || all <= cus ? 1024
               : (n <= 1024 && all > 6 * cus) || (n <= 2048 && all > 16 * cus) ? 256 : 512;
+    if (h->sched.block != kDefaultBlock) p.block = h->sched.block;  // the caller's
     // few graphs: their trees are cut into smaller groups, down to eight, until
     // every CU has one
     while (p.multi && (int64_t)bi->G * p.groups * 2 <= h->cu_count && p.per > 8) {
@@ -939,7 +942,7 @@ int fi_batch_create(int32_t G, const int64_t* h_vertex_offsets, const int64_t* h
   bi->L = L;
   h->ws = ws;
   h->ws_bytes = ws_bytes;
-  h->sched = fi_schedule{0, 256, 0, 512, 1};
+  h->sched = fi_schedule{0, kDefaultBlock, 0, 512, 1};
   h->dg.ctl = (uint64_t*)(ws + L.ctl);
   h->prof_events = prof_events_new();
   if (!h->prof_events) return fail(FI_EINVAL);

@@ -691,8 +691,9 @@ class BatchGraph:
 
     def set_schedule(self, block=256, grid=0, path=0):
         """path 0: up to 64 trees of a graph per workgroup pass or one workgroup
-        per tree, by the graphs' sizes and the trees per graph (the block is
-        chosen too); 1: one workgroup per tree; 4: 64 trees per pass."""
+        per tree, by the graphs' sizes and the trees per graph (the default
+        block of 256 is then replaced too); 1: one workgroup per tree; 4: 64
+        trees per pass."""
         s = Schedule(path, block, grid, 512, 1)
         _check(self.lib.fi_set_schedule(self.handle, ctypes.byref(s)), "set_schedule")
 

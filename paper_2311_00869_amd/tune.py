@@ -105,7 +105,7 @@ def default_batch_schedule(batch):
     cache = _load()
     if _batch_key(batch) in cache:
         return dict(cache[_batch_key(batch)])
-    return dict(block=512, grid=0, path=0)
+    return dict(block=256, grid=0, path=0)  # the automatic schedule, block and all
 
 
 def autotune_batch(batch, trees: int = 64, seed: int = 12345, save: bool = True, verbose=False):
