@@ -156,6 +156,7 @@ struct RowArgs {
   int64_t ncr;              // C * R
   int32_t main_slot;        // the largest component: its maxima are combined per block
   int shift;                // rescale threshold and step, log2
+  int nan_counts;           // a NaN is above every threshold in the main component too
 };
 
 __device__ __forceinline__ float pair_scale(const RowArgs& A, int32_t c, int R, int sub) {
@@ -172,7 +173,8 @@ __device__ __forceinline__ void note_row(const RowArgs& A, int64_t i, int32_t c,
   if (c < 0) return;
   const float a = fabsf(v);
   if (c == A.main_slot) mx_main = fmaxf(mx_main, a);
-  else atomicMax((unsigned int*)&A.max_out[(size_t)c * R + sub], __float_as_uint(a));
+  if (c != A.main_slot || (A.nan_counts && a != a))
+    atomicMax((unsigned int*)&A.max_out[(size_t)c * R + sub], __float_as_uint(a));
   if (A.comp[i] == i && sc != 1.0f) A.exps[(size_t)c * R + sub] += A.shift;
 }
 
@@ -530,7 +532,7 @@ __global__ void __launch_bounds__(1024) k_gl_plan(const int32_t* rp, const int32
 // a multiply-add.  The leading entries of a row sit in registers, missing ones
 // point at a zero, and rows are dealt by length so that a wave's are alike.
 // The overflow policy compares a component's maximum with one threshold, so a
-// value that reaches it sets a flag.  500 steps at R = 32, us: 1,000 vertices,
+// value that reaches it sets a flag (a NaN does not in component no_nan).  500 steps at R = 32, us: 1,000 vertices,
 // 5,000 edges 475 (the row's entries decoded in every step, the CSR in LDS: 755),
 // 300 / 1,200 262 (485), 4,096 / 12,000 1,180 (2,425); with hubs, 1,000 / 5,000
 // 3,420 (a launch per step: 6,930).
@@ -557,8 +559,8 @@ __global__ void __launch_bounds__(1024) k_gl_descend_small(const int32_t* rp, co
                                                            const int32_t* aslot, int32_t n,
                                                            int32_t ncomp, int32_t nheavy, int groups, int R,
                                                            float alpha, int64_t steps, int shift,
-                                                           const float* start, float* gamma,
-                                                           int32_t* exps) {
+                                                           int32_t no_nan, const float* start,
+                                                           float* gamma, int32_t* exps) {
   constexpr int H = held_entries(Q), kBatch = Q == 4 ? 4 : 8, kTail = 8;
   constexpr uint32_t kCol = (uint32_t)small_column(Q), kZero = 8 * 1024 * Q;
   extern __shared__ uint32_t sm[];
@@ -679,7 +681,7 @@ __global__ void __launch_bounds__(1024) k_gl_descend_small(const int32_t* rp, co
         own[q] = v;
         *(float2*)(gout + 8 * row[q]) = make_float2(v, -v);
         if (sc != 1.0f && ra[q]) ex[c] += shift;
-        if (c >= 0 && __float_as_uint(fabsf(v)) >= thresh) mout[c] = 1u;
+        if (c >= 0 && __float_as_uint(fabsf(v)) >= thresh && (c != no_nan || v == v)) mout[c] = 1u;
       }
     }
     for (int32_t h = tid >> 6; h < nheavy; h += 16) {
@@ -713,7 +715,7 @@ __global__ void __launch_bounds__(1024) k_gl_descend_small(const int32_t* rp, co
         const float v = *(const float*)(gin + 8 * w.row) * sc - alpha * g;
         *(float2*)(gout + 8 * w.row) = make_float2(v, -v);
         if (sc != 1.0f && comp[w.row] == w.row) ex[w.slot] += shift;
-        if (__float_as_uint(fabsf(v)) >= thresh) mout[w.slot] = 1u;
+        if (__float_as_uint(fabsf(v)) >= thresh && (w.slot != no_nan || v == v)) mout[w.slot] = 1u;
       }
     }
     k3 = k3 == 2 ? 0 : k3 + 1;
@@ -1067,7 +1069,7 @@ hipError_t descend_small(fi_graph* g, int32_t ncomp, int groups, int32_t R, floa
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_gl_descend_small<Q>, dim3(R), dim3(1024), lds, s, g->dg.row_ptr, g->dg.adj,
                      g->dg.comp, (const int32_t*)(g->ws + g->L.aslot), g->dg.n, ncomp, g->gl_nheavy, groups, (int)R,
-                     alpha, steps, (int)shift, start, gamma, exps);
+                     alpha, steps, (int)shift, g->gl_nheavy ? g->gl_main_slot : -1, start, gamma, exps);
   return hipGetLastError();
 }
 
@@ -1121,6 +1123,7 @@ int descend(fi_graph* g, const float* start, float* d_gamma, float* d_work, int3
     A.ncr = (int64_t)std::max<int32_t>(g->nanch, 1) * R;
     A.main_slot = g->gl_main_slot;
     A.shift = rescale_log2;
+    A.nan_counts = g->dg.n <= kSmallDescentN && g->gl_nheavy == 0;
     if (launch_rows(g, in, R, A, outb, s) != hipSuccess) return FI_EDEVICE;
     in = outb;
   }
