@@ -136,23 +136,24 @@ __global__ void __launch_bounds__(1024) k_sweep_rdfs(DevGraph G, SweepArgs A, Rd
     if constexpr (SHARED) __syncthreads();
     else order(MARKS);
   };
-  for (uint64_t t0 = A.t0 + blockIdx.x; t0 < A.t1; t0 += (uint64_t)ntree * gridDim.x) {
-    const uint64_t t = t0 + (uint64_t)tree * gridDim.x;
+  const uint64_t first = A.t0 + (SHARED ? 0ull : (uint64_t)wave * gridDim.x) + blockIdx.x;
+  for (uint64_t t0 = first; t0 < A.t1; t0 += (uint64_t)ntree * gridDim.x) {
+    const uint64_t t = t0 + (SHARED ? (uint64_t)tree * gridDim.x : 0ull);
     const uint64_t salt = tree_salt(A.seed, t);
-    // (the hybrid's other trees are BFS)
-    const bool live = t < A.t1 && (A.sampler != kSamplerHybrid || wg::hybrid_coin(salt));
-    if (!SHARED && !live) continue;
+    const bool bfs = A.sampler == kSamplerHybrid && !wg::hybrid_coin(salt);  // another kernel's tree
+    if (!SHARED && bfs) continue;
+    const bool live = !SHARED || (t < A.t1 && !bfs);
     const KeyMix km = key_mix(salt);
     for (int32_t i = part * 64 + lane; i < mw; i += 64 * share) mark[i] = 0;
     if (SHARED && part == 0 && lane == 0) s_next[tree] = (uint32_t)share;
     together();
-    auto next = [&](int32_t k) {  // the wave's component after the k-th
-      if constexpr (!SHARED) return k + 1;
+    auto draw = [&] {  // the wave's next component
       uint32_t x = 0;
       if (lane == 0) x = atomicAdd(&s_next[tree], 1u);
       return __builtin_amdgcn_readfirstlane((int)x);
     };
-    for (int32_t k = live ? __builtin_amdgcn_readfirstlane(part) : ncomp; k < ncomp; k = next(k)) {
+    for (int32_t k = SHARED ? (live ? __builtin_amdgcn_readfirstlane(part) : ncomp) : 0; k < ncomp;
+         k = SHARED ? draw() : k + 1) {
       const int32_t b = R.cptr[k], e = R.cptr[k + 1];
       auto* stack = SHARED ? stk + b : stk;  // a component's part of it
       // the component's minimum-key vertex
