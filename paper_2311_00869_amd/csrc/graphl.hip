@@ -156,7 +156,6 @@ struct RowArgs {
   int64_t ncr;              // C * R
   int32_t main_slot;        // the largest component: its maxima are combined per block
   int shift;                // rescale threshold and step, log2
-  int nan_counts;           // a NaN is above every threshold in the main component too
 };
 
 __device__ __forceinline__ float pair_scale(const RowArgs& A, int32_t c, int R, int sub) {
@@ -167,13 +166,15 @@ __device__ __forceinline__ float pair_scale(const RowArgs& A, int32_t c, int R, 
 }
 
 // After a row's output v of restart `sub`: its component's maximum and, on
-// the component's anchor row, the scale.
+// the component's anchor row, the scale.  NAN_COUNTS: a NaN is above every
+// threshold in the main component too.
+template <bool NAN_COUNTS>
 __device__ __forceinline__ void note_row(const RowArgs& A, int64_t i, int32_t c, int R, int sub,
                                          float sc, float v, float& mx_main) {
   if (c < 0) return;
   const float a = fabsf(v);
   if (c == A.main_slot) mx_main = fmaxf(mx_main, a);
-  if (c != A.main_slot || (A.nan_counts && a != a))
+  if (c != A.main_slot || (NAN_COUNTS && a != a))
     atomicMax((unsigned int*)&A.max_out[(size_t)c * R + sub], __float_as_uint(a));
   if (A.comp[i] == i && sc != 1.0f) A.exps[(size_t)c * R + sub] += A.shift;
 }
@@ -304,7 +305,7 @@ __device__ __forceinline__ Lane<V> row_sum(const uint32_t* adj, int32_t e0, int3
 // entries on one group each, now 22, of 5,000 / 20,000 29 us, now 15.  SCALED keeps
 // the registers of the overflow policy out of gradients, four and five waves per
 // SIMD (200,000 / 2M at R = 64: 100 us; one kernel of 134 registers, three: 128).
-template <int P, int V, bool SCALED>
+template <int P, int V, bool SCALED, bool NAN_COUNTS>
 __global__ void __launch_bounds__(kGLBlock, P * V < 16 ? 1 : SCALED ? 4 : 5) k_gl_pass(const int32_t* rp, const uint32_t* adj,
                                                       int32_t n, GLPlan L, const float* gamma, int R,
                                                       RowArgs A, float* out) {
@@ -354,7 +355,7 @@ __global__ void __launch_bounds__(kGLBlock, P * V < 16 ? 1 : SCALED ? 4 : 5) k_g
     store_lane<V>(out + o, v);
     if constexpr (SCALED)
 #pragma unroll
-      for (int k = 0; k < V; ++k) note_row(A, i, c, R, r0 + k, sc.x[k], v.x[k], mx.x[k]);
+      for (int k = 0; k < V; ++k) note_row<NAN_COUNTS>(A, i, c, R, r0 + k, sc.x[k], v.x[k], mx.x[k]);
   };
 
   // long rows' items
@@ -478,7 +479,7 @@ __global__ void __launch_bounds__(kGLBlock) k_gl_combine(const int32_t* rp, cons
       const size_t o = (size_t)i * R + sub;
       const float v = A.update ? gamma[o] * sc - A.alpha * g : g;
       out[o] = v;
-      if (scaled) note_row(A, i, c, R, sub, sc, v, mx_main);
+      if (scaled) note_row<false>(A, i, c, R, sub, sc, v, mx_main);
     }
   }
   if (scaled) {
@@ -532,10 +533,10 @@ __global__ void __launch_bounds__(1024) k_gl_plan(const int32_t* rp, const int32
 // a multiply-add.  The leading entries of a row sit in registers, missing ones
 // point at a zero, and rows are dealt by length so that a wave's are alike.
 // The overflow policy compares a component's maximum with one threshold, so a
-// value that reaches it sets a flag (a NaN does not in component no_nan).  500 steps at R = 32, us: 1,000 vertices,
-// 5,000 edges 475 (the row's entries decoded in every step, the CSR in LDS: 755),
-// 300 / 1,200 262 (485), 4,096 / 12,000 1,180 (2,425); with hubs, 1,000 / 5,000
-// 3,420 (a launch per step: 6,930).
+// value that reaches it sets a flag.  500 steps at R = 32, us: 1,000 vertices,
+// 5,000 edges 457 (with long rows' code in the same kernel 475; the row's entries
+// decoded in every step, the CSR in LDS: 755), 300 / 1,200 262 (485), 4,096 /
+// 12,000 1,180 (2,425); with hubs, 1,000 / 5,000 3,420 (a launch per step: 6,930).
 constexpr int kSmallDescentN = 4096;
 constexpr size_t kSmallDescentLds = 152 * 1024;
 // Beyond, a restart's one CU takes longer than a launch per step (500 steps, us:
@@ -553,13 +554,14 @@ constexpr int held_entries(int q) { return q == 1 ? 32 : q == 2 ? 24 : 16; }
 // LDS bytes of the two columns: n pairs (value, negation), then a zero
 constexpr size_t small_column(int q) { return 8 * ((size_t)1024 * q + 1); }
 
-template <int Q>
+// LONG: with rows of more than kGLHeavy entries.
+template <int Q, bool LONG>
 __global__ void __launch_bounds__(1024) k_gl_descend_small(const int32_t* rp, const uint32_t* adj,
                                                            const int32_t* comp,
                                                            const int32_t* aslot, int32_t n,
                                                            int32_t ncomp, int32_t nheavy, int groups, int R,
                                                            float alpha, int64_t steps, int shift,
-                                                           int32_t no_nan, const float* start,
+                                                           int32_t main_slot, const float* start,
                                                            float* gamma, int32_t* exps) {
   constexpr int H = held_entries(Q), kBatch = Q == 4 ? 4 : 8, kTail = 8;
   constexpr uint32_t kCol = (uint32_t)small_column(Q), kZero = 8 * 1024 * Q;
@@ -681,10 +683,10 @@ __global__ void __launch_bounds__(1024) k_gl_descend_small(const int32_t* rp, co
         own[q] = v;
         *(float2*)(gout + 8 * row[q]) = make_float2(v, -v);
         if (sc != 1.0f && ra[q]) ex[c] += shift;
-        if (c >= 0 && __float_as_uint(fabsf(v)) >= thresh && (c != no_nan || v == v)) mout[c] = 1u;
+        if (c >= 0 && __float_as_uint(fabsf(v)) >= thresh && (!LONG || c != main_slot || v == v)) mout[c] = 1u;
       }
     }
-    for (int32_t h = tid >> 6; h < nheavy; h += 16) {
+    for (int32_t h = tid >> 6; LONG && h < nheavy; h += 16) {
       const SmallHeavy w = heavy[h];
       const float sc = min_[w.slot] ? down : 1.0f;
       float acc = 0.0f;
@@ -715,7 +717,7 @@ __global__ void __launch_bounds__(1024) k_gl_descend_small(const int32_t* rp, co
         const float v = *(const float*)(gin + 8 * w.row) * sc - alpha * g;
         *(float2*)(gout + 8 * w.row) = make_float2(v, -v);
         if (sc != 1.0f && comp[w.row] == w.row) ex[w.slot] += shift;
-        if (__float_as_uint(fabsf(v)) >= thresh && (w.slot != no_nan || v == v)) mout[w.slot] = 1u;
+        if (__float_as_uint(fabsf(v)) >= thresh && (w.slot != main_slot || v == v)) mout[w.slot] = 1u;
       }
     }
     k3 = k3 == 2 ? 0 : k3 + 1;
@@ -929,6 +931,9 @@ void with_lanes(int R, bool aligned, F f) {
   }
 }
 
+// A NaN counts for the scales in every component.
+bool nan_counts_all(const fi_graph* g) { return g->dg.n <= kSmallDescentN && g->gl_nheavy == 0; }
+
 hipError_t launch_rows(fi_graph* g, const float* gin, int R, const RowArgs& A, float* out,
                        hipStream_t s) {
   const Layout& L = g->L;
@@ -949,12 +954,11 @@ hipError_t launch_rows(fi_graph* g, const float* gin, int R, const RowArgs& A, f
     const int grid = (int)std::min<int64_t>(plan.nitems + mid + pass_grid(g->dg.n, P), kGLPassBlocks);
     plan.mid_at = plan.nitems % grid;
     plan.short_at = (plan.nitems + mid) % grid;
-    if (A.max_in)
-      hipLaunchKernelGGL((k_gl_pass<P, V, true>), dim3(grid), dim3(kGLBlock), 0, s, g->dg.row_ptr,
-                         g->dg.adj, g->dg.n, plan, gin, R, A, out);
-    else
-      hipLaunchKernelGGL((k_gl_pass<P, V, false>), dim3(grid), dim3(kGLBlock), 0, s, g->dg.row_ptr,
-                         g->dg.adj, g->dg.n, plan, gin, R, A, out);
+    const auto pass = !A.max_in           ? k_gl_pass<P, V, false, false>
+                      : nan_counts_all(g) ? k_gl_pass<P, V, true, true>
+                                          : k_gl_pass<P, V, true, false>;
+    hipLaunchKernelGGL(pass, dim3(grid), dim3(kGLBlock), 0, s, g->dg.row_ptr, g->dg.adj, g->dg.n, plan, gin,
+                       R, A, out);
   });
   if (g->gl_nheavy == 0) return hipGetLastError();
   const uint32_t nheavy = (uint32_t)g->gl_nheavy, rows_per_block = kGLBlock / lanes_for(R);
@@ -1064,12 +1068,12 @@ template <int Q>
 hipError_t descend_small(fi_graph* g, int32_t ncomp, int groups, int32_t R, float alpha, int64_t steps,
                          int32_t shift, const float* start, float* gamma, int32_t* exps, hipStream_t s) {
   const size_t lds = small_lds<Q>(g, ncomp);
-  const hipError_t e = hipFuncSetAttribute((const void*)k_gl_descend_small<Q>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  const auto f = g->gl_nheavy ? k_gl_descend_small<Q, true> : k_gl_descend_small<Q, false>;
+  const hipError_t e = hipFuncSetAttribute((const void*)f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_gl_descend_small<Q>, dim3(R), dim3(1024), lds, s, g->dg.row_ptr, g->dg.adj,
-                     g->dg.comp, (const int32_t*)(g->ws + g->L.aslot), g->dg.n, ncomp, g->gl_nheavy, groups, (int)R,
-                     alpha, steps, (int)shift, g->gl_nheavy ? g->gl_main_slot : -1, start, gamma, exps);
+  hipLaunchKernelGGL(f, dim3(R), dim3(1024), lds, s, g->dg.row_ptr, g->dg.adj, g->dg.comp,
+                     (const int32_t*)(g->ws + g->L.aslot), g->dg.n, ncomp, g->gl_nheavy, groups, (int)R, alpha,
+                     steps, (int)shift, g->gl_main_slot, start, gamma, exps);
   return hipGetLastError();
 }
 
@@ -1123,7 +1127,6 @@ int descend(fi_graph* g, const float* start, float* d_gamma, float* d_work, int3
     A.ncr = (int64_t)std::max<int32_t>(g->nanch, 1) * R;
     A.main_slot = g->gl_main_slot;
     A.shift = rescale_log2;
-    A.nan_counts = g->dg.n <= kSmallDescentN && g->gl_nheavy == 0;
     if (launch_rows(g, in, R, A, outb, s) != hipSuccess) return FI_EDEVICE;
     in = outb;
   }
