@@ -175,8 +175,9 @@ __device__ __forceinline__ void edges_trees(const DevGraph& G, const SweepArgs& 
       }
     }
     __syncthreads();
-    int32_t left = later;
-    for (uint32_t L = 0; left > 0; ++L) {
+    int32_t left = later, go = left;  // go: vertices left, or -1 of a deep tree
+    uint32_t L = 0;
+    for (; go > 0; ++L) {
       uint32_t mine = 0;
       edges([&](const uint32_t* x) {
         uint32_t lu[kEBatch], lv[kEBatch];
@@ -202,13 +203,10 @@ __device__ __forceinline__ void edges_trees(const DevGraph& G, const SweepArgs& 
       __syncthreads();
       const uint32_t f = sh.found[L % 3];
       if (tid == 0) sh.found[(L + 2) % 3] = 0;
-      if (f == 0) break;  // (no component runs out before its last vertex)
       left -= (int32_t)f;
-      if (L + 1 >= kEDeep && left > kEFew * (int32_t)f) {
-        deep_levels<NT>(G, km, L + 1, left, sh, pw, lev);
-        break;
-      }
+      go = L + 1 >= kEDeep && left > kEFew * (int32_t)f ? -1 : left;
     }
+    if (go < 0) deep_levels<NT>(G, km, L, left, sh, pw, lev);
 
     // the states in place of the levels
     for (int32_t v = tid; v < n; v += NT) lev[v] = (uint16_t)(pw[v] & 1);
