@@ -338,7 +338,7 @@ inline bool bfs_fits_lds(const fi_graph* g) {
 // 1,940 and 3,210 at 55 (66,000); from about one tree per CU on, one per workgroup
 // takes twice as long (1,000 of the 13,000: 1,180 and 1,650 at 27 levels, 3,630 and
 // 1,870 at 96).
-inline int64_t deep_levels(const fi_graph* g, uint64_t trees) {
+inline int64_t deep_line(const fi_graph* g, uint64_t trees) {
   const int64_t per = ((int64_t)g->dg.n + g->dg.m / 2) / kDeepPerLevel * (trees < kDeepManyTrees ? 1 : 2);
   return per < kDeepLevels ? per : kDeepLevels;
 }

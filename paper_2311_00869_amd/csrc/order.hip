@@ -366,7 +366,7 @@ int centrality_setup(fi_graph* g, hipStream_t s) {
     // up to kDeepWork such a graph is swept one tree per workgroup, in any order;
     // beyond, a long BFS pays on large components only (a ring of 60,000 with
     // four neighbours on either side: 7,500 levels, 74 ms of an upload's 80)
-    if (small ? g->levels > deep_levels(g, kDeepManyTrees)
+    if (small ? g->levels > deep_line(g, kDeepManyTrees)
               : g->levels > kDeepLevels && g->main_end - g->main_begin < kCentDeepVertices)
       return FI_OK;
   }

@@ -105,7 +105,7 @@ int pick_path(fi_graph* g, uint64_t trees, hipStream_t s) {
   // 222 and 224, 300 512 and 338), but on a deep graph it pays its barriers at
   // every level.
   const bool many = g->dg.m >= kMultiMinEdges && trees * (uint64_t)g->dg.m >= kMultiMinTreeEdges;
-  const bool plain = g->levels > deep_levels(g, trees) || ((fits ? many : work <= kDeepWork) && capturing(s));
+  const bool plain = g->levels > deep_line(g, trees) || ((fits ? many : work <= kDeepWork) && capturing(s));
   if (fits && (!many || plain)) return 1;
   // One tree per workgroup in workspace memory costs about m per tree (30,000
   // / 150,000: 1.5 ms for 100 trees, 7.3 ms for 1,000; the multi-tree path 0.4
