@@ -149,7 +149,7 @@ struct RowArgs {
   const int32_t* comp;      // anchor of each vertex's component
   const int32_t* aslot;     // component slot of each anchor
   const int32_t* anchors;   // anchor of each component slot
-  const uint32_t* max_in;   // [C][R] float bits of max |G_in|
+  const uint32_t* max_in;   // [C][R] float bits of max |G_in| (exact from the threshold on)
   uint32_t* max_out;        // [C][R] max |G_out| (atomic max)
   uint32_t* max_clear;      // [C][R] the buffer the step after next fills
   int32_t* exps;            // [C][R] log2 scales
@@ -158,11 +158,14 @@ struct RowArgs {
   int shift;                // rescale threshold and step, log2
 };
 
+__device__ __forceinline__ uint32_t scale_threshold(const RowArgs& A) {
+  return (uint32_t)(127 + A.shift) << 23;  // 2^shift
+}
 __device__ __forceinline__ float pair_scale(const RowArgs& A, int32_t c, int R, int sub) {
   if (c < 0) return 1.0f;
-  const uint32_t thresh = (uint32_t)(127 + A.shift) << 23;  // 2^shift
-  return A.max_in[(size_t)c * R + sub] >= thresh ? __uint_as_float((uint32_t)(127 - A.shift) << 23)
-                                                 : 1.0f;
+  return A.max_in[(size_t)c * R + sub] >= scale_threshold(A)
+             ? __uint_as_float((uint32_t)(127 - A.shift) << 23)
+             : 1.0f;
 }
 
 // After a row's output v of restart `sub`: its component's maximum and, on
@@ -174,7 +177,9 @@ __device__ __forceinline__ void note_row(const RowArgs& A, int64_t i, int32_t c,
   if (c < 0) return;
   const float a = fabsf(v);
   if (c == A.main_slot) mx_main = fmaxf(mx_main, a);
-  if (c != A.main_slot || (NAN_COUNTS && a != a))
+  // only whether the threshold is reached matters (20 rings of 1,000 at R = 64
+  // spent 120 of a step's 128 us on the maxima of values below it)
+  if ((c != A.main_slot || (NAN_COUNTS && a != a)) && __float_as_uint(a) >= scale_threshold(A))
     atomicMax((unsigned int*)&A.max_out[(size_t)c * R + sub], __float_as_uint(a));
   if (A.comp[i] == i && sc != 1.0f) A.exps[(size_t)c * R + sub] += A.shift;
 }
