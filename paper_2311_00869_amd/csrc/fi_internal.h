@@ -250,7 +250,7 @@ void sort_entries(std::vector<fi_cloud_entry>& rows);  // by key
 constexpr int kGraphLMaxR = 64;
 constexpr int kGraphLBlocks = 2048;
 constexpr int kCountBlocks = 4096;  // workgroups of the exact count (max)
-constexpr int kCountDirect = 64;    // up to so many add to the counts themselves
+constexpr int kCountDirect = 320;   // up to so many add to the counts themselves
 constexpr int kGLHeavy = 256;   // graphL rows longer than this are cut into items
 constexpr int kGLMid = 48;      // and rows longer than this take a wave each
 constexpr int kGLChunk = 1024;  // CSR entries per item of a long graphL row

@@ -398,7 +398,7 @@ __global__ void k_cloud_load(DevGraph G, const uint64_t* e, int64_t count) {
 // by k_count_final.  (One global atomic per block and state instead: the
 // 32,000 of 1,000 blocks on four lines were most of the kernel's 96 us on 4M
 // edges and 32 states, now 41.)  Up to kCountDirect blocks do add to counts by
-// atomics: a second launch would take 3 us of their 15 to 20.
+// atomics: a second launch takes 3 us, the atomics of 293 blocks 2 and of 782 5.
 constexpr int kCountBlock = 256;
 constexpr int kCountPlanes = 8;
 constexpr int kCountEdges = 4;
