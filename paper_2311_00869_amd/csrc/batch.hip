@@ -792,8 +792,23 @@ BatchPlan plan_batch(const fi_graph* h, int64_t trees) {
     // 2,770 and 3,600; 200 of up to 10,000 and 20 trees 2,820 and 840, 1,000 and 64
     // trees 5,700 and 11,400).
     const double walks = (double)trees * (double)bi->nnz_total;
-    const double t4 = 180.0 + 0.0125 * (double)bi->nnz_max + 1.2e-6 * walks;
-    const double t1 = 40.0 + (bi->n_max > kLdsMaxN ? 1.8e-5 : 3.2e-6) * walks;
+    double t4 = 180.0 + 0.0125 * (double)bi->nnz_max + 1.2e-6 * walks;
+    double t1 = 40.0 + (bi->n_max > kLdsMaxN ? 1.8e-5 : 3.2e-6) * walks;
+    int block4 = 1024;
+    // Graphs of a few hundred vertices: path 4 takes its items' levels, in rounds of
+    // as many as are resident, and narrow workgroups, eight to a CU, for graphs
+    // that leave wide ones idle or more items than those hold; path 1 a few ns for
+    // every tree (us, path 4 with 256 and 1,024 threads, path 1: 2,000 graphs of 20
+    // to 200 vertices, 16 trees 393, 711, 317, 64 trees 491, 880, 991; 1,000 of 100
+    // to 400, 64 trees 749, 589, 733, 128 trees 829, 1,089, 1,345; 3,000 of 100 to
+    // 300, 32 trees 813, 1,309, 934).
+    const double mean = (double)bi->nnz_total / bi->G, items = (double)bi->G * p.groups;
+    if (mean <= 4096.0) {
+      t1 += 4.5e-3 * (double)trees * bi->G;
+      if (mean <= 1536.0 || items > 4.0 * h->cu_count) block4 = 256;
+      const double level = block4 == 256 ? 250.0 + 0.05 * (double)bi->nnz_max : 180.0 + 0.0125 * (double)bi->nnz_max;
+      t4 = std::max(1.0, items / ((block4 == 256 ? 8.0 : 2.0) * h->cu_count)) * level + 0.7e-6 * walks;
+    }
     p.multi = trees >= 16 && t4 <= t1;
     // path 1: as many threads as a CU's registers hold in two workgroups, unless
     // LDS holds only one or the trees are few; small graphs' in four, from fewer
@@ -802,7 +817,7 @@ BatchPlan plan_batch(const fi_graph* h, int64_t trees) {
     // which take 100 levels, 367 and 565; 2,000 / 12,000 with 8 270 and 236)
     const int32_t n = bi->n_max_small;
     const int64_t all = trees * bi->G, cus = h->cu_count;
-    p.block = p.multi ? 1024
+    p.block = p.multi ? block4
               : n > 7500 || all <= cus ? 1024
               : (n <= 1024 && all > 6 * cus) || (n <= 2048 && all > 16 * cus) ? 256 : 512;
     if (h->sched.block != kDefaultBlock) p.block = h->sched.block;  // the caller's

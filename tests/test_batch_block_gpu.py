@@ -5,6 +5,7 @@ import ctypes
 import pytest
 import torch
 
+import oracle
 from paper_2311_00869_amd import synth, tune
 
 pytestmark = pytest.mark.gpu
@@ -53,4 +54,40 @@ def test_block_of_the_automatic_path(graphs, n_lo, n_hi, trees, auto):
     for default in (dict(), dict(block=256), tune.default_batch_schedule(B)):
         B.set_schedule(**default)
         assert _blocks(B, trees) == sorted([256, 256, auto]), default
+    B.close()
+
+
+# batches of small graphs: trees alone; 64 at a time in narrow workgroups, for
+# small graphs and for more of them than wide workgroups hold, and in wide ones
+@pytest.mark.parametrize("graphs,n_lo,n_hi,trees,block", [
+    (2000, 20, 200, 16, 256), (2000, 20, 200, 64, 256), (2000, 20, 200, 128, 256),
+    (1000, 100, 400, 64, 1024), (1000, 100, 400, 128, 256)])
+def test_automatic_block_of_small_graphs(graphs, n_lo, n_hi, trees, block):
+    gs = synth.config_batch(graphs, seed=6, n_lo=n_lo, n_hi=n_hi)
+    B = fr.BatchGraph(gs, cloud_capacity_per_graph=trees)
+    assert _blocks(B, trees) == sorted([256, 256, block])
+    mn, ds = (x.cpu().numpy() for x in B.sweep(trees, 3))
+    for i in range(0, graphs, graphs // 5):
+        r = oracle.sweep(gs[i], 3, 0, trees, checks=False)
+        assert tuple(mn[i]) == r.best and ds[i] == len(r.cloud), i
+    B.close()
+
+
+def test_automatic_block_is_the_best_of_64_trees_at_a_time():
+    B = fr.BatchGraph(synth.config_batch(2000, seed=6, n_lo=20, n_hi=200), cloud_capacity_per_graph=64)
+    mn = torch.empty((B.G, 2), dtype=torch.int64, device="cuda")
+
+    def ms(**schedule):
+        B.set_schedule(**schedule)
+        best = float("inf")
+        for _ in range(4):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            B.sweep_into(64, 5, mn)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+
+    assert ms(path=0) <= 1.2 * min(ms(path=4, block=block) for block in (256, 512, 1024))
     B.close()
