@@ -122,7 +122,11 @@ int fi_clean_no_alloc(int32_t n, int64_t E, const int32_t* d_src, const int32_t*
 
 /* Bytes of device workspace for a graph with n vertices, nnz CSR entries
  * (2 per undirected edge) and a cloud of up to cloud_capacity distinct
- * states.  Pure host arithmetic. */
+ * states.  Pure host arithmetic.  The largest parts: up to 8 GiB of slots for
+ * one tree per workgroup (n <= 1,000,000), about 100 bytes per vertex for each
+ * pass of the multi-tree schedule that can be in flight (eight up to 1M in
+ * n + m/2, four up to 8M, two up to 16M, else one), about 245 bytes per vertex
+ * and 17 per entry for the rest. */
 int fi_graph_workspace_size(int32_t n, int64_t nnz, int64_t cloud_capacity, size_t* out_bytes);
 
 /* Upload and validate a signed graph (blocks).
@@ -334,9 +338,10 @@ int fi_batch_cloud_read(fi_graph* b, int32_t graph, fi_cloud_entry* h_out, int64
  *      of the SplitMix64 finalizer of salt xor (u << 32 | v); ties go to the
  *      earlier edge of the sorted edge list; the tree is the unique minimum
  *      spanning forest (computed here by Boruvka rounds).
- * Samplers other than BFS run one tree per workgroup (Kruskal) or per wave
- * (the randomized DFS), whose threads `block` does not set (schedule paths 1 and
- * 2, whatever fi_set_schedule chose), so they need the tree in LDS (n up to
+ * Samplers other than BFS run one tree per workgroup (Kruskal) or per wave (the
+ * randomized DFS; up to four waves where it has several components), whose
+ * threads `block` does not set (schedule paths 1 and 2, whatever
+ * fi_set_schedule chose), so they need the tree in LDS (n up to
  * about 8,000 for Kruskal, 10,000 for DFS) or a workspace slot (n <= 10^6):
  * FI_ERANGE otherwise.  fi_sweep_stats takes BFS only (FI_EINVAL). */
 int fi_set_sampler(fi_graph* g, int32_t sampler);
@@ -449,13 +454,15 @@ int fi_bcloud_stats(fi_bcloud* c, int64_t* out_trees, int64_t* out_dropped, void
 /* ---------------------------------------------------------------- schedule */
 
 /* How a sweep is laid on the GPU.  Every schedule gives bit-identical
- * results; fi_set_schedule only changes speed.  path: 0 = automatic (from the
- * graph's size n + m/2 with m undirected edges, its BFS depth, the sampler and
- * the call's tree count: path 1 when the tree fits LDS and the trees are few
- * or the graph below 20,000, path 2 for deep graphs up to 135,000, else 4 or
- * 5; the block is chosen too, the block field is ignored, and a grid of 0 is
- * sized to the graph), 1 = one workgroup per tree with the tree state in LDS
- * (n <= 12,000), 2 = one workgroup per tree with the tree state in workspace memory
+ * results; fi_set_schedule only changes speed.  path: 0 = automatic: path 1
+ * when the tree fits LDS, unless the graph has 65,536 edges or more and edges
+ * times trees reach 80 million; path 2 for deep graphs of up to 135,000 in
+ * n + m/2 (m undirected edges; deep by the levels of a BFS against that size
+ * and the call's tree count, counted at upload) and for captured calls up to
+ * there; else 4 or 5, by size and tree count (the block is chosen too, the
+ * block field is ignored, and a grid of 0 is sized to the graph; samplers
+ * other than BFS take paths 1 and 2), 1 = one workgroup per tree with the tree
+ * state in LDS (n <= 10,922), 2 = one workgroup per tree with the tree state in workspace memory
  * (n <= 1,000,000), 3 = the whole grid on a few trees at a time
  * (persistent cooperative kernel, any n), 4 = passes of 64 trees at once with
  * one bit per tree in each field of a per-vertex record (cooperative, any n;

@@ -76,9 +76,7 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
 __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t x) {
   return wave_reduce<true>(x, [](uint64_t a, uint64_t b) { return a + b; });
 }
-// (LDS permutes here: the one hot caller, the randomized DFS step, shares its
-// kernel with the one-tree-per-workgroup BFS, which ran a quarter slower when
-// this minimum used DPP moves.)
+// (By LDS permutes; the whole-grid path takes it once per word of a root search.)
 __device__ __forceinline__ uint64_t wave_min_u64(uint64_t x) {
 #pragma unroll
   for (int d = 32; d > 0; d >>= 1) {

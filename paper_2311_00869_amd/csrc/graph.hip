@@ -584,7 +584,7 @@ constexpr int32_t kRootChunkSmall = 256;
 constexpr int32_t kRootWide = 2097152;
 
 // Sets of working state, so passes of the multi-tree path that can be in
-// flight at once (about 110 bytes per vertex each).  On graphs of 10^4 to 10^6
+// flight at once (about 100 bytes per vertex each).  On graphs of 10^4 to 10^6
 // vertices a pass leaves most of the chip waiting at its barriers and on its
 // longest rows; past about 16M in n + m/2 one pass keeps the memory busy alone
 // (plan_multi has the figures).
