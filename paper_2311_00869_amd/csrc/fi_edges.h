@@ -16,6 +16,10 @@
 // through a queue, lanes spread over the frontier's rows (deep_levels).  100 trees
 // of a 100 by 100 grid 195 us (over the edges to the end 496, through a queue alone
 // 409), of a ring of 10,000 with 10 neighbours on either side 539 (7,760, 1,039).
+// Edges past those in registers are read from memory at every level, so there the
+// queue takes over as soon as the levels shrink and its rows, by the mean degree,
+// are half of what the levels to come look at: 64 trees of 5,400 vertices of degree
+// 40 beside a ring of 167 177 us (at the seventh level 495, through a queue alone 319).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -176,6 +180,7 @@ __device__ __forceinline__ void edges_trees(const DevGraph& G, const SweepArgs& 
     }
     __syncthreads();
     int32_t left = later, go = left;  // go: vertices left, or -1 of a deep tree
+    int32_t last = 0;                 // vertices that the level before reached
     uint32_t L = 0;
     for (; go > 0; ++L) {
       uint32_t mine = 0;
@@ -204,7 +209,10 @@ __device__ __forceinline__ void edges_trees(const DevGraph& G, const SweepArgs& 
       const uint32_t f = sh.found[L % 3];
       if (tid == 0) sh.found[(L + 2) % 3] = 0;
       left -= (int32_t)f;
-      go = L + 1 >= kEDeep && left > kEFew * (int32_t)f ? -1 : left;
+      const bool few = m > kEHeld * NT && (int32_t)f < last &&
+                       4 * (int32_t)f * ((int32_t)f + left) < n * max((int32_t)f, left);
+      go = left > 0 && (few || (L + 1 >= kEDeep && left > kEFew * (int32_t)f)) ? -1 : left;
+      last = (int32_t)f;
     }
     if (go < 0) deep_levels<NT>(G, km, L, left, sh, pw, lev);
 
