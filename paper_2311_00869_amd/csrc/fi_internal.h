@@ -230,8 +230,9 @@ constexpr int kMSplit = 2048;     // rows longer than this are split into units 
 constexpr int64_t kMultiMinWork = 20000;
 constexpr int64_t kDeepWork = 135000;
 constexpr int32_t kDeepLevels = 64;   // deep whatever the work
-constexpr int32_t kDeepPerLevel = 1000;  // deep with less work than this per level,
-constexpr uint64_t kDeepManyTrees = 192;  // than half of it from so many trees
+// deep with less work than this per level and tree, among so few and so many trees
+constexpr int64_t kDeepPerLevel = 615000;
+constexpr uint64_t kDeepFewTrees = 400, kDeepManyTrees = 1000;
 constexpr int kMSets = 8;         // passes in flight on the multi-tree path (max)
 constexpr int kMCtlWords = 1024;  // control words of a pass
 constexpr int kBigComp = 1024;    // components larger than this find their roots in chunks
@@ -332,14 +333,17 @@ namespace fi {
 inline bool bfs_fits_lds(const fi_graph* g) {
   return 12 * (size_t)g->dg.n + 32768 <= (size_t)g->max_shared;
 }
-// The levels past which a graph is deep.  100 trees of 13,000 vertices take 567 us on
-// the multi-tree path and 683 one per workgroup at 17 levels (18,000 edges), 870
-// and 606 at 27 (a tree), of 30,000 1,560 and 1,550 at 46 (33,000 edges), of 60,000
-// 1,940 and 3,210 at 55 (66,000); from about one tree per CU on, one per workgroup
-// takes twice as long (1,000 of the 13,000: 1,180 and 1,650 at 27 levels, 3,630 and
-// 1,870 at 96).
+// The levels past which a graph is deep, by the edges and the vertices that have one.
+// 100 trees of 13,000 vertices take 567 us on the multi-tree path and 683 one per
+// workgroup at 17 levels (18,000 edges), 870 and 606 at 27 (a tree), of 18,000 with
+// 23,500 edges 634 and 580 at 30, of 30,000 1,560 and 1,550 at 46 (33,000 edges), of
+// 60,000 1,940 and 3,210 at 55 (66,000); where most vertices are alone, 13,200 with
+// 2,900 edges, 211 and 168 at 4.  With more trees than the CUs hold at once, one per
+// workgroup takes longer (the 18,000: 300 798 and 757, 1,000 971 and 1,509; 1,000 of
+// the 13,000: 1,180 and 1,650 at 27 levels, 3,630 and 1,870 at 96).
 inline int64_t deep_line(const fi_graph* g, uint64_t trees) {
-  const int64_t per = ((int64_t)g->dg.n + g->dg.m / 2) / kDeepPerLevel * (trees < kDeepManyTrees ? 1 : 2);
-  return per < kDeepLevels ? per : kDeepLevels;
+  const int64_t k = (int64_t)(trees < kDeepFewTrees ? kDeepFewTrees : trees < kDeepManyTrees ? trees : kDeepManyTrees);
+  const int64_t line = ((int64_t)g->dg.n - g->nisolated + g->dg.m) * k / kDeepPerLevel;
+  return line < kDeepLevels ? line : kDeepLevels;
 }
 }  // namespace fi
