@@ -1068,6 +1068,18 @@ size_t small_lds(const fi_graph* g, int32_t ncomp) {
   return 2 * small_column(Q) + 16 * ((size_t)ncomp + (size_t)g->gl_nheavy);
 }
 
+// Whether a step of the fused descent, whose waves add the long rows' items one
+// after the other, would take longer than launches of its own: per item 10.2 us
+// in 256 groups, 5.8 in 128, 3.6 in 64 and 32, 4.7 in 16, against about 11 us a
+// step (50 steps of stars, us: 2,360 vertices, R = 1 1,582 and 585, R = 8 880 and
+// 483, R = 32 505 and 551; 1,200, R = 2 521 and 473, R = 3 310 and 433; 4,000, R = 16
+// 724 and 497, R = 64 964 and 888).
+bool long_rows_wait(const fi_graph* g, int32_t R, int groups) {
+  if (g->gl_nheavy == 0) return false;
+  const double items = (double)g->gl_nitems / std::min(16, g->gl_nheavy);
+  return items * (0.04 * groups + 64.0 / groups) > 10.6 + 2.5e-5 * (double)R * g->dg.n;
+}
+
 // The fused descent, Q rows per thread (n <= 1024 Q).
 template <int Q>
 hipError_t descend_small(fi_graph* g, int32_t ncomp, int groups, int32_t R, float alpha, int64_t steps,
@@ -1103,12 +1115,12 @@ int descend(fi_graph* g, const float* start, float* d_gamma, float* d_work, int3
     FI_HIP(hipMemcpyAsync(d_gamma, start, bytes, hipMemcpyDeviceToDevice, s));
   if (g->dg.n == 0 || steps == 0) return hipGetLastError() == hipSuccess ? FI_OK : FI_EDEVICE;
   const int32_t ncomp = std::max<int32_t>(g->nanch, 1);
+  int groups = 0;
+  with_lanes(R, ((uintptr_t)start | (uintptr_t)d_gamma | (uintptr_t)d_work) % 16 == 0,
+             [&](auto p, auto) { groups = kGLBlock / decltype(p)::value; });
   if (g->dg.n <= kSmallDescentN && g->dg.nnz <= (g->gl_nheavy ? kSmallEntries / 2 : kSmallEntries) &&
-      small_lds<4>(g, ncomp) <= kSmallDescentLds) {
+      small_lds<4>(g, ncomp) <= kSmallDescentLds && !long_rows_wait(g, R, groups)) {
     const auto f = g->dg.n <= 1024 ? descend_small<1> : g->dg.n <= 2048 ? descend_small<2> : descend_small<4>;
-    int groups = 0;
-    with_lanes(R, ((uintptr_t)start | (uintptr_t)d_gamma | (uintptr_t)d_work) % 16 == 0,
-               [&](auto p, auto) { groups = kGLBlock / decltype(p)::value; });
     return f(g, ncomp, groups, R, alpha, steps, rescale_log2, start, d_gamma, (int32_t*)aux, s) == hipSuccess
                ? FI_OK
                : FI_EDEVICE;
