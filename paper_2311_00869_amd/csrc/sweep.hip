@@ -134,6 +134,9 @@ int auto_block(fi_graph* g, int path, uint64_t trees) {
   // (Kruskal's rounds on a few hundred edges are barriers: 64 trees of 50 vertices
   // 15.1 us with 256 threads, 16.8 with 1,024; of 300 25.8 and 23.5)
   if (g->sampler == kSamplerKruskal && g->dg.n <= 256) return 256;
+  // (BFS in less than the time of its barriers: one vertex 18.8 us with 256 threads,
+  // 19.6 with 1,024; 100 22.2 and 22.8, 200 23.3 and 23.3)
+  if (g->dg.n <= 128) return 256;
   const size_t lds = wg_lds_bytes(g->dg.n, g->sampler);
   if (lds > 65536 || trees <= (uint64_t)g->cu_count) return 1024;
   return lds <= 24576 && trees > 3 * (uint64_t)g->cu_count ? 256 : 512;
