@@ -269,7 +269,7 @@ hipError_t launch_grid(fi_graph* g, const SweepArgs& a, hipStream_t s);
 hipError_t launch_edges(fi_graph* g, const SweepArgs& a, int nt, hipStream_t s);
 hipError_t launch_kruskal(fi_graph* g, const SweepArgs& a, int path, int nt, hipStream_t s);
 bool kruskal_forest_fits(const fi_graph* g);  // a workgroup's forest in LDS
-hipError_t launch_rdfs(fi_graph* g, const SweepArgs& a, int path, hipStream_t s);
+hipError_t launch_rdfs(fi_graph* g, const SweepArgs& a, int path, bool* both, hipStream_t s);
 hipError_t launch_multi(fi_graph* g, const SweepArgs& a, int words, hipStream_t s);
 // words per vertex (1 or 2) of the automatic schedule's multi-tree pass over `trees` trees
 int multi_words(const fi_graph* g, uint64_t trees);

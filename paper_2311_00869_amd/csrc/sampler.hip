@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "fi_edges.h"
 #include "fi_internal.h"
 #include "fi_prims.h"
 #include "fi_wg.h"
@@ -45,6 +46,12 @@ struct RdfsArgs {
   size_t slot_stride;
   int share;              // waves to a tree, a power of two
   uint32_t cus;
+  // with the hybrid's BFS trees in the same launch:
+  int ntree;              // randomized DFS trees of a workgroup at a time
+  uint32_t dfs;           // workgroups of them, the first ones
+  int32_t later;          // BFS in LDS: vertices that are not a root and have an edge
+  char* bfs_slots;        // else per workgroup, words and queue
+  size_t bfs_stride;
 };
 
 // 32-bit words of a wave's marks: two bits per vertex, visited and state.
@@ -86,15 +93,39 @@ __device__ __forceinline__ uint32_t least_key(uint32_t x, bool few) {
 // CSR: the graph's row offsets and adjacency in LDS, once per workgroup; LINKS
 // (without CSR): entries read with their neighbour's row; STK: the tree's stack
 // in LDS; MARKS: its marks in LDS; SHARED (with MARKS): R.share waves to a tree.
-template <bool CSR, bool LINKS, bool STK, bool MARKS, bool SHARED>
-__global__ void __launch_bounds__(1024) k_sweep_rdfs(DevGraph G, SweepArgs A, RdfsArgs R) {
-  extern __shared__ uint32_t sm[];
+// BFS: the workgroups past R.dfs, all of kBothThreads threads, take the hybrid's
+// other trees, so that neither kind waits for the other (a path of 13,000, 100 trees
+// 32.7 ms in two launches, 27.3 here; of 2,000 2,020 us and 1,230; 50 / 100, 500 trees
+// 69 and 53).
+constexpr int kBothThreads = 256;
+enum : int { kNoBfs = 0, kBfsLds = 1, kBfsSlots = 2 };
+
+template <bool CSR, bool LINKS, bool STK, bool MARKS, bool SHARED, int BFS>
+__global__ void __launch_bounds__(BFS ? kBothThreads : 1024) k_sweep_rdfs(DevGraph G, SweepArgs A, RdfsArgs R) {
+  extern __shared__ __align__(16) uint32_t sm[];
+  if constexpr (BFS != kNoBfs) {
+    if (blockIdx.x >= R.dfs) {
+      const uint32_t b = blockIdx.x - R.dfs, step = gridDim.x - R.dfs;
+      if constexpr (BFS == kBfsLds) {
+        __shared__ wg::EShared<kBothThreads> sh;
+        wg::edges_trees<kBothThreads>(G, A, A.t0 + b, A.t1, step, R.later, sh, (uint64_t*)sm);
+      } else {
+        __shared__ wg::WgShared<kBothThreads> sh;
+        uint64_t* pw = (uint64_t*)(R.bfs_slots + (size_t)b * R.bfs_stride);
+        for (uint64_t t = A.t0 + b; t < A.t1; t += step)
+          if (!wg::hybrid_coin(tree_salt(A.seed, t)))
+            wg::wg_tree<kBothThreads>(G, A, t, pw, (int32_t*)(pw + G.n), sh);
+      }
+      return;
+    }
+  }
+  const uint32_t blocks = BFS ? R.dfs : gridDim.x;
   __shared__ uint32_t s_next[kRdfsStatic / 4];  // per tree of the workgroup: components handed out
   // the wave's tree among the workgroup's `ntree`, and which of the tree's waves
   // it is: the first takes the first component, mostly the longest, so those of
   // the trees on a CU lie on different SIMDs
   const int lane = lane_id(), wave = threadIdx.x >> 6, nwv = blockDim.x >> 6;
-  const int share = SHARED ? R.share : 1, ntree = SHARED ? nwv / share : nwv;
+  const int share = SHARED ? R.share : 1, ntree = SHARED ? nwv / share : BFS ? R.ntree : nwv;
   const int tree = SHARED ? wave % ntree : wave;
   const int part = SHARED ? (int)(wave / ntree + blockIdx.x / R.cus) % share : 0;
   const int32_t n = G.n, mw = mark_words(n);
@@ -109,6 +140,7 @@ __global__ void __launch_bounds__(1024) k_sweep_rdfs(DevGraph G, SweepArgs A, Rd
     at += n + 1 + G.nnz;
     __syncthreads();
   }
+  if (BFS && !SHARED && wave >= ntree) return;
   char* slot = R.slots + ((size_t)blockIdx.x * ntree + tree) * R.slot_stride;
   uint32_t* mark;
   std::conditional_t<STK, uint16_t, int32_t>* stk;
@@ -139,11 +171,11 @@ __global__ void __launch_bounds__(1024) k_sweep_rdfs(DevGraph G, SweepArgs A, Rd
     if constexpr (SHARED) __syncthreads();
     else order(MARKS);
   };
-  const uint64_t first = A.t0 + (SHARED ? 0ull : (uint64_t)wave * gridDim.x) + blockIdx.x;
-  for (uint64_t t0 = first; t0 < A.t1; t0 += (uint64_t)ntree * gridDim.x) {
-    const uint64_t t = t0 + (SHARED ? (uint64_t)tree * gridDim.x : 0ull);
+  const uint64_t first = A.t0 + (SHARED ? 0ull : (uint64_t)wave * blocks) + blockIdx.x;
+  for (uint64_t t0 = first; t0 < A.t1; t0 += (uint64_t)ntree * blocks) {
+    const uint64_t t = t0 + (SHARED ? (uint64_t)tree * blocks : 0ull);
     const uint64_t salt = tree_salt(A.seed, t);
-    const bool bfs = A.sampler == kSamplerHybrid && !wg::hybrid_coin(salt);  // another kernel's tree
+    const bool bfs = A.sampler == kSamplerHybrid && !wg::hybrid_coin(salt);  // not this kind
     if (!SHARED && bfs) continue;
     const bool live = !SHARED || (t < A.t1 && !bfs);
     const KeyMix km = key_mix(salt);
@@ -337,11 +369,11 @@ template <bool CSR, bool LINKS, bool STK, bool MARKS, bool SHARED>
 hipError_t rdfs_run(fi_graph* g, const SweepArgs& a, const RdfsArgs& r, int trees_per_wg, size_t lds,
                        size_t slots, hipStream_t s) {
   const int waves = trees_per_wg * r.share;
-  const void* f = (const void*)k_sweep_rdfs<CSR, LINKS, STK, MARKS, SHARED>;
+  const void* f = (const void*)k_sweep_rdfs<CSR, LINKS, STK, MARKS, SHARED, kNoBfs>;
   hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   int per_cu = 0;
-  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_sweep_rdfs<CSR, LINKS, STK, MARKS, SHARED>,
+  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_sweep_rdfs<CSR, LINKS, STK, MARKS, SHARED, kNoBfs>,
                                                    64 * waves, lds);
   if (e != hipSuccess) return e;
   int64_t grid = (int64_t)std::max(1, per_cu) * g->cu_count;
@@ -349,14 +381,68 @@ hipError_t rdfs_run(fi_graph* g, const SweepArgs& a, const RdfsArgs& r, int tree
   if (!(STK && MARKS)) grid = std::min<int64_t>(grid, (int64_t)slots / trees_per_wg);
   const uint64_t trees = a.t1 - a.t0;
   grid = std::min<int64_t>(grid, (int64_t)((trees + trees_per_wg - 1) / trees_per_wg));
-  hipLaunchKernelGGL((k_sweep_rdfs<CSR, LINKS, STK, MARKS, SHARED>),
+  hipLaunchKernelGGL((k_sweep_rdfs<CSR, LINKS, STK, MARKS, SHARED, kNoBfs>),
                      dim3((unsigned)std::max<int64_t>(grid, 1)), dim3(64 * waves), lds, s, g->dg, a, r);
   return hipGetLastError();
 }
 
+// Both kinds of the hybrid's trees in one launch, while its workgroups are resident
+// at once (half of those of one tree at a time find none); *both: whether it was made.
+template <bool CSR, bool LINKS, bool STK, bool MARKS, bool SHARED, int BFS>
+hipError_t both_run(fi_graph* g, const SweepArgs& a, RdfsArgs r, size_t lds, size_t region, bool* both,
+                    hipStream_t s) {
+  const auto f = k_sweep_rdfs<CSR, LINKS, STK, MARKS, SHARED, BFS>;
+  const size_t fixed =
+      kRdfsStatic + (BFS == kBfsLds ? sizeof(wg::EShared<kBothThreads>) : sizeof(wg::WgShared<kBothThreads>));
+  if (BFS == kBfsLds) lds = std::max(lds, 10 * (size_t)g->dg.n);
+  if (lds + fixed + 64 > (size_t)g->max_shared) return hipSuccess;
+  hipError_t e = hipFuncSetAttribute((const void*)f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  int per_cu = 0;
+  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, kBothThreads, lds);
+  if (e != hipSuccess) return e;
+  const uint64_t trees = a.t1 - a.t0, dfs = (trees + r.ntree - 1) / r.ntree;
+  if ((r.ntree == 1 ? dfs : 2 * dfs) + trees > 2 * (uint64_t)per_cu * g->cu_count) return hipSuccess;
+  const size_t used = STK && MARKS ? 0 : dfs * r.ntree * r.slot_stride;
+  uint64_t bfs = trees;
+  if (BFS == kBfsSlots) {
+    if (used > region || (region - used) / g->L.slot_stride < trees) return hipSuccess;
+    r.bfs_slots = r.slots + used;
+    r.bfs_stride = g->L.slot_stride;
+  } else if (used) {
+    return hipSuccess;
+  }
+  r.dfs = (uint32_t)dfs;
+  r.later = g->dg.n - g->nisolated - g->nanch;
+  hipLaunchKernelGGL(f, dim3((unsigned)(dfs + bfs)), dim3(kBothThreads), lds, s, g->dg, a, r);
+  *both = true;
+  return hipGetLastError();
+}
+
+// both: null, or where to say that the hybrid's BFS trees were launched with them
 template <bool CSR, bool LINKS, bool STK, bool MARKS>
-hipError_t rdfs_launch(fi_graph* g, const SweepArgs& a, const RdfsArgs& r, int trees_per_wg, size_t lds,
-                       size_t slots, hipStream_t s) {
+hipError_t rdfs_launch(fi_graph* g, const SweepArgs& a, const RdfsArgs& r, int path, int trees_per_wg, size_t lds,
+                       size_t region, bool* both, hipStream_t s) {
+  if constexpr (CSR || LINKS) {
+    if (both) {
+      constexpr int kWaves = kBothThreads / 64;
+      RdfsArgs b = r;
+      b.ntree = r.share > 1 ? kWaves / r.share : CSR ? std::min(kWaves, trees_per_wg) : 1;
+      const size_t tree = 4 * ((MARKS ? (size_t)mark_words(g->dg.n) : 0) + (STK ? (size_t)stack_words(g->dg.n) : 0));
+      const size_t blds = lds - tree * trees_per_wg + tree * b.ntree;
+      auto run = [&](auto kind) -> hipError_t {
+        constexpr int BFS = decltype(kind)::value;
+        if constexpr (MARKS)
+          if (r.share > 1) return both_run<CSR, LINKS, STK, MARKS, true, BFS>(g, a, b, blds, region, both, s);
+        return both_run<CSR, LINKS, STK, MARKS, false, BFS>(g, a, b, blds, region, both, s);
+      };
+      hipError_t e = hipSuccess;
+      if (path == 2) e = run(std::integral_constant<int, kBfsSlots>{});
+      else if constexpr (STK && MARKS) e = run(std::integral_constant<int, kBfsLds>{});
+      if (e != hipSuccess || *both) return e;
+    }
+  }
+  const size_t slots = r.slot_stride ? region / r.slot_stride : 0;
   if constexpr (MARKS)
     if (r.share > 1) return rdfs_run<CSR, LINKS, STK, MARKS, true>(g, a, r, trees_per_wg, lds, slots, s);
   return rdfs_run<CSR, LINKS, STK, MARKS, false>(g, a, r, trees_per_wg, lds, slots, s);
@@ -666,8 +752,9 @@ hipError_t launch_kruskal(fi_graph* g, const SweepArgs& a, int path, int nt, hip
 }
 
 // path 1: the trees in LDS; 2: what does not fit there, for as many waves as
-// the trees need, in workspace slots
-hipError_t launch_rdfs(fi_graph* g, const SweepArgs& a, int path, hipStream_t s) {
+// the trees need, in workspace slots.  both: null, or where to say whether the
+// hybrid's BFS trees were launched with them.
+hipError_t launch_rdfs(fi_graph* g, const SweepArgs& a, int path, bool* both, hipStream_t s) {
   const size_t n = (size_t)g->dg.n, marks = 4 * (size_t)mark_words(g->dg.n);
   const size_t stack = 4 * (size_t)stack_words(g->dg.n);
   const size_t csr = 4 * (n + 1) + 4 * (size_t)g->dg.nnz;
@@ -688,7 +775,8 @@ hipError_t launch_rdfs(fi_graph* g, const SweepArgs& a, int path, hipStream_t s)
   r.cus = (uint32_t)cus;
   // the CSR in LDS while it leaves room for them
   if (csr + want * (marks + stack) <= most)
-    return rdfs_launch<true, false, true, true>(g, a, r, (int)want, csr + want * (marks + stack), 0, s);
+    return rdfs_launch<true, false, true, true>(g, a, r, path, (int)want, csr + want * (marks + stack),
+                                                g->L.slot_stride * g->L.nslots, both, s);
   // else one tree per workgroup, with links: on path 1, whose sweeps may overlap
   // others of the handle, in a region of their own (every launch writes the same
   // bytes there); on path 2 in the slots' region, in front of the slots, where
@@ -710,15 +798,14 @@ hipError_t launch_rdfs(fi_graph* g, const SweepArgs& a, int path, hipStream_t s)
     hipLaunchKernelGGL(k_rdfs_links, dim3(grid), dim3(256), 0, s, g->dg.row_ptr, g->dg.adj, g->dg.nnz, at);
     r.links = at;
   }
-  const size_t slots = r.slot_stride ? region / r.slot_stride : 0;
   const size_t lds = (stk_lds ? stack : 0) + (stk_lds || marks_lds ? marks : 0);
   if (r.links)
-    return stk_lds    ? rdfs_launch<false, true, true, true>(g, a, r, 1, lds, slots, s)
-           : marks_lds ? rdfs_launch<false, true, false, true>(g, a, r, 1, lds, slots, s)
-                      : rdfs_launch<false, true, false, false>(g, a, r, 1, lds, slots, s);
-  return stk_lds    ? rdfs_launch<false, false, true, true>(g, a, r, 1, lds, slots, s)
-         : marks_lds ? rdfs_launch<false, false, false, true>(g, a, r, 1, lds, slots, s)
-                    : rdfs_launch<false, false, false, false>(g, a, r, 1, lds, slots, s);
+    return stk_lds    ? rdfs_launch<false, true, true, true>(g, a, r, path, 1, lds, region, both, s)
+           : marks_lds ? rdfs_launch<false, true, false, true>(g, a, r, path, 1, lds, region, both, s)
+                      : rdfs_launch<false, true, false, false>(g, a, r, path, 1, lds, region, both, s);
+  return stk_lds    ? rdfs_launch<false, false, true, true>(g, a, r, path, 1, lds, region, both, s)
+         : marks_lds ? rdfs_launch<false, false, false, true>(g, a, r, path, 1, lds, region, both, s)
+                    : rdfs_launch<false, false, false, false>(g, a, r, path, 1, lds, region, both, s);
 }
 
 }  // namespace fi

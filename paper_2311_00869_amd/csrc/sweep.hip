@@ -174,13 +174,19 @@ hipError_t launch_sweep(fi_graph* g, const SweepArgs& a, hipStream_t s) {
   } else if (a.sampler == kSamplerKruskal) {
     e = launch_kruskal(g, a, path, nt, s);
   } else if (a.sampler == kSamplerRdfs) {
-    e = launch_rdfs(g, a, path, s);
+    e = launch_rdfs(g, a, path, nullptr, s);
   } else {
-    e = path == 1   ? launch_edges(g, a, nt, s)
-        : nt == 1024 ? launch_wg<1024>(g, a, s)
-        : nt == 512  ? launch_wg<512>(g, a, s)
-                     : launch_wg<256>(g, a, s);
-    if (e == hipSuccess && a.sampler == kSamplerHybrid) e = launch_rdfs(g, a, path, s);
+    e = hipSuccess;
+    bool both = false;
+    if (a.sampler == kSamplerHybrid) {
+      const bool may = g->sched.grid == 0 && (g->sched.path == 0 || nt == 256);
+      e = launch_rdfs(g, a, path, may ? &both : nullptr, s);
+    }
+    if (e == hipSuccess && !both)
+      e = path == 1   ? launch_edges(g, a, nt, s)
+          : nt == 1024 ? launch_wg<1024>(g, a, s)
+          : nt == 512  ? launch_wg<512>(g, a, s)
+                       : launch_wg<256>(g, a, s);
   }
   prof_end(g, s, tok, 0);
   return e;
