@@ -302,6 +302,7 @@ struct fi_graph {
   int32_t mtasks, mnbig;  // multi-tree path: root-finding tasks, big components
   int32_t gl_nheavy;      // graphL rows longer than kGLHeavy (their items are planned at upload)
   int32_t gl_nitems;      // and their items
+  bool gl_longer;         // rows longer than the small descent's registers hold
   int32_t gl_nmid;        // rows longer than kGLMid, up to kGLHeavy
   int32_t sampler;        // kSampler*
   int32_t gl_main_slot;   // slot of the component with the most vertices (-1: none)

@@ -556,10 +556,14 @@ struct SmallHeavy {  // a long row
 
 // leading entries of a row in registers, for so many rows per thread
 constexpr int held_entries(int q) { return q == 1 ? 32 : q == 2 ? 24 : 16; }
+// rows per thread
+constexpr int small_rows(int32_t n) { return n <= 1024 ? 1 : n <= 2048 ? 2 : 4; }
 // LDS bytes of the two columns: n pairs (value, negation), then a zero
 constexpr size_t small_column(int q) { return 8 * ((size_t)1024 * q + 1); }
 
-// LONG: with rows of more than kGLHeavy entries.
+// LONG: with rows of more than H entries, and of more than kGLHeavy if there are
+// any (without that code in the same kernel those of H to kGLHeavy take longer: 500
+// steps of 1,413 vertices, 3,500 entries and rows of up to 148 2,346 us, here 1,815).
 template <int Q, bool LONG>
 __global__ void __launch_bounds__(1024) k_gl_descend_small(const int32_t* rp, const uint32_t* adj,
                                                            const int32_t* comp,
@@ -758,14 +762,15 @@ __global__ void k_gl_scales(const int32_t* rp, const int32_t* comp, const int32_
 }
 
 // Rows longer than kGLHeavy and rows longer than mid_len, in any order (each is
-// summed on its own).
-__global__ void k_gl_heavy_list(const int32_t* rp, int32_t n, int32_t mid_len, int32_t* list,
+// summed on its own), and whether any is longer than `held`.
+__global__ void k_gl_heavy_list(const int32_t* rp, int32_t n, int32_t mid_len, int32_t held, int32_t* list,
                                 int32_t* mid, uint32_t* ctl) {
   for (int64_t b = (int64_t)blockIdx.x * blockDim.x; b < n; b += (int64_t)gridDim.x * blockDim.x) {
     const int64_t i = b + threadIdx.x;
     const int32_t d = i < n ? rp[i + 1] - rp[i] : 0;
     wave_append(d > kGLHeavy, (int32_t)i, list, ctl);
     wave_append(d > mid_len && d <= kGLHeavy, (int32_t)i, mid, ctl + 2);
+    if (d > held) ctl[3] = 1;
   }
 }
 
@@ -982,20 +987,21 @@ hipError_t graphl_setup(fi_graph* g, hipStream_t s) {
   int32_t* first = (int32_t*)(g->ws + L.glfirst);
   int2* items = (int2*)(g->ws + L.glitems);
   uint32_t* ctl = gl_ctl(g);
-  hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s, ctl, (int64_t)3, 0u);
+  hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s, ctl, (int64_t)4, 0u);
   if (g->dg.n > 0) {
     const int grid =
         (int)std::max<int64_t>(1, std::min<int64_t>(((int64_t)g->dg.n + 255) / 256, 16384));
-    hipLaunchKernelGGL(k_gl_heavy_list, dim3(grid), dim3(256), 0, s, g->dg.row_ptr, g->dg.n, mid_len(g), list,
-                       (int32_t*)(g->ws + L.glmid), ctl);
+    hipLaunchKernelGGL(k_gl_heavy_list, dim3(grid), dim3(256), 0, s, g->dg.row_ptr, g->dg.n, mid_len(g),
+                       held_entries(small_rows(g->dg.n)), list, (int32_t*)(g->ws + L.glmid), ctl);
     hipLaunchKernelGGL(k_gl_plan, dim3(1), dim3(1024), 0, s, g->dg.row_ptr, list, ctl, first, items);
   }
-  uint32_t cnt[3] = {0, 0, 0};
+  uint32_t cnt[4] = {0, 0, 0, 0};
   hipError_t e = hipMemcpyAsync(cnt, ctl, sizeof(cnt), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   g->gl_nheavy = (int32_t)cnt[0];
   g->gl_nitems = (int32_t)cnt[1];
   g->gl_nmid = (int32_t)cnt[2];
+  g->gl_longer = cnt[3] != 0;
   return e == hipSuccess ? hipGetLastError() : e;
 }
 
@@ -1085,12 +1091,12 @@ template <int Q>
 hipError_t descend_small(fi_graph* g, int32_t ncomp, int groups, int32_t R, float alpha, int64_t steps,
                          int32_t shift, const float* start, float* gamma, int32_t* exps, hipStream_t s) {
   const size_t lds = small_lds<Q>(g, ncomp);
-  const auto f = g->gl_nheavy ? k_gl_descend_small<Q, true> : k_gl_descend_small<Q, false>;
+  const auto f = g->gl_longer ? k_gl_descend_small<Q, true> : k_gl_descend_small<Q, false>;
   const hipError_t e = hipFuncSetAttribute((const void*)f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(f, dim3(R), dim3(1024), lds, s, g->dg.row_ptr, g->dg.adj, g->dg.comp,
                      (const int32_t*)(g->ws + g->L.aslot), g->dg.n, ncomp, g->gl_nheavy, groups, (int)R, alpha,
-                     steps, (int)shift, g->gl_main_slot, start, gamma, exps);
+                     steps, (int)shift, g->gl_nheavy ? g->gl_main_slot : -1, start, gamma, exps);
   return hipGetLastError();
 }
 
@@ -1120,7 +1126,8 @@ int descend(fi_graph* g, const float* start, float* d_gamma, float* d_work, int3
              [&](auto p, auto) { groups = kGLBlock / decltype(p)::value; });
   if (g->dg.n <= kSmallDescentN && g->dg.nnz <= (g->gl_nheavy ? kSmallEntries / 2 : kSmallEntries) &&
       small_lds<4>(g, ncomp) <= kSmallDescentLds && !long_rows_wait(g, R, groups)) {
-    const auto f = g->dg.n <= 1024 ? descend_small<1> : g->dg.n <= 2048 ? descend_small<2> : descend_small<4>;
+    const int q = small_rows(g->dg.n);
+    const auto f = q == 1 ? descend_small<1> : q == 2 ? descend_small<2> : descend_small<4>;
     return f(g, ncomp, groups, R, alpha, steps, rescale_log2, start, d_gamma, (int32_t*)aux, s) == hipSuccess
                ? FI_OK
                : FI_EDEVICE;
