@@ -48,7 +48,7 @@ struct RdfsArgs {
   uint32_t cus;
   // with the hybrid's BFS trees in the same launch:
   int ntree;              // randomized DFS trees of a workgroup at a time
-  uint32_t dfs;           // workgroups of them, the first ones
+  uint32_t dfs;           // workgroups of them, the first ones; 0: each has one tree of either kind
   int32_t later;          // BFS in LDS: vertices that are not a root and have an edge
   char* bfs_slots;        // else per workgroup, words and queue
   size_t bfs_stride;
@@ -93,8 +93,8 @@ __device__ __forceinline__ uint32_t least_key(uint32_t x, bool few) {
 // CSR: the graph's row offsets and adjacency in LDS, once per workgroup; LINKS
 // (without CSR): entries read with their neighbour's row; STK: the tree's stack
 // in LDS; MARKS: its marks in LDS; SHARED (with MARKS): R.share waves to a tree.
-// BFS: the workgroups past R.dfs, all of kBothThreads threads, take the hybrid's
-// other trees, so that neither kind waits for the other (a path of 13,000, 100 trees
+// BFS: the workgroups past R.dfs, or with no such line those of a BFS tree, take the
+// hybrid's other trees (all are of kBothThreads threads), so that neither kind waits for the other (a path of 13,000, 100 trees
 // 32.7 ms in two launches, 27.3 here; of 2,000 2,020 us and 1,230; 50 / 100, 500 trees
 // 69 and 53).
 constexpr int kBothThreads = 256;
@@ -104,7 +104,9 @@ template <bool CSR, bool LINKS, bool STK, bool MARKS, bool SHARED, int BFS>
 __global__ void __launch_bounds__(BFS ? kBothThreads : 1024) k_sweep_rdfs(DevGraph G, SweepArgs A, RdfsArgs R) {
   extern __shared__ __align__(16) uint32_t sm[];
   if constexpr (BFS != kNoBfs) {
-    if (blockIdx.x >= R.dfs) {
+    const bool own = R.dfs == 0;  // a tree per workgroup, of either kind
+    if (own ? A.t0 + blockIdx.x < A.t1 && !wg::hybrid_coin(tree_salt(A.seed, A.t0 + blockIdx.x))
+            : blockIdx.x >= R.dfs) {
       const uint32_t b = blockIdx.x - R.dfs, step = gridDim.x - R.dfs;
       if constexpr (BFS == kBfsLds) {
         __shared__ wg::EShared<kBothThreads> sh;
@@ -119,7 +121,7 @@ __global__ void __launch_bounds__(BFS ? kBothThreads : 1024) k_sweep_rdfs(DevGra
       return;
     }
   }
-  const uint32_t blocks = BFS ? R.dfs : gridDim.x;
+  const uint32_t blocks = BFS && R.dfs ? R.dfs : gridDim.x;
   __shared__ uint32_t s_next[kRdfsStatic / 4];  // per tree of the workgroup: components handed out
   // the wave's tree among the workgroup's `ntree`, and which of the tree's waves
   // it is: the first takes the first component, mostly the longest, so those of
@@ -387,7 +389,7 @@ hipError_t rdfs_run(fi_graph* g, const SweepArgs& a, const RdfsArgs& r, int tree
 }
 
 // Both kinds of the hybrid's trees in one launch, while its workgroups are resident
-// at once (half of those of one tree at a time find none); *both: whether it was made.
+// at once (half of the BFS trees' find none); *both: whether it was made.
 template <bool CSR, bool LINKS, bool STK, bool MARKS, bool SHARED, int BFS>
 hipError_t both_run(fi_graph* g, const SweepArgs& a, RdfsArgs r, size_t lds, size_t region, bool* both,
                     hipStream_t s) {
@@ -402,9 +404,10 @@ hipError_t both_run(fi_graph* g, const SweepArgs& a, RdfsArgs r, size_t lds, siz
   e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, kBothThreads, lds);
   if (e != hipSuccess) return e;
   const uint64_t trees = a.t1 - a.t0, dfs = (trees + r.ntree - 1) / r.ntree;
-  if ((r.ntree == 1 ? dfs : 2 * dfs) + trees > 2 * (uint64_t)per_cu * g->cu_count) return hipSuccess;
+  const bool own = r.ntree == 1;
+  if (own ? trees > (uint64_t)per_cu * g->cu_count : 2 * dfs + trees > 2 * (uint64_t)per_cu * g->cu_count)
+    return hipSuccess;
   const size_t used = STK && MARKS ? 0 : dfs * r.ntree * r.slot_stride;
-  uint64_t bfs = trees;
   if (BFS == kBfsSlots) {
     if (used > region || (region - used) / g->L.slot_stride < trees) return hipSuccess;
     r.bfs_slots = r.slots + used;
@@ -412,9 +415,9 @@ hipError_t both_run(fi_graph* g, const SweepArgs& a, RdfsArgs r, size_t lds, siz
   } else if (used) {
     return hipSuccess;
   }
-  r.dfs = (uint32_t)dfs;
+  r.dfs = own ? 0 : (uint32_t)dfs;
   r.later = g->dg.n - g->nisolated - g->nanch;
-  hipLaunchKernelGGL(f, dim3((unsigned)(dfs + bfs)), dim3(kBothThreads), lds, s, g->dg, a, r);
+  hipLaunchKernelGGL(f, dim3((unsigned)(r.dfs + trees)), dim3(kBothThreads), lds, s, g->dg, a, r);
   *both = true;
   return hipGetLastError();
 }
