@@ -7,6 +7,7 @@
 #include <stdint.h>
 #include <stddef.h>
 
+#include <algorithm>
 #include <mutex>
 #include <vector>
 
@@ -230,9 +231,10 @@ constexpr int kMSplit = 2048;     // rows longer than this are split into units 
 constexpr int64_t kMultiMinWork = 20000;
 constexpr int64_t kDeepWork = 135000;
 constexpr int32_t kDeepLevels = 64;   // deep whatever the work
-// deep with less work than this per level and tree, among so few and so many trees
-constexpr int64_t kDeepPerLevel = 615000;
-constexpr uint64_t kDeepFewTrees = 400, kDeepManyTrees = 1000;
+// deep with so much less work per level than this among a few trees, fewer and many
+constexpr int64_t kDeepPerLevel = 1540, kDeepLone = 1000, kDeepMost = 615;
+constexpr uint64_t kDeepLoneTrees = 16, kDeepFewTrees = 400, kDeepManyTrees = 1000;
+constexpr int64_t kDeepLeast = 8000;  // work that is deep at any level
 constexpr int kMSets = 8;         // passes in flight on the multi-tree path (max)
 constexpr int kMCtlWords = 1024;  // control words of a pass
 constexpr int kBigComp = 1024;    // components larger than this find their roots in chunks
@@ -341,10 +343,16 @@ inline bool bfs_fits_lds(const fi_graph* g) {
 // 60,000 1,940 and 3,210 at 55 (66,000); where most vertices are alone, 13,200 with
 // 2,900 edges, 211 and 168 at 4.  With more trees than the CUs hold at once, one per
 // workgroup takes longer (the 18,000: 300 798 and 757, 1,000 971 and 1,509; 1,000 of
-// the 13,000: 1,180 and 1,650 at 27 levels, 3,630 and 1,870 at 96).
+// the 13,000: 1,180 and 1,650 at 27 levels, 3,630 and 1,870 at 96), and a few do
+// not fill a pass (the 18,000: 1 479 and 541, 10 534 and 566).  In a few thousand edges and
+// vertices a tree costs little beside a pass's barriers.
 inline int64_t deep_line(const fi_graph* g, uint64_t trees) {
-  const int64_t k = (int64_t)(trees < kDeepFewTrees ? kDeepFewTrees : trees < kDeepManyTrees ? trees : kDeepManyTrees);
-  const int64_t line = ((int64_t)g->dg.n - g->nisolated + g->dg.m) * k / kDeepPerLevel;
-  return line < kDeepLevels ? line : kDeepLevels;
+  const int64_t work = (int64_t)g->dg.n - g->nisolated + g->dg.m;
+  if (work < kDeepLeast) return 0;
+  const int64_t many = (int64_t)std::min(trees, kDeepManyTrees);
+  const int64_t line = trees <= kDeepLoneTrees  ? work / kDeepLone
+                       : trees < kDeepFewTrees ? work / kDeepPerLevel
+                                               : work * many / (kDeepMost * (int64_t)kDeepManyTrees);
+  return std::min<int64_t>(line, kDeepLevels);
 }
 }  // namespace fi

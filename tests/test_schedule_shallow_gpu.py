@@ -48,7 +48,8 @@ def _us(G, trees, path):
 
 
 @pytest.mark.parametrize("sizes,edges,alone,trees", [((600, 480), 1800, 12100, 64), ((600, 480), 1800, 12100, 130),
-                                                     ((6700, 1000, 430), 0, 9500, 130), ((14000,), 60000, 0, 100)])
+                                                     ((6700, 1000, 430), 0, 9500, 130), ((14000,), 60000, 0, 100),
+                                                     ((600, 480), 1800, 12100, 1000), ((14000,), 0, 0, 7)])
 def test_path_of_shallow_graphs(sizes, edges, alone, trees):
     g = _parts(sizes, edges, alone, 3)
     G = fr.Graph(g.row_ptr, g.col, g.sign, cloud_capacity=2 * trees)
