@@ -29,9 +29,10 @@ using wg::amin64;
 // and the trees run beside one another: a wave per tree, its marks in LDS, and
 // the stack and the CSR there too while they fit; with the CSR in global memory
 // a neighbour's row bounds come with its entry (links).  A hub is scanned again
-// at every return to it, with four loads per lane in flight (a star of 99 leaves
-// 122 us, 144 with eight, of 999 2,080 and 1,910; 20,000 / 100,000 with hubs, 64
-// trees 15.0 ms and 15.4).  Backing up looks
+// at every return to it, with four loads per lane in flight, eight in rows of more
+// entries than those (a star of 99 leaves 124 us, with eight everywhere 144; of 999
+// 2,000, with four 2,080; 20,000 / 100,000 with hubs, 64 trees 14.9 ms and 15.3 with
+// eight).  Backing up looks
 // at four stack entries at a time, and the search ends with the last vertex
 // instead of unwinding.  Components are chains of their own, so while a CU has
 // few trees, a tree's components go to several waves.  1,000 trees of n = 1,000,
@@ -61,6 +62,7 @@ __host__ __device__ constexpr int32_t stack_words(int32_t n) { return (n + 1) / 
 constexpr int32_t kStackMaxN = 1 << 16;
 constexpr size_t kRdfsStatic = 64;  // LDS bytes beside the trees'
 constexpr int kRdfsBatch = 4;  // loads of a long row in flight per lane
+constexpr int kRdfsMore = 8;   // of a longer one than those
 constexpr int kRdfsCount = 8;  // and of edges counted
 
 // An adjacency entry together with its neighbour's row: x = vertex | its
@@ -252,19 +254,38 @@ __global__ void __launch_bounds__(BFS ? kBothThreads : 1024) k_sweep_rdfs(DevGra
         } else {
           uint32_t ck = ~0u, ca = 0;
           bool has = false;
-          for (int32_t c = lane; c - lane < d; c += 64 * kRdfsBatch) {
-            uint32_t a[kRdfsBatch], w[kRdfsBatch];
+          if (d <= 64 * kRdfsBatch) {
+            for (int32_t c = lane; c - lane < d; c += 64 * kRdfsBatch) {
+              uint32_t a[kRdfsBatch], w[kRdfsBatch];
 #pragma unroll
-            for (int q = 0; q < kRdfsBatch; ++q) a[q] = adj[e0 + min(c + 64 * q, d - 1)];
+              for (int q = 0; q < kRdfsBatch; ++q) a[q] = adj[e0 + min(c + 64 * q, d - 1)];
 #pragma unroll
-            for (int q = 0; q < kRdfsBatch; ++q) w[q] = visited((int32_t)(a[q] & kVertexMask));
+              for (int q = 0; q < kRdfsBatch; ++q) w[q] = visited((int32_t)(a[q] & kVertexMask));
 #pragma unroll
-            for (int q = 0; q < kRdfsBatch; ++q) {
-              const uint32_t key = vkey(km, a[q] & kVertexMask);
-              if (!w[q] && (!has || key < ck)) {
-                ck = key;
-                ca = a[q];
-                has = true;
+              for (int q = 0; q < kRdfsBatch; ++q) {
+                const uint32_t key = vkey(km, a[q] & kVertexMask);
+                if (!w[q] && (!has || key < ck)) {
+                  ck = key;
+                  ca = a[q];
+                  has = true;
+                }
+              }
+            }
+          } else {
+            for (int32_t c = lane; c - lane < d; c += 64 * kRdfsMore) {
+              uint32_t a[kRdfsMore], w[kRdfsMore];
+#pragma unroll
+              for (int q = 0; q < kRdfsMore; ++q) a[q] = adj[e0 + min(c + 64 * q, d - 1)];
+#pragma unroll
+              for (int q = 0; q < kRdfsMore; ++q) w[q] = visited((int32_t)(a[q] & kVertexMask));
+#pragma unroll
+              for (int q = 0; q < kRdfsMore; ++q) {
+                const uint32_t key = vkey(km, a[q] & kVertexMask);
+                if (!w[q] && (!has || key < ck)) {
+                  ck = key;
+                  ca = a[q];
+                  has = true;
+                }
               }
             }
           }
