@@ -36,7 +36,7 @@ using wg::amin64;
 // at four stack entries at a time, and the search ends with the last vertex
 // instead of unwinding.  Components are chains of their own, so while a CU has
 // few trees, a tree's components go to several waves.  1,000 trees of n = 1,000,
-// m = 5,000: 0.46 ms, that is 0.46 us a vertex (a workgroup per tree, its waves
+// m = 5,000: 0.45 ms, that is 0.45 us a vertex (a workgroup per tree, its waves
 // but one idle: 0.97); 4,000 / 16,000: 2.2 ms (7.6); 500 trees of 20,000 /
 // 100,000: 15.7 (36.7).
 struct RdfsArgs {
